@@ -830,8 +830,9 @@ ep_result_t ep_dispatch(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_in
         return EP_SUCCESS;
     }
 
-    // Once per destination rank: send to the staging windows, rank the header entries on
-    // the receiving side, fan out to the expert rows.
+    // Once per destination rank: send to the staging windows and expand to the expert rows.  In one
+    // launch when the call is not split; otherwise the receive phase (ep_complete) ranks the header
+    // entries that have arrived and fans the messages out.
     const ep_tensor_t* ti = find_tag(inputs, num_inputs, EP_TAG_TOPK_IDX);
     if (!check_2d(ti, EP_DTYPE_I32, h->T, c.top_k, true)) return EP_ERR_INVALID_ARG;
     const Slab& s = h->slab;
@@ -845,15 +846,19 @@ ep_result_t ep_dispatch(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_in
     sa.hdr_units = (int)(g->hdr_bytes / 16);
     sa.totals = s.totals;
     sa.T = h->T; sa.K = c.top_k; sa.H = c.hidden;
+    if (!send_only) {
+        const DedupExpandArgs xa = {s.dst_row, s.expert_kept, a.win, a.recv_w, a.recv_src, a.recv_count, c.num_experts};
+        return launch_dedup_send_expand(sa, xa, (hipStream_t)stream) == hipSuccess ? EP_SUCCESS : EP_ERR_HIP;
+    }
     if (launch_dedup_send(sa, (hipStream_t)stream) != hipSuccess) return EP_ERR_HIP;
 
     DedupRankArgs ra;
     ra.staging = g->staging[set]; ra.msg_stride = g->msg_stride; ra.msg_lead = g->msg_lead;
     ra.staging_slots = g->staging_slots;
     ra.slots_per_rank = c.mode == EP_MODE_LL ? c.max_tokens_per_rank : 0;
-    // a staged call lets the receiving side learn the message counts from the counters
-    ra.rank_offset = send_only ? s.recv_rank_offset : s.rank_offset;
-    ra.rank_count = send_only ? s.recv_rank_count : s.rank_token_count;
+    // the receiving side learns the message counts from the counters
+    ra.rank_offset = s.recv_rank_offset;
+    ra.rank_count = s.recv_rank_count;
     ra.expert_offset = s.expert_offset;
     ra.recv_dst_row = s.recv_dst_row; ra.recv_count = s.recv_count; ra.recv_kept = s.recv_kept;
     ra.K = c.top_k; ra.E = c.num_experts; ra.R = c.num_ranks; ra.L = g->L; ra.L_shift = g->L_shift;
@@ -869,17 +874,13 @@ ep_result_t ep_dispatch(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_in
     fa.win = a.win; fa.recv_w = a.recv_w; fa.recv_src = a.recv_src; fa.recv_count = a.recv_count;
     fa.totals = s.totals;
     fa.K = c.top_k; fa.H = c.hidden; fa.E = c.num_experts; fa.R = c.num_ranks;
-    if (send_only) {
-        if (launch_publish_counts(g->sig_rank(set), s.rank_token_count, c.num_ranks, (hipStream_t)stream) != hipSuccess)
-            return EP_ERR_HIP;
-        h->pending = PENDING_DISPATCH_DEDUP;
-        h->pending_set = set;
-        h->pending_rank = ra;
-        h->pending_fanout = fa;
-        return EP_SUCCESS;
-    }
-    if (launch_dedup_rank(ra, (hipStream_t)stream) != hipSuccess) return EP_ERR_HIP;
-    return launch_dedup_fanout(fa, (hipStream_t)stream) == hipSuccess ? EP_SUCCESS : EP_ERR_HIP;
+    if (launch_publish_counts(g->sig_rank(set), s.rank_token_count, c.num_ranks, (hipStream_t)stream) != hipSuccess)
+        return EP_ERR_HIP;
+    h->pending = PENDING_DISPATCH_DEDUP;
+    h->pending_set = set;
+    h->pending_rank = ra;
+    h->pending_fanout = fa;
+    return EP_SUCCESS;
 }
 
 ep_result_t ep_layout_dispatch(ep_handle_t* handle, ep_group_t g, const ep_tensor_t* topk_idx,

@@ -152,6 +152,17 @@ struct DedupSendArgs {
     int T, K, H;
 };
 
+// What the once-per-rank send needs to place the expert rows as well.
+struct DedupExpandArgs {
+    const int32_t* dst_row;      // [T, K]
+    const int32_t* expert_kept;  // [E]
+    WindowDesc win;
+    float* recv_w;
+    int32_t* recv_src;
+    int32_t* recv_count;
+    int E;
+};
+
 struct DedupFanoutArgs {
     const uint8_t* staging;
     int64_t msg_stride, msg_lead, hdr_bytes;
@@ -194,6 +205,8 @@ bool layout_dispatch_fusable(const LayoutArgs& a, const DispatchArgs& d);
 hipError_t launch_layout_dispatch(const LayoutArgs& a, const DispatchArgs& d, hipStream_t s);
 hipError_t launch_dedup_rank(const DedupRankArgs& a, hipStream_t s);
 hipError_t launch_dedup_send(const DedupSendArgs& a, hipStream_t s);
+// Send and expansion in one launch, for calls that are not split into phases.
+hipError_t launch_dedup_send_expand(const DedupSendArgs& a, const DedupExpandArgs& x, hipStream_t s);
 hipError_t launch_dedup_fanout(const DedupFanoutArgs& a, hipStream_t s);
 hipError_t launch_dispatch(const DispatchArgs& a, hipStream_t s);
 hipError_t launch_dispatch_fp8(const DispatchArgs& a, float* recv_scales, hipStream_t s);

@@ -1356,6 +1356,45 @@ def test_once_per_rank_dispatch_parity(ep, hx, oracle_mod, name, T, H, mode, C, 
     assert not held
 
 
+@pytest.mark.parametrize("T,H,R,E,K,mode,C", [
+    (900, 64, 1, 64, 4, "ht", 0),      # one window of several passes per wave
+    (333, 64, 4, 24, 3, "ll", 50),     # K and L not powers of two, capacity drops
+    (130, 1000, 16, 128, 64, "ht", 0),  # headers of 64 ids
+    (1, 72, 2, 8, 2, "ht", 0),
+])
+def test_once_per_rank_one_launch_equals_two_phases(ep, hx, oracle_mod, T, H, R, E, K, mode, C):
+    """The undivided dispatch places the rows by the layout's record, the receive phase of the divided
+    one by ranking the headers that arrived: same rows, weights, sources and counts, the oracle's."""
+    ll = mode == "ll"
+    w = wl.make_workload("ll_decode", T=T, H=H, R=R, E=E, K=K)
+    topk = _mess_up(w.topk_idx, E, seed=T, frac_masked=0.02)
+    lay = oracle_mod.layout(topk, E=E, R=R, layout=int(ll), C=C, C_rank=T)
+    rows = E * C if ll else int(lay.expert_offset[-1])
+    want = [np.full((rows, H), hx.POISON, np.uint16), np.full(rows, np.float32(-3.5)), np.full(rows, -9, np.int32)]
+    oracle_mod.dispatch(w.x_bits, w.topk_w, lay, *want)
+    g = ep.ep_group_create(ep.make_config(R, E, H, K, T, mode=ep.EP_MODE_LL if ll else ep.EP_MODE_HT, slots_per_subregion=C,
+                                          dispatch_path=ep.EP_PATH_RANK_DEDUP, staged_buffers=1))
+    try:
+        d_topk, d_w, x = torch.from_numpy(topk).to(hx.DEV), torch.from_numpy(w.topk_w).to(hx.DEV), hx.bits_to_dev(w.x_bits)
+        for send_only in (0, 1):
+            store = hx.poison_bf16((rows, H))
+            r_w = torch.full((rows,), -3.5, dtype=torch.float32, device=hx.DEV)
+            r_src = torch.full((rows,), -9, dtype=torch.int32, device=hx.DEV)
+            cnt = torch.full((E,), -1, dtype=torch.int32, device=hx.DEV)
+            h = ep.ep_layout(g, d_topk)
+            ep.ep_dispatch(h, x, store.view(E, C, H) if ll else store, topk_weights=d_w, recv_w=r_w, recv_src=r_src,
+                           recv_count=cnt, topk_idx=d_topk, send_only=send_only)
+            if send_only:
+                ep.ep_complete(h)
+            torch.cuda.synchronize()
+            assert np.array_equal(hx.dev_to_bits(store), want[0])
+            assert np.array_equal(r_w.cpu().numpy(), want[1]) and np.array_equal(r_src.cpu().numpy(), want[2])
+            assert np.array_equal(cnt.cpu().numpy(), lay.expert_kept)
+            ep.ep_handle_destroy(h)
+    finally:
+        ep.ep_group_destroy(g)
+
+
 # ------------------------------------------------------------------------------ quantising dispatch (FP8 + scales)
 
 FP8_CASES = [

@@ -522,6 +522,15 @@ EP_API ep_result_t ep_layout_dispatch(ep_handle_t *handle, ep_group_t group, con
 EP_API ep_result_t ep_combine_backward(ep_handle_t handle, const ep_tensor_t *inputs, int32_t num_inputs,
                                        const ep_tensor_t *outputs, int32_t num_outputs, ep_stream_t stream);
 
+/*
+ * ep_combine_backward_full -- ep_combine_backward whose grad_y may come uninitialised: the rows
+ * that no entry reaches become zero in the same launch (the tail of the concatenated layout, the
+ * unused slots of padded windows).  EP_ERR_UNSUPPORTED for a handle made with expert_base, whose
+ * rows lie among those of other sources.
+ */
+EP_API ep_result_t ep_combine_backward_full(ep_handle_t handle, const ep_tensor_t *inputs, int32_t num_inputs,
+                                            const ep_tensor_t *outputs, int32_t num_outputs, ep_stream_t stream);
+
 /* Options of ep_complete.  `size` must be sizeof(ep_complete_config_t). */
 typedef struct {
     uint32_t size;

@@ -49,7 +49,7 @@ STATUS_INVALID_IDS, STATUS_CAPACITY_DROP, STATUS_OUTPUT_OVERFLOW, STATUS_TIMEOUT
 EXPORTS = [
     "ep_error_string", "ep_version", "ep_build_id", "ep_layout_plan", "ep_dispatch_plan", "ep_combine_plan", "ep_calibration_copy", "ep_calibration_fill", "ep_calibration_read", "ep_group_create", "ep_group_destroy", "ep_group_query",
     "ep_layout", "ep_layout_prefetch", "ep_layout_static", "ep_layout_dispatch", "ep_handle_query", "ep_handle_get_num_recv_tokens", "ep_handle_destroy",
-    "ep_dispatch", "ep_combine", "ep_combine_backward", "ep_complete", "ep_group_reset_signals",
+    "ep_dispatch", "ep_combine", "ep_combine_backward", "ep_combine_backward_full", "ep_complete", "ep_group_reset_signals",
 ]
 
 
@@ -161,7 +161,8 @@ def load() -> ctypes.CDLL:
         lib.ep_handle_destroy.argtypes = [vp]
         for fn in (lib.ep_dispatch, lib.ep_combine):
             fn.argtypes = [vp, ctypes.POINTER(ep_tensor_t), i32, ctypes.POINTER(ep_tensor_t), i32, i32, vp]
-        lib.ep_combine_backward.argtypes = [vp, ctypes.POINTER(ep_tensor_t), i32, ctypes.POINTER(ep_tensor_t), i32, vp]
+        for fn in (lib.ep_combine_backward, lib.ep_combine_backward_full):
+            fn.argtypes = [vp, ctypes.POINTER(ep_tensor_t), i32, ctypes.POINTER(ep_tensor_t), i32, vp]
         lib.ep_calibration_copy.argtypes = [vp, vp, ctypes.c_size_t, vp]
         lib.ep_calibration_fill.argtypes = [vp, ctypes.c_size_t, vp]
         lib.ep_calibration_read.argtypes = [vp, ctypes.c_size_t, vp, vp]
@@ -427,6 +428,16 @@ def ep_combine(handle, y: torch.Tensor, out: torch.Tensor, topk_weights: Optiona
 def ep_combine_backward(handle, grad_out: torch.Tensor, grad_y: torch.Tensor, topk_weights: Optional[torch.Tensor] = None,
                         y: Optional[torch.Tensor] = None, grad_w: Optional[torch.Tensor] = None, stream=None) -> None:
     """Backward of the weighted combine: grad_y (windows) and, when y is given, grad_w [T, K]."""
+    _combine_backward("ep_combine_backward", handle, grad_out, grad_y, topk_weights, y, grad_w, stream)
+
+
+def ep_combine_backward_full(handle, grad_out: torch.Tensor, grad_y: torch.Tensor, topk_weights: Optional[torch.Tensor] = None,
+                             y: Optional[torch.Tensor] = None, grad_w: Optional[torch.Tensor] = None, stream=None) -> None:
+    """ep_combine_backward into a grad_y that may be uninitialised: rows without an entry become zero."""
+    _combine_backward("ep_combine_backward_full", handle, grad_out, grad_y, topk_weights, y, grad_w, stream)
+
+
+def _combine_backward(name, handle, grad_out, grad_y, topk_weights, y, grad_w, stream) -> None:
     ins = [(grad_out, EP_TAG_TOKENS)]
     if topk_weights is not None:
         ins.append((topk_weights, EP_TAG_TOPK_WEIGHTS))
@@ -435,8 +446,7 @@ def ep_combine_backward(handle, grad_out: torch.Tensor, grad_y: torch.Tensor, to
     outs = [(grad_y, EP_TAG_TOKENS)]
     if grad_w is not None:
         outs.append((grad_w, EP_TAG_TOPK_WEIGHTS))
-    _check(load().ep_combine_backward(handle, _descs(ins), len(ins), _descs(outs), len(outs), _stream_ptr(stream)),
-           "ep_combine_backward")
+    _check(getattr(load(), name)(handle, _descs(ins), len(ins), _descs(outs), len(outs), _stream_ptr(stream)), name)
 
 
 class PreparedCall:

@@ -149,13 +149,13 @@ class EPBuffer:
         sp = self.comm_stream.cuda_stream
         with torch.cuda.stream(self.comm_stream):
             if y is not None:
-                grad_y = torch.zeros(y.shape, dtype=torch.bfloat16, device=self.device)
+                grad_y = torch.empty(y.shape, dtype=torch.bfloat16, device=self.device)
             else:
                 rows = self.E * self.C if self.ll else handle.num_tokens * self.K
-                store = torch.zeros((rows, self.H), dtype=torch.bfloat16, device=self.device)
+                store = torch.empty((rows, self.H), dtype=torch.bfloat16, device=self.device)
                 grad_y = store.view(self.E, self.C, self.H) if self.ll else store
             grad_w = torch.empty((handle.num_tokens, self.K), dtype=torch.float32, device=self.device) if y is not None else None
-            ep.ep_combine_backward(handle.raw, grad_out, grad_y, topk_weights=topk_weights, y=y, grad_w=grad_w, stream=sp)
+            ep.ep_combine_backward_full(handle.raw, grad_out, grad_y, topk_weights=topk_weights, y=y, grad_w=grad_w, stream=sp)
             for t in (grad_out, grad_y) + ((y, grad_w) if y is not None else ()):
                 t.record_stream(self.comm_stream)
         return grad_y, grad_w, self._leave()

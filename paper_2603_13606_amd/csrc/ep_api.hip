@@ -1053,8 +1053,8 @@ ep_result_t ep_layout_static(const ep_group_config_t* cfg, const ep_tensor_t* to
     return launch_layout(a, (hipStream_t)stream) == hipSuccess ? EP_SUCCESS : EP_ERR_HIP;
 }
 
-ep_result_t ep_combine_backward(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_inputs,
-                                const ep_tensor_t* outputs, int32_t num_outputs, ep_stream_t stream) {
+static ep_result_t combine_backward(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_inputs,
+                                    const ep_tensor_t* outputs, int32_t num_outputs, bool clear, ep_stream_t stream) {
     if (!h || !inputs || !outputs || num_inputs < 1 || num_outputs < 1) return EP_ERR_INVALID_ARG;
     if (has_scales(inputs, num_inputs) || has_scales(outputs, num_outputs)) return EP_ERR_UNSUPPORTED;
     ep_group_s* g = h->group;
@@ -1085,9 +1085,22 @@ ep_result_t ep_combine_backward(ep_handle_t h, const ep_tensor_t* inputs, int32_
     a.out = nullptr; a.out_stride = 0;
     a.T = h->T; a.K = c.top_k; a.H = c.hidden;
     a.staged = 0; a.entry_rank = nullptr; a.ranks_per_node = 0; a.nodes = 1;
+    // among another source's rows there is no telling which rows are nobody's
+    if (clear && h->expert_base) return EP_ERR_UNSUPPORTED;
+    const int32_t* reached = !clear ? nullptr : gyw.padded ? h->slab.expert_kept : h->slab.totals + TOT_ROWS_END;
     h->last_stream = (hipStream_t)stream;
     return launch_combine_backward(a, (const uint16_t*)go->data, go->stride[0], gyw, gw ? (float*)gw->data : nullptr,
-                                   gw ? gw->stride[0] : 0, (hipStream_t)stream) == hipSuccess ? EP_SUCCESS : EP_ERR_HIP;
+                                   gw ? gw->stride[0] : 0, reached, (hipStream_t)stream) == hipSuccess ? EP_SUCCESS : EP_ERR_HIP;
+}
+
+ep_result_t ep_combine_backward(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_inputs,
+                                const ep_tensor_t* outputs, int32_t num_outputs, ep_stream_t stream) {
+    return combine_backward(h, inputs, num_inputs, outputs, num_outputs, false, stream);
+}
+
+ep_result_t ep_combine_backward_full(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_inputs,
+                                     const ep_tensor_t* outputs, int32_t num_outputs, ep_stream_t stream) {
+    return combine_backward(h, inputs, num_inputs, outputs, num_outputs, true, stream);
 }
 
 }  // extern "C"

@@ -228,8 +228,10 @@ struct CombinePlan {
 void plan_combine(int64_t T, int H, int ranks_per_node, int compute_units, CombinePlan* out);
 // Backward of the weighted combine: a.win = expert outputs y (base may be nullptr: no grad_w), a.w, a.dst_row,
 // T, K, H as for the forward; g = gradient of the combined output [T, H]; gy = windows for grad_y.
+// `reached`, when given: the rows of gy without an entry are set to zero; concatenated windows: it points
+// to the number of leading rows that have entries; padded: to the kept entries per expert.
 hipError_t launch_combine_backward(const CombineArgs& a, const uint16_t* g, int64_t g_stride, const WindowDesc& gy,
-                                   float* grad_w, int64_t gw_stride, hipStream_t s);
+                                   float* grad_w, int64_t gw_stride, const int32_t* reached, hipStream_t s);
 hipError_t launch_publish_counts(int32_t* sig, const int32_t* counts, int n, hipStream_t s);
 hipError_t launch_await_counts(int32_t* sig, int n, int spin_limit, int32_t* count_out, int32_t* offset_out,
                                int32_t* totals, hipStream_t s);

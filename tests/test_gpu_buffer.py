@@ -130,6 +130,46 @@ def test_backward_calls_match_the_oracle_composition(hx, oracle_mod, name, T, H,
         buf.close()
 
 
+@pytest.mark.parametrize("E,T,C", [(8, 40, 0), (8, 40, 3), (8, 40, 90), (96, 7, 5), (768, 30, 4), (8, 0, 0), (8, 0, 4)])
+def test_backward_clears_exactly_the_rows_without_an_entry(hx, oracle_mod, E, T, C):
+    """ep_combine_backward_full into poisoned windows: rows of entries as ep_combine_backward leaves them,
+    every other row zero, nothing outside the rows (a strided window); C = 0 is the concatenated layout.  More
+    experts than the clearing workgroups (768), a number that does not divide them (96), empty inputs."""
+    from paper_2603_13606_amd import binding as ep
+    H, K, B = 136, 4, max(T, 1)
+    gen = torch.Generator(hx.DEV).manual_seed(E + T)
+    topk = torch.randint(0, E, (T, K), generator=gen, device=hx.DEV, dtype=torch.int32)
+    topk[::5, 1] = -1
+    lay = oracle_mod.layout(topk.cpu().numpy(), E=E, R=8, layout=int(C > 0), C=C or B, C_rank=B)
+    cfg = ep.make_config(8, E, H, K, B, mode=ep.EP_MODE_LL if C else ep.EP_MODE_HT, slots_per_subregion=C)
+    group = ep.ep_group_create(cfg)
+    try:
+        h = ep.ep_layout(group, topk)
+        rows = E * C if C else B * K + 3
+        g = torch.randn((T, H), generator=gen, device=hx.DEV).bfloat16()
+        store = torch.full((rows, H + 8), 7.0, dtype=torch.bfloat16, device=hx.DEV)
+        plain = store.clone()
+        win = lambda s: (s.view(E, C, H + 8) if C else s)[..., :H]
+        ep.ep_combine_backward_full(h, g, win(store))
+        ep.ep_combine_backward(h, g, win(plain))
+        torch.cuda.synchronize()
+        reached = np.zeros(rows, bool)
+        reached[lay.dst_row[lay.dst_row >= 0]] = True
+        want = plain.cpu()
+        want[torch.from_numpy(~reached), :H] = 0
+        assert torch.equal(store.cpu(), want)
+        assert np.all(want[torch.from_numpy(~reached), H:].float().numpy() == 7.0)
+        ep.ep_handle_destroy(h)
+        if not C:  # among another source's rows: refused
+            h = ep.ep_layout(group, topk, expert_base=torch.zeros(E, dtype=torch.int32, device=hx.DEV))
+            with pytest.raises(ep.EpError):
+                ep.ep_combine_backward_full(h, g, win(store))
+            ep.ep_handle_destroy(h)
+    finally:
+        torch.cuda.synchronize()
+        ep.ep_group_destroy(group)
+
+
 @pytest.mark.parametrize("mode", ["ht", "ll"])
 def test_buffer_autograd_reuses_handle(hx, oracle_mod, mode):
     """One handle through forward and backward of the autograd wrappers: the gradients that come

@@ -9,6 +9,7 @@
 // Bound by HBM: K rows read, one row written per token.  Work unit = one
 // wavefront reducing one 1 KiB segment of one token: every lane issues up to 8
 // independent 16-byte loads before it starts to accumulate.
+#include <algorithm>
 #include <atomic>
 
 #include "ep_internal.h"
@@ -289,8 +290,20 @@ __global__ __launch_bounds__(256) void combine_hier_kernel(CombineArgs a, int ns
 // tail of concatenated windows and the slots beyond the kept entries of padded ones.
 // Clearing whole windows before the launch took 58 us at 32768 rows of 14 336 bytes, all of
 // which were then written again; with every row reached these workgroups read one word.
+//
+// Large calls run as two launches of the same kernel, one for the weight gradients (reads
+// only) and one for the rows: a read stream next to a stream of randomly placed writes
+// reaches 4.8 TB/s, reads alone 6.6 and such writes alone 4.9 (at 4096 x 7168, top-8: 195 us in one
+// launch, 174 in two, with g read twice).  Same order of every sum either way.
 constexpr int KBB = 8;  // entries handled together
 constexpr int kClearBlocks = 256;
+// Two launches from this many bytes of rows and this many entries per token on (us in two / in one,
+// rows of 14 336 bytes unless given): top-8 26.3/26.7 at 59 MB, 40.2/42.0 at 98 MB, 46.8/50.1 at
+// 117 MB; rows of 2048 bytes 32.0/30.5 at 67 MB, of 5760 top-6 42.6/43.9 at 104 MB; top-4 43.1/44.6 at
+// 98 MB, 94/102 at 235 MB; top-3 75.3/73.3 at 176 MB, top-2 62/54 at 117 MB: there g, read once
+// more, is too large a part.
+constexpr int64_t kSplitBackwardBytes = 88ll << 20;
+constexpr int kSplitBackwardMinEntries = 4;
 
 __device__ void clear_unreached_rows(const WindowDesc& gy, const int32_t* reached, int units, int b) {
     const u32x4 zero = {0u, 0u, 0u, 0u};
@@ -312,6 +325,7 @@ __device__ void clear_unreached_rows(const WindowDesc& gy, const int32_t* reache
     }
 }
 
+template <bool ROWS, bool WEIGHTS>
 __global__ __launch_bounds__(256) void combine_backward_kernel(CombineArgs a, const uint16_t* g, int64_t g_stride,
                                                                WindowDesc gy, float* grad_w, int64_t gw_stride, int units,
                                                                const int32_t* reached) {
@@ -344,14 +358,14 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(CombineArgs a, co
                 if (j >= nk) row[b] = -1;
                 w[b] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), j & (kWave - 1)));
                 const int r = max(row[b], 0);
-                yrow[b] = a.win.base ? (const u32x4*)(a.win.base + window_offset(a.win, r)) : nullptr;
-                gyrow[b] = (u32x4*)(gy.base + window_offset(gy, r));
+                yrow[b] = WEIGHTS ? (const u32x4*)(a.win.base + window_offset(a.win, r)) : nullptr;
+                gyrow[b] = ROWS ? (u32x4*)(gy.base + window_offset(gy, r)) : nullptr;
                 dot[b] = 0.0f;
             }
             for (int u = threadIdx.x; u < units; u += blockDim.x) {
                 const u32x4 gv = grow[u];
                 u32x4 yv[KBB];
-                if (a.win.base) {
+                if (WEIGHTS) {
 #pragma unroll
                     for (int b = 0; b < KBB; ++b)
                         if (row[b] >= 0) yv[b] = __builtin_nontemporal_load(yrow[b] + u);
@@ -364,14 +378,14 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(CombineArgs a, co
                 }
 #pragma unroll
                 for (int b = 0; b < KBB; ++b) {
-                    if (row[b] < 0) continue;  // wave-uniform
+                    if (!ROWS || row[b] < 0) continue;  // wave-uniform
                     u32x4 o;
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
                         o[c] = pack_bf16(__fmul_rn(w[b], gf[2 * c]), __fmul_rn(w[b], gf[2 * c + 1]));
                     __builtin_nontemporal_store(o, gyrow[b] + u);
                 }
-                if (a.win.base) {
+                if (WEIGHTS) {
 #pragma unroll
                     for (int b = 0; b < KBB; ++b) {
                         if (row[b] < 0) continue;
@@ -383,7 +397,7 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(CombineArgs a, co
                     }
                 }
             }
-            if (grad_w) {  // uniform over the workgroup: every thread takes part
+            if (WEIGHTS) {  // uniform over the workgroup: every thread takes part
 #pragma unroll
                 for (int b = 0; b < KBB; ++b) {
                     float d = dot[b];
@@ -408,8 +422,18 @@ hipError_t launch_combine_backward(const CombineArgs& a, const uint16_t* g, int6
                                    float* grad_w, int64_t gw_stride, const int32_t* reached, hipStream_t s) {
     const unsigned nblk = (unsigned)a.T + (reached ? kClearBlocks : 0);
     if (nblk == 0) return hipSuccess;
-    hipLaunchKernelGGL(combine_backward_kernel, dim3(nblk), dim3(256), 0, s, a, g, g_stride, gy, grad_w, gw_stride, a.H / 8,
-                       reached);
+    const int units = a.H / 8;
+    auto launch = [&](auto kernel, unsigned blocks) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, a, g, g_stride, gy, grad_w, gw_stride, units, reached);
+    };
+    if (!a.win.base || a.T == 0) {
+        launch(combine_backward_kernel<true, false>, nblk);
+    } else if (a.K < kSplitBackwardMinEntries || std::min((int64_t)a.T * a.K, gy.rows_cap) * units * 16 < kSplitBackwardBytes) {
+        launch(combine_backward_kernel<true, true>, nblk);
+    } else {
+        launch(combine_backward_kernel<false, true>, (unsigned)a.T);
+        launch(combine_backward_kernel<true, false>, nblk);
+    }
     return hipGetLastError();
 }
 

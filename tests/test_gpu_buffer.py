@@ -170,6 +170,51 @@ def test_backward_clears_exactly_the_rows_without_an_entry(hx, oracle_mod, E, T,
         ep.ep_group_destroy(group)
 
 
+@pytest.mark.parametrize("C", [0, 100])
+def test_large_backward_gives_the_gradients_of_its_halves(hx, C):
+    """A call large enough for two launches (12 000 rows of 8 KiB, 98 MB) against the same tokens in two calls
+    of half the size (one launch each): bit for bit, concatenated and padded with entries cut."""
+    from paper_2603_13606_amd import binding as ep
+    E, T, H, K = 128, 1500, 4096, 8
+    gen = torch.Generator(hx.DEV).manual_seed(C)
+    topk = torch.randint(0, E, (T, K), generator=gen, device=hx.DEV, dtype=torch.int32)
+    topk[::7, 3] = -1
+    w = torch.rand((T, K), generator=gen, device=hx.DEV)
+    g = torch.randn((T, H), generator=gen, device=hx.DEV).bfloat16()
+    cfg = ep.make_config(8, E, H, K, T, mode=ep.EP_MODE_LL if C else ep.EP_MODE_HT, slots_per_subregion=C)
+    group = ep.ep_group_create(cfg)
+    rows = E * C if C else T * K
+    y = torch.randn((rows, H), generator=gen, device=hx.DEV).bfloat16()
+    shape = (E, C, H) if C else (rows, H)
+    try:
+        def run(lo, hi, src):
+            h = ep.ep_layout(group, topk[lo:hi])
+            dst = ep.read_device_i32(ep.ep_handle_query(h).dst_row, (hi - lo) * K).view(-1, K).to(hx.DEV).long()
+            ys = torch.zeros_like(y)
+            ys[dst[dst >= 0]] = src(dst)
+            gy, gw = torch.zeros_like(y), torch.empty((hi - lo, K), device=hx.DEV)
+            ep.ep_combine_backward(h, g[lo:hi], gy.view(shape), topk_weights=w[lo:hi], y=ys.view(shape), grad_w=gw)
+            torch.cuda.synchronize()
+            ep.ep_handle_destroy(h)
+            return dst, gy, gw
+        dst, gy, gw = run(0, T, lambda d: y[d[d >= 0]])
+        for lo, hi in ((0, T // 2), (T // 2, T)):
+            whole = dst[lo:hi]
+
+            def src(d):
+                part = torch.zeros((hi - lo, K, H), dtype=torch.bfloat16, device=hx.DEV)
+                part[whole >= 0] = y[whole[whole >= 0]]
+                return part[d >= 0]
+            d2, gy2, gw2 = run(lo, hi, src)
+            both = (whole >= 0) & (d2 >= 0)   # a capacity cuts other entries of a half
+            assert both.sum() >= (3000 if C else (topk[lo:hi] >= 0).sum())
+            assert torch.equal(gw[lo:hi][both], gw2[both])
+            assert torch.equal(gy[whole[both]], gy2[d2[both]])
+    finally:
+        torch.cuda.synchronize()
+        ep.ep_group_destroy(group)
+
+
 @pytest.mark.parametrize("mode", ["ht", "ll"])
 def test_buffer_autograd_reuses_handle(hx, oracle_mod, mode):
     """One handle through forward and backward of the autograd wrappers: the gradients that come

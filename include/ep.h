@@ -489,10 +489,11 @@ EP_API ep_result_t ep_combine(ep_handle_t handle, const ep_tensor_t *inputs, int
 /*
  * ep_layout_dispatch -- ep_layout (Table II "ncclEpCreateHandle") and ep_dispatch of the
  * tokens it was made for, in one call.  In the paper's low-latency kernels the token count
- * runs next to the send (Sec. IV-C); here an input of at most 1024 routed entries on the
- * direct path with bf16 rows is laid out and dispatched by ONE kernel launch: every
+ * runs next to the send (Sec. IV-C); here an input of at most 8192 routed entries on the
+ * direct path with bf16 rows (176 MiB of tokens and rows at most, not one that goes in
+ * destination order) is laid out and dispatched by ONE kernel launch: every
  * workgroup derives the layout from the few KB of ids in its own LDS and copies its share
- * of the rows, one workgroup also writes the handle's arrays.  Any other input runs the two
+ * of the rows, further workgroups write the handle's arrays.  Any other input runs the two
  * calls one after the other (the layout with the tokens announced, as ep_layout_prefetch
  * does).  Arguments, outputs, results and errors are those of ep_layout and ep_dispatch
  * (send_only = 0); on an error no handle is returned.

@@ -405,6 +405,16 @@ __device__ int write_tables(const LayoutArgs& a, const Lds& l, int tid, int lane
     return rows_end;
 }
 
+// One past the highest destination row of the concatenated layout.  One wavefront; must be called
+// by all 64 lanes.
+__device__ int last_row_end(const LayoutArgs& a, const Lds& l, int lane) {
+    if (!a.expert_base) return l.S[a.E];
+    int end = 0;
+    for (int e = lane; e < a.E; e += kWave)
+        if (l.tot[e] > 0) end = max(end, a.expert_base[e] + l.tot[e]);
+    return wave_max(end);
+}
+
 // The status word of the totals block.  One wavefront; must be called by all 64 lanes.
 __device__ void write_status(const LayoutArgs& a, const Lds& l, int lane, int extra_status) {
     int dropped = 0;
@@ -446,7 +456,6 @@ __device__ void warm_tokens(const LayoutArgs& a, int wb, int nwb) {
 }
 
 constexpr int kLookLimit = 1 << 19;  // rounds of polling after which a thread stops waiting (about a second)
-constexpr int HB = 32;               // chunks whose published words a thread loads in one batch (at most 32: bit masks)
 constexpr int kTagShift = 24;        // a published word is (tag << 24) | count: a chunk holds fewer than 2^24 entries
 constexpr uint32_t kCountMask = (1u << kTagShift) - 1u;
 constexpr uint32_t kTags = 255;      // tags 1 .. 255; 0 is what a cleared word holds
@@ -454,6 +463,7 @@ constexpr uint32_t kTags = 255;      // tags 1 .. 255; 0 is what a cleared word 
 // Loads the words chunks r0 .. r0+HB-1 have published for bin c.  Every lane loads from a
 // valid address (rows beyond the last chunk repeat it, their words are ignored later):
 // no branch, so all HB loads are in flight together.
+template <int HB>
 __device__ __forceinline__ void look_across(const LayoutArgs& a, int c, int r0, uint32_t (&v)[HB]) {
     const int last = a.nchunks - 1;
     const uint32_t* row = a.pub + (int64_t)min(r0, last) * a.W;  // wave-uniform: the row pointer steps in scalar registers
@@ -480,7 +490,8 @@ __device__ __forceinline__ void look_across(const LayoutArgs& a, int c, int r0, 
 // Tags never repeat between two clearings of pub, and the scratch starts out all zero,
 // which no launch uses as a tag.
 //
-// MULTI: more than one chunk.  ONE_GROUP: a wave's entries fit one load group (at most PU
+// HB: chunks whose published words a thread loads in one batch (at most 32: bit masks), 0 = there
+// is one chunk.  ONE_GROUP: a wave's entries fit one load group (at most PU
 // passes) and stay in registers from the histogram to the emit.
 // The same workgroups, for a group that quantises ahead: instead of only reading the token
 // rows they quantise them (the FP8 dispatch's format, see ep_fp8.h) into a staging copy, row t
@@ -507,7 +518,7 @@ __device__ void quantize_tokens(const LayoutArgs& a, int wb, int nwb) {
     }
 }
 
-template <bool MULTI, bool ONE_GROUP>
+template <int HB, bool ONE_GROUP>
 __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, const int b) {
     const int wpb = blockDim.x >> 6;
     const Lds l = carve_lds(lds, a, wpb);
@@ -518,7 +529,7 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
     const int wc = b * wpb + w;
     const int nchunks = a.nchunks;
     const bool active = wc < a.nwc;
-    constexpr bool one_group = ONE_GROUP, multi = MULTI;
+    constexpr bool one_group = ONE_GROUP, multi = HB > 0;
 
     // (1) the global loads this workgroup can issue at once: its own ids and the generation
     //     (first needed in (3): nothing here waits for it)
@@ -571,15 +582,15 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
     lds_barrier();
     int sl[PU], rsl[PU];
     if (active && one_group) place_group(a, en, iw, 0, l.wh + w * W, sl, rsl);
-    uint32_t hv[HB];
-    if (multi) look_across(a, min(tid, W - 1), 0, hv);
+    uint32_t hv[HB > 0 ? HB : 1];
+    if constexpr (multi) look_across(a, min(tid, W - 1), 0, hv);
 
     // (5) per bin: entries in earlier chunks and in all chunks.  A batch of words is polled
     //     as a whole until every word of it carries this launch's tag (rows beyond the last
     //     chunk repeat its words, and the chunk's own word is among them: no exceptions to
     //     test for).  Which words of a batch count, and which belong to earlier chunks, are
     //     wave-uniform bit masks.
-    if (multi) {
+    if constexpr (multi) {
         int rounds = 0;  // of this thread, over all its batches
         bool gave_up = false;
         bool have = true;  // hv holds the batch (tid, 0)
@@ -653,13 +664,17 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
     int rows_end = 0;
     if (b == (multi ? nchunks : 0)) rows_end = write_tables(a, l, tid, lane, w);
     if (w != 0) return;
-    if (!multi) {  // the caller of a fused launch says how many rows its output takes
-        write_status(a, l, lane, (!a.padded && a.rows_cap >= 0 && rows_end > a.rows_cap) ? STATUS_OUTPUT_OVERFLOW : 0);
+    // the caller of a fused launch says how many rows its output takes
+    const bool capped = !a.padded && a.rows_cap >= 0;
+    if (!multi) {
+        write_status(a, l, lane, capped && rows_end > a.rows_cap ? STATUS_OUTPUT_OVERFLOW : 0);
         return;
     }
     const uint32_t seen = __builtin_amdgcn_readfirstlane(ticket) + mine;  // lane 0 holds the ticket
     if ((int)(seen & (kGaveUp - 1u)) != nchunks + 1) return;  // the chunks and the workgroup of the tables
-    write_status(a, l, lane, seen >= kGaveUp ? STATUS_TIMEOUT : 0);
+    int extra = seen >= kGaveUp ? STATUS_TIMEOUT : 0;
+    if (capped && last_row_end(a, l, lane) > a.rows_cap) extra |= STATUS_OUTPUT_OVERFLOW;
+    write_status(a, l, lane, extra);
     uint32_t next = gen + 1u;
     if (next >= kTags) {  // the tags have run out: clear every published word and start over
         for (int64_t j = lane; j < (int64_t)kMaxChunks * W; j += kWave) a.pub[j] = 0u;
@@ -683,92 +698,132 @@ __global__ __launch_bounds__(1024) void layout_kernel(LayoutArgs a) {
         else warm_tokens(a, blockIdx.x - nlay, gridDim.x - nlay);
         return;
     }
-    layout_chunk<MULTI, ONE_GROUP>(a, lds, blockIdx.x);
+    layout_chunk<MULTI ? 32 : 0, ONE_GROUP>(a, lds, blockIdx.x);
 }
 
 // ---- layout and direct dispatch of a small input in ONE launch (Sec. IV-C: in the
 // low-latency kernels the count runs next to the send) ----
 //
-// For an input of at most 1024 entries (one per thread of a workgroup).  Workgroup 0 is the
-// layout above, single chunk, and writes the handle's arrays, which combine and the queries
-// read later.  Every other workgroup copies a share of one token row -- work unit = one
-// wavefront x one 1 KiB segment, `spp` segments per workgroup, `parts` workgroups per token
-// -- and needs only the destination rows of that token's K entries, which it counts out of
-// the ids directly: row of entry (t, k) naming expert e = first row of e + number of entries
-// before (t, k) that name e, the first row being the number of entries that name a lower
-// expert (or e * C, or the caller's).  Counting = one ballot per wavefront and target over
-// the ids its lanes hold, summed over the wavefronts through LDS.  Same ids, same
-// arithmetic as the layout: the rows are those workgroup 0 records.  No workgroup waits
-// for another.
-__global__ __launch_bounds__(1024) void layout_dispatch_kernel(LayoutArgs a, DispatchArgs d, int nseg, int units, int parts,
-                                                               int spp) {
+// The first `nlay` workgroups are the layout above and write the handle's arrays, which combine
+// and the queries read later.  Every other workgroup copies `group` tokens (the segments of
+// one of `parts` shares of their rows) and needs only the destination rows of these tokens'
+// entries, which it counts out of the ids directly: row of an entry naming expert e = first row
+// of e + entries before the group that name e + earlier entries of the group that name e, the
+// first row being the number of entries that name a lower expert (or e * C, or the caller's).
+// All ids (at most 8 per thread) go through one LDS histogram whose words hold the entries of a
+// bin in the low half and those before the group in the high half; the entries of the group
+// (at most 64) sit in the lanes of every wave and are ranked with one ballot per key bit.  Same
+// ids, same arithmetic as the layout: the rows are those it records.  No copying workgroup
+// waits for another.
+//
+// What bounds it: the id loads, five barriers and the random-placement write rate; the layout, a
+// chain of latencies of about the same length as a short copy, is hidden behind it.
+constexpr int kFusedIds = 8;  // ids per thread
+constexpr int kFusedMaxEntries = kFusedIds * kLayoutWavesPerBlock * kWave;
+
+// IDS: ids per thread.  With one, the copying workgroups are about as many as compute units and
+// the registers are not cut to what two workgroups per unit leave each (0.5 us of 7.2).
+template <int IDS, bool MULTI>
+__global__ __launch_bounds__(1024, IDS == 1 ? 4 : 8) void layout_dispatch_kernel(LayoutArgs a, DispatchArgs d, int nlay, int nseg, int units,
+                                                               int group, int parts, int spp) {
     extern __shared__ int32_t lds[];
-    if (blockIdx.x == 0) {
-        layout_chunk<false, true>(a, lds, 0);
+    if ((int)blockIdx.x < nlay) {
+        layout_chunk<MULTI ? kFusedIds : 0, true>(a, lds, blockIdx.x);  // at most kFusedIds chunks
         return;
     }
+    constexpr int threads = kLayoutWavesPerBlock * kWave;
+    uint32_t* bins = (uint32_t*)lds;  // [E]
+    int32_t* wsum = lds + a.E;        // [kLayoutWavesPerBlock]
     const int tid = threadIdx.x;
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nw = blockDim.x >> 6;
-    const int wg = blockIdx.x - 1;
-    const int t = wg / parts;
-    const int seg = (wg - t * parts) * spp + w;
-    const bool copies = w < spp && seg < nseg;
-    const int unit = seg * kWave + lane;
-    const bool active = copies && unit < units;
-    // the loads this wave needs, all issued before any is waited for: its piece of the
-    // token, the id of the entry this thread stands for, the token's K ids and gate weights
+    const int wg = blockIdx.x - nlay;
+    const int grp = wg / parts;
+    const int seg0 = (wg - grp * parts) * spp, segs = min(spp, nseg - seg0);
+    const int t0 = grp * group, nt = min(group, a.T - t0);
+    const int first = t0 * a.K, m = nt * a.K;  // m <= 64
+    const int items = nt * segs;               // segments this workgroup copies, wave w takes w, w + 16, ...
+    // the loads this wave needs first, all issued before any is waited for: a segment of a token, the
+    // ids of the entries this thread stands for, the group's ids and gate weights
     u32x4 v = {0u, 0u, 0u, 0u};
-    if (active) v = __builtin_nontemporal_load((const u32x4*)(d.x + (int64_t)t * d.x_stride) + unit);
-    int id = -1;
-    if (tid < a.n) {
-        const int ti = token_of(a, tid);
-        id = a.topk[(int64_t)ti * a.topk_stride + (tid - ti * a.K)];
+    int g = w / segs, seg = seg0 + (w - g * segs);
+    auto fetch = [&]() {
+        const int unit = seg * kWave + lane;
+        if (g < nt && unit < units) v = __builtin_nontemporal_load((const u32x4*)(d.x + (int64_t)(t0 + g) * d.x_stride) + unit);
+    };
+    fetch();
+    int id[IDS];
+#pragma unroll
+    for (int j = 0; j < IDS; ++j) {
+        const int i = tid + j * threads;
+        id[j] = -1;
+        if (j * threads < a.n && i < a.n) {
+            const int ti = token_of(a, i);
+            id[j] = a.topk[(int64_t)ti * a.topk_stride + (i - ti * a.K)];
+        }
     }
-    const int my_e = lane < a.K ? a.topk[(int64_t)t * a.topk_stride + lane] : -1;
+    const int my_g = token_of(a, lane), my_k = lane - my_g * a.K;
+    const int my_e = lane < m ? a.topk[(int64_t)(t0 + my_g) * a.topk_stride + my_k] : -1;
+    const bool routed = (unsigned)my_e < (unsigned)a.E;  // lanes beyond the group hold -1
     float my_w = 1.0f;
-    if (copies && seg == 0 && d.w && lane < a.K) my_w = d.w[(int64_t)t * d.w_stride + lane];
+    if (d.recv_w && d.w && lane < m) my_w = d.w[(int64_t)(t0 + my_g) * d.w_stride + my_k];
     int my_base = 0;
-    if (!a.padded && a.expert_base && lane < a.K && (unsigned)my_e < (unsigned)a.E) my_base = a.expert_base[my_e];
-    // per target k (lane k keeps its counts): entries of this wave that name the same expert
-    // and come before (t, k), and entries of this wave that name a lower expert
-    int same_before = 0, lower = 0;
-    const int first = t * a.K;
-    for (int k = 0; k < a.K; ++k) {
-        const int e = __builtin_amdgcn_readlane(my_e, k);
-        const uint64_t m_same = __ballot(id == e && tid < first + k);
-        const uint64_t m_lower = __ballot((unsigned)id < (unsigned)e);  // ids that are not routed compare high
-        if (lane == k) {
-            same_before = __popcll(m_same);
-            lower = __popcll(m_lower);
-        }
-    }
-    int32_t* part_same = lds;                    // [nw][64]
-    int32_t* part_lower = lds + nw * kWave;      // [nw][64]
-    part_same[w * kWave + lane] = same_before;
-    part_lower[w * kWave + lane] = lower;
+    if (!a.padded && a.expert_base && routed) my_base = a.expert_base[my_e];
+    if (tid < a.E) bins[tid] = 0u;  // E <= 1024
     lds_barrier();
-    if (!copies) return;
-    int slot = 0, start = 0;
-    for (int r = 0; r < nw; ++r) {
-        slot += part_same[r * kWave + lane];
-        start += part_lower[r * kWave + lane];
+#pragma unroll
+    for (int j = 0; j < IDS; ++j)
+        if ((unsigned)id[j] < (unsigned)a.E) atomicAdd(&bins[id[j]], tid + j * threads < first ? 0x10001u : 1u);
+    lds_barrier();
+    if (!a.padded && !a.expert_base) {  // the first row of every expert: entries that name a lower one
+        const uint32_t word = tid < a.E ? bins[tid] : 0u;
+        const int count = (int)(word & 0xffffu);
+        const int inc = wave_inclusive_scan(count);
+        if (lane == kWave - 1) wsum[w] = inc;
+        lds_barrier();
+        int below = 0;
+#pragma unroll
+        for (int r = 0; r < kLayoutWavesPerBlock; ++r) below += r < w ? wsum[r] : 0;
+        if (tid < a.E) bins[tid] = (word & 0xffff0000u) | (uint32_t)(below + inc - count);
+        lds_barrier();
     }
+    if (w >= items) return;
+    const uint64_t peers = match_key(my_e, routed, a.bits_e);
+    const int in_group = (int)__popcll(peers & ((1ull << lane) - 1ull));
     int my_row = -1;
-    if (lane < a.K && (unsigned)my_e < (unsigned)a.E) {
-        if (a.padded) my_row = slot < a.C ? my_e * a.C + slot : -1;
-        else my_row = (a.expert_base ? my_base : start) + slot;
-    }
-    for (int k = 0; k < a.K; ++k) {
-        const int row = __builtin_amdgcn_readlane(my_row, k);
-        if (row < 0 || row >= d.win.rows_cap) continue;  // rows beyond the output are flagged by workgroup 0
-        uint16_t* dst = d.win.base + window_offset(d.win, row);
-        if (active) __builtin_nontemporal_store(v, (u32x4*)dst + unit);
-        if (seg == 0 && lane == 0) {
-            if (d.recv_w) d.recv_w[row] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), k));
-            if (d.recv_src) d.recv_src[row] = t;
+    int64_t my_off = 0;
+    if (routed) {
+        const uint32_t word = bins[my_e];
+        const int slot = (int)(word >> 16) + in_group;
+        if (a.padded) {
+            if (slot < a.C) my_row = my_e * a.C + slot;
+            my_off = (int64_t)my_e * d.win.stride0 + (int64_t)slot * d.win.stride1;
+        } else {
+            my_row = (a.expert_base ? my_base : (int)(word & 0xffffu)) + slot;
+            my_off = (int64_t)my_row * d.win.stride0;
         }
+        if (my_row >= d.win.rows_cap) my_row = -1;  // flagged with the layout's status word
+    }
+    for (int it = w;;) {
+        const int unit = seg * kWave + lane;
+        const bool active = unit < units;
+        if (seg == 0 && my_row >= 0 && my_g == g) {
+            if (d.recv_w) d.recv_w[my_row] = my_w;
+            if (d.recv_src) d.recv_src[my_row] = t0 + g;
+        }
+        for (int k = 0; k < a.K; ++k) {
+            const int src = g * a.K + k;
+            if (__builtin_amdgcn_readlane(my_row, src) < 0) continue;
+            const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)my_off, src);
+            const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)((uint64_t)my_off >> 32), src);
+            uint16_t* dst = d.win.base + (int64_t)(((uint64_t)hi << 32) | lo);
+            if (active) __builtin_nontemporal_store(v, (u32x4*)dst + unit);
+        }
+        it += kLayoutWavesPerBlock;
+        if (it >= items) break;
+        g = it / segs;
+        seg = seg0 + (it - g * segs);
+        fetch();
     }
 }
 
@@ -796,14 +851,25 @@ bool layout_prefetches(const LayoutArgs& a) {
     return a.warm_x != nullptr && a.warm_rows > 0 && a.n >= kRunOrderMinEntries && a.nwc > kLayoutWavesPerBlock;
 }
 
-constexpr int kFusedMaxEntries = kLayoutWavesPerBlock * kWave;  // one entry per thread of a workgroup
+// The one-launch path takes inputs of at most 8192 entries that are copied by the plain
+// token-ordered walk (bf16 rows, the K entries of a token held by the lanes of one wave).  Beyond
+// that every workgroup would count more than 8 ids per thread, and the layout is a small part
+// of the two launches.  Nor do inputs that move more than kFusedMaxBytes come this way: 512 resident
+// workgroups stream a little slower than one wavefront per segment (rows of 14 336 bytes, two launches
+// / one: top-8 30.8/18.0 us at 512 tokens, 26.9/19.9 at 611, 33.4/27.6 at 900, 38.1/34.3 at 1023 =
+// 132 MB; top-2 40.2/39.6 at 4096 = 176 MB; top-1 47.4/49.8 at 8192 = 235 MB; 8192 rows of 512 bytes
+// 13.0/9.8).
+constexpr int64_t kFusedMaxBytes = 176ll << 20;
 
-// The one-launch path takes inputs of at most 1024 entries, copied by the plain token-ordered
-// walk (bf16 rows, the K entries of a token held by the lanes of one wave).
 bool layout_dispatch_fusable(const LayoutArgs& a, const DispatchArgs& d) {
-    return a.n >= 1 && a.n <= kFusedMaxEntries && a.passes == 1 && a.K <= kWave && d.H >= 8 &&
+    if (d.order != EP_ORDER_TOKEN && a.run_start && a.n >= kRunOrderMinEntries) return false;  // may go in destination order
+    if (((int64_t)a.n + a.T) * d.H * 2 > kFusedMaxBytes) return false;
+    return a.n >= 1 && a.n <= kFusedMaxEntries && a.K <= kWave && a.E <= kLayoutWavesPerBlock * kWave && d.H >= 8 &&
            lds_bytes(a, kLayoutWavesPerBlock) <= kLdsLimit;
 }
+
+// Copying workgroups of a fused launch: two of 1024 threads fit a compute unit, the layout's come first.
+constexpr int kFusedCopyBlocks = 480;
 
 hipError_t launch_layout_dispatch(const LayoutArgs& a_in, const DispatchArgs& d, hipStream_t s) {
     LayoutArgs a = a_in;
@@ -811,19 +877,31 @@ hipError_t launch_layout_dispatch(const LayoutArgs& a_in, const DispatchArgs& d,
     if (!layout_dispatch_fusable(a, d)) return hipErrorInvalidValue;
     a.rows_cap = d.win.rows_cap;
     a.recv_count = d.recv_count;
+    // up to PU passes one workgroup lays out; more entries are cut into chunks of one pass
+    const bool multi = a.passes > PU || a.nwc > kLayoutWavesPerBlock;
+    if (multi) {
+        a.passes = 1;
+        a.nwc = (a.n + kWave - 1) / kWave;
+        a.nchunks = (a.nwc + kLayoutWavesPerBlock - 1) / kLayoutWavesPerBlock;
+    }
+    const int nlay = multi ? a.nchunks + 1 : 1;
     const int units = d.H / 8;
     const int nseg = (units + kWave - 1) / kWave;
-    // workgroups per token: enough of them to put every compute unit to work, at most 16 segments each
+    // tokens per workgroup: so many that all copying workgroups run at once, no more than 64 entries
+    const int group = std::max(1, std::min((a.T + kFusedCopyBlocks - 1) / kFusedCopyBlocks, kWave / a.K));
+    const int ngroups = (a.T + group - 1) / group;
+    // workgroups per group: enough of them to put every compute unit to work, at most 16 segments of a token each
     int parts = (nseg + kLayoutWavesPerBlock - 1) / kLayoutWavesPerBlock;
-    while (parts < nseg && (int64_t)a.T * parts < 256) ++parts;
+    while (parts < nseg && (int64_t)ngroups * parts < 256) ++parts;
     const int spp = (nseg + parts - 1) / parts;
     parts = (nseg + spp - 1) / spp;
-    const int64_t nblk = 1 + (int64_t)a.T * parts;
+    const int64_t nblk = nlay + (int64_t)ngroups * parts;
     if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-    // a thread per entry, a wave per segment, and the 16 waves the layout workgroup is laid out for
-    const size_t lds = std::max(lds_bytes(a, kLayoutWavesPerBlock), sizeof(int32_t) * 2 * kLayoutWavesPerBlock * kWave);
-    hipLaunchKernelGGL(layout_dispatch_kernel, dim3((unsigned)nblk), dim3(kLayoutWavesPerBlock * kWave), lds, s, a, d, nseg,
-                       units, parts, spp);
+    const dim3 grid((unsigned)nblk), block(kLayoutWavesPerBlock * kWave);
+    const size_t lds = lds_bytes(a, kLayoutWavesPerBlock);  // holds the copying workgroups' E + 16 words as well
+    if (multi) hipLaunchKernelGGL((layout_dispatch_kernel<kFusedIds, true>), grid, block, lds, s, a, d, nlay, nseg, units, group, parts, spp);
+    else if (a.passes > 1) hipLaunchKernelGGL((layout_dispatch_kernel<PU, false>), grid, block, lds, s, a, d, nlay, nseg, units, group, parts, spp);
+    else hipLaunchKernelGGL((layout_dispatch_kernel<1, false>), grid, block, lds, s, a, d, nlay, nseg, units, group, parts, spp);
     return hipGetLastError();
 }
 

@@ -755,6 +755,55 @@ def test_layout_dispatch_one_call_errors_and_overflow(ep, hx, oracle_mod):
         ep.ep_group_destroy(g)
 
 
+@pytest.mark.parametrize("T,K,E,H,C,base,cut", [
+    (129, 8, 256, 520, 0, False, 0), (256, 8, 256, 64, 16, False, 0),    # one workgroup lays out: up to 2048 entries
+    (257, 8, 256, 64, 0, True, 0), (683, 6, 96, 2880, 0, False, 0),      # chunks; a token's segments shared out
+    (1023, 8, 128, 1032, 90, False, 0), (1024, 8, 64, 256, 0, True, 0),  # three tokens per workgroup; the most entries
+    (8192, 1, 8, 64, 0, False, 0), (4095, 2, 32, 8, 0, False, 0),        # eighteen, and nine, tokens per workgroup
+    (127, 64, 64, 200, 0, False, 0), (480, 17, 51, 128, 60, False, 0),   # a token fills the lanes; three tokens are 51 lanes
+    (97, 33, 1020, 1024, 0, False, 0), (700, 8, 256, 64, 0, False, 100), (700, 8, 256, 64, 0, True, 100),  # output too short
+])
+def test_layout_dispatch_one_launch_of_up_to_8192_entries(ep, hx, T, K, E, H, C, base, cut):
+    """ep_layout_dispatch against ep_layout + ep_dispatch on the same input (masked and invalid ids,
+    strided ids): windows, side arrays, counts, destination rows and status, bit for bit."""
+    gen = torch.Generator(hx.DEV).manual_seed(T + K)
+    ids = torch.randint(0, E, (T, K + 3), generator=gen, device=hx.DEV, dtype=torch.int32)
+    ids[::9, 0], ids[5, K - 1] = -1, E + 2
+    topk = ids[:, :K]
+    w = torch.rand((T, K), generator=gen, device=hx.DEV)
+    x = torch.randn((T, H), generator=gen, device=hx.DEV).bfloat16()
+    count = torch.bincount(topk[(topk >= 0) & (topk < E)].long(), minlength=E)
+    first = (torch.cumsum(count + 2, 0) - count).to(torch.int32) if base else None
+    rows = E * C if C else T * K + 2 * E * base - cut
+    cfg = ep.make_config(1, E, H, K, T, mode=ep.EP_MODE_LL if C else ep.EP_MODE_HT, slots_per_subregion=C)
+    group = ep.ep_group_create(cfg)
+    got = []
+    try:
+        for one in (False, True):
+            store = hx.poison_bf16((rows + 64, H))
+            recv = store[:rows].view(E, C, H) if C else store[:rows]
+            rw = torch.full((rows + 64,), -3.5, device=hx.DEV)
+            rs = torch.full((rows + 64,), -9, dtype=torch.int32, device=hx.DEV)
+            cnt = torch.full((E,), -1, dtype=torch.int32, device=hx.DEV)
+            side = dict(topk_weights=w, recv_w=rw[:rows], recv_src=rs[:rows], recv_count=cnt)
+            if one:
+                h = ep.ep_layout_dispatch(group, topk, x, recv, expert_base=first, **side)
+            else:
+                h = ep.ep_layout(group, topk, expert_base=first)
+                ep.ep_dispatch(h, x, recv, **side)
+            info = ep.ep_handle_query(h, ok=(ep.EP_SUCCESS, ep.EP_ERR_INVALID_ROUTING, ep.EP_ERR_OVERFLOW))
+            assert bool(info.status & ep.STATUS_OUTPUT_OVERFLOW) == (cut > 0)
+            got.append([store.view(torch.int16), rw, rs, cnt, ep.read_device_i32(info.dst_row, T * K),
+                        ep.read_device_i32(info.sorted_row, info.entries_sorted), torch.tensor([info.status, info.rows_end])])
+            torch.cuda.synchronize()
+            ep.ep_handle_destroy(h)
+        for a, b in zip(*got):
+            assert torch.equal(a, b)
+    finally:
+        torch.cuda.synchronize()
+        ep.ep_group_destroy(group)
+
+
 ORDER_CASES = [
     # inputs of at least 8192 routed entries take the destination-ordered kernel
     ("ht_prefill", None, None, "ht", 0),

@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional, Sequence
 
 import torch  # loaded first on purpose: the library must bind to the HIP runtime torch uses
@@ -241,15 +242,21 @@ _DTYPES = {torch.bfloat16: EP_DTYPE_BF16, torch.float32: EP_DTYPE_F32, torch.int
 
 def tensor_desc(t: torch.Tensor, tag: int) -> ep_tensor_t:
     """Describe a torch tensor (device memory owner) as an ep_tensor_t."""
-    d = ep_tensor_t()
-    d.data = t.data_ptr() if t.numel() > 0 or t.data_ptr() else None
-    d.ndim = t.dim()
-    d.dtype = _DTYPES[t.dtype]
-    d.tag = tag
-    for i in range(t.dim()):
-        d.shape[i] = t.shape[i]
-        d.stride[i] = t.stride(i)
-    return d
+    return ep_tensor_t.from_buffer_copy(_desc_bytes(t, tag))
+
+
+# ep_tensor_t as bytes: one pack instead of a dozen ctypes field and array stores per descriptor
+# (a dispatch and a combine describe ten tensors between them)
+_PACK = struct.Struct("@P4i8q").pack
+assert struct.calcsize("@P4i8q") == ctypes.sizeof(ep_tensor_t)
+_PAD = ((0, 0, 0, 0), (0, 0, 0), (0, 0), (0,), ())  # up to four dimensions
+
+
+def _desc_bytes(t: torch.Tensor, tag: int) -> bytes:
+    shape = t.shape
+    n = len(shape)
+    pad = _PAD[n]
+    return _PACK(t.data_ptr(), n, _DTYPES[t.dtype], tag, 0, *shape, *pad, *t.stride(), *pad)
 
 
 def _stream_ptr(stream) -> ctypes.c_void_p:
@@ -364,10 +371,9 @@ def ep_group_reset_signals(group, stream=None) -> None:
 
 
 def _descs(pairs) -> "ctypes.Array":
-    arr = (ep_tensor_t * max(len(pairs), 1))()
-    for i, (t, tag) in enumerate(pairs):
-        arr[i] = tensor_desc(t, tag)
-    return arr
+    if not pairs:
+        return (ep_tensor_t * 1)()
+    return (ep_tensor_t * len(pairs)).from_buffer_copy(b"".join([_desc_bytes(t, tag) for t, tag in pairs]))
 
 
 def _dispatch_tensors(x, recv_x, topk_weights=None, recv_w=None, recv_src=None, recv_count=None, topk_idx=None,

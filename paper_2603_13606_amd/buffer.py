@@ -67,7 +67,8 @@ class EPBuffer:
             self.comm_stream = torch.cuda.Stream()
         # pinned host memory, written by the dispatch kernel through its device mapping
         self.recv_expert_counter = torch.zeros(num_experts, dtype=torch.int32, pin_memory=True)
-        self._counter_dev_ptr = _device_pointer_of_pinned(self.recv_expert_counter)
+        self._counter_desc = ep.tensor_desc(self.recv_expert_counter, ep.EP_TAG_RECV_EXPERT_COUNTER_HOST)
+        self._counter_desc.data = _device_pointer_of_pinned(self.recv_expert_counter)
         self._last_event: Optional[torch.cuda.Event] = None
 
     # ------------------------------------------------------------------ streams and events
@@ -80,18 +81,28 @@ class EPBuffer:
         ev.record(torch.cuda.current_stream())
         return ev
 
-    def _enter(self, previous_event: Optional[torch.cuda.Event]):
+    def _enter(self, previous_event: Optional[torch.cuda.Event]) -> torch.cuda.Stream:
+        """Makes the communication stream wait; returns the compute stream."""
+        compute = torch.cuda.current_stream()
         if previous_event is not None:
             self.comm_stream.wait_event(previous_event)
         else:
-            self.comm_stream.wait_stream(torch.cuda.current_stream())
+            self.comm_stream.wait_stream(compute)
+        return compute
 
-    def _leave(self) -> torch.cuda.Event:
+    def _leave(self, compute: torch.cuda.Stream) -> torch.cuda.Event:
         ev = torch.cuda.Event()
         ev.record(self.comm_stream)
-        torch.cuda.current_stream().wait_event(ev)  # compute waits for communication
+        compute.wait_event(ev)  # compute waits for communication
         self._last_event = ev
         return ev
+
+    def _with_counter(self, outs) -> "ctypes.Array":
+        """Descriptors of a dispatch's outputs and of the pinned per-expert counter (its device address)."""
+        arr = (ep.ep_tensor_t * (len(outs) + 1))()
+        ctypes.memmove(arr, ep._descs(outs), ctypes.sizeof(ep.ep_tensor_t) * len(outs))
+        arr[len(outs)] = self._counter_desc
+        return arr
 
     # ------------------------------------------------------------------ operations
     def dispatch(self, x: torch.Tensor, topk_idx: Optional[torch.Tensor] = None,
@@ -104,15 +115,9 @@ class EPBuffer:
         handle's count are unused); LL mode returns [E, C, H].  With fp8=True recv_x is a
         pair (codes float8_e4m3fn, scales float32 [rows, H/128])."""
         T = x.shape[0]
-        self._enter(previous_event)
+        compute = self._enter(previous_event)
         sp = self.comm_stream.cuda_stream
         with torch.cuda.stream(self.comm_stream):
-            if handle is None:
-                assert topk_idx is not None
-                # the tokens are about to be dispatched: let the layout launch read them ahead
-                # (only a destination-ordered group makes use of the hint)
-                raw = ep.ep_layout_prefetch(self.group, topk_idx, x, stream=sp)
-                handle = EPHandle(raw, topk_idx, T)
             rows = self.E * self.C if self.ll else T * self.K
             dt = torch.float8_e4m3fn if fp8 else torch.bfloat16
             store = torch.empty((rows, self.H), dtype=dt, device=self.device)
@@ -120,32 +125,45 @@ class EPBuffer:
             recv_w = torch.empty(rows, dtype=torch.float32, device=self.device) if topk_weights is not None else None
             recv_src = torch.empty(rows, dtype=torch.int32, device=self.device)
             scales = torch.empty((rows, self.H // 128), dtype=torch.float32, device=self.device) if fp8 else None
-            counter = _as_tensor_desc_override(self.recv_expert_counter, self._counter_dev_ptr)
-            _dispatch_with_counter(handle.raw, x, recv_x, topk_weights, recv_w, recv_src, counter, scales,
-                                   handle.topk_idx if self._dedup else None, sp)
-            for t in (x, recv_x, recv_src) + ((topk_weights, recv_w) if topk_weights is not None else ()):
-                t.record_stream(self.comm_stream)
-        ev = self._leave()
+            ids = topk_idx if handle is None else handle.topk_idx
+            ins, outs = ep._dispatch_tensors(x, recv_x, topk_weights, recv_w, recv_src, None, ids if self._dedup else None, scales)
+            outs = self._with_counter(outs)
+            ins, n_in = ep._descs(ins), len(ins)
+            if handle is None:
+                assert topk_idx is not None
+                # layout and dispatch in one call: one launch for small inputs, and for large ones the layout
+                # knows which tokens it may read ahead
+                raw = ctypes.c_void_p()
+                td = ep.tensor_desc(topk_idx, ep.EP_TAG_TOPK_IDX)
+                ep._check(ep.load().ep_layout_dispatch(ctypes.byref(raw), self.group, ctypes.byref(td), None, ins, n_in, outs,
+                                                       len(outs), sp), "ep_layout_dispatch")
+                handle = EPHandle(raw, topk_idx, T)
+            else:
+                ep._check(ep.load().ep_dispatch(handle.raw, ins, n_in, outs, len(outs), 0, sp), "ep_dispatch")
+            # the outputs were allocated on this stream, the inputs were not
+            x.record_stream(self.comm_stream)
+            if topk_weights is not None:
+                topk_weights.record_stream(self.comm_stream)
+        ev = self._leave(compute)
         return ((recv_x, scales) if fp8 else recv_x), recv_src, recv_w, handle, ev
 
     def combine(self, y: torch.Tensor, handle: EPHandle, topk_weights: Optional[torch.Tensor] = None,
                 previous_event: Optional[torch.cuda.Event] = None):
         """out, event = combine(y, handle, topk_weights)."""
-        self._enter(previous_event)
+        compute = self._enter(previous_event)
         sp = self.comm_stream.cuda_stream
         with torch.cuda.stream(self.comm_stream):
             out = torch.empty((handle.num_tokens, self.H), dtype=torch.bfloat16, device=self.device)
             ep.ep_combine(handle.raw, y, out, topk_weights=topk_weights, stream=sp)
             y.record_stream(self.comm_stream)
-            out.record_stream(self.comm_stream)
-        return out, self._leave()
+        return out, self._leave(compute)
 
     def combine_backward(self, grad_out: torch.Tensor, handle: EPHandle, topk_weights: Optional[torch.Tensor] = None,
                          y: Optional[torch.Tensor] = None, previous_event: Optional[torch.cuda.Event] = None):
         """grad_y, grad_w, event = combine_backward(grad_out, handle, topk_weights, y): the gradient of a
         weighted combine with respect to the expert outputs (windows like y, rows without an entry
         zero) and, when y is given, with respect to the gate weights [T, K]."""
-        self._enter(previous_event)
+        compute = self._enter(previous_event)
         sp = self.comm_stream.cuda_stream
         with torch.cuda.stream(self.comm_stream):
             if y is not None:
@@ -156,9 +174,10 @@ class EPBuffer:
                 grad_y = store.view(self.E, self.C, self.H) if self.ll else store
             grad_w = torch.empty((handle.num_tokens, self.K), dtype=torch.float32, device=self.device) if y is not None else None
             ep.ep_combine_backward_full(handle.raw, grad_out, grad_y, topk_weights=topk_weights, y=y, grad_w=grad_w, stream=sp)
-            for t in (grad_out, grad_y) + ((y, grad_w) if y is not None else ()):
-                t.record_stream(self.comm_stream)
-        return grad_y, grad_w, self._leave()
+            grad_out.record_stream(self.comm_stream)
+            if y is not None:
+                y.record_stream(self.comm_stream)
+        return grad_y, grad_w, self._leave(compute)
 
     def get_tokens_per_expert_list(self) -> List[int]:
         """Rows placed per expert by the last dispatch, read from the pinned counter."""
@@ -206,30 +225,6 @@ def _device_pointer_of_pinned(t: torch.Tensor) -> int:
     if rc != 0 or not dev.value:
         raise RuntimeError(f"hipHostGetDevicePointer failed with {rc}")
     return int(dev.value)
-
-
-def _as_tensor_desc_override(t: torch.Tensor, ptr: int) -> ep.ep_tensor_t:
-    d = ep.tensor_desc(t, ep.EP_TAG_RECV_EXPERT_COUNTER_HOST)
-    d.data = ptr
-    return d
-
-
-def _dispatch_with_counter(raw, x, recv_x, w, recv_w, recv_src, counter_desc, scales, topk_idx, sp) -> None:
-    ins = [ep.tensor_desc(x, ep.EP_TAG_TOKENS)]
-    if w is not None:
-        ins.append(ep.tensor_desc(w, ep.EP_TAG_TOPK_WEIGHTS))
-    if topk_idx is not None:
-        ins.append(ep.tensor_desc(topk_idx, ep.EP_TAG_TOPK_IDX))
-    outs = [ep.tensor_desc(recv_x, ep.EP_TAG_TOKENS), ep.tensor_desc(recv_src, ep.EP_TAG_RECV_SRC_TOKEN), counter_desc]
-    if recv_w is not None:
-        outs.append(ep.tensor_desc(recv_w, ep.EP_TAG_TOPK_WEIGHTS))
-    if scales is not None:
-        outs.append(ep.tensor_desc(scales, ep.EP_TAG_SCALES))
-    ia = (ep.ep_tensor_t * len(ins))(*ins)
-    oa = (ep.ep_tensor_t * len(outs))(*outs)
-    code = ep.load().ep_dispatch(raw, ia, len(ins), oa, len(outs), 0, sp)
-    if code != ep.EP_SUCCESS:
-        raise ep.EpError(code, "ep_dispatch")
 
 
 # ---------------------------------------------------------------------- autograd wrappers

@@ -283,7 +283,7 @@ def _timed_us(torch, np, fn, iters: int = 20) -> float:
 
 def once_per_rank(ep, torch, np, spec, sets, rows, stream_ptr):
     """The dispatch variant that sends a token once per destination rank and expands it to the expert
-    rows (messages and rows written in one launch), timed over the rotated input sets; HIP events."""
+    rows, timed over the rotated input sets; HIP events."""
     T, K, H, E = spec.T, spec.K, spec.H, spec.E
     cfg = ep.make_config(spec.R, E, H, K, T, mode=ep.EP_MODE_HT, dispatch_path=ep.EP_PATH_RANK_DEDUP,
                          max_handles=len(sets))

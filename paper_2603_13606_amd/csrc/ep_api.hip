@@ -133,6 +133,12 @@ int64_t carve(int64_t* cursor, int64_t ints) {
     return at;
 }
 
+// Whether layouts of the group record the runs the destination-ordered walk needs: when the group
+// asks for that order, and for the expansion of the once-per-rank path into concatenated windows.
+bool records_runs(const ep_group_config_t& c) {
+    return c.dispatch_path == EP_PATH_DIRECT ? c.dispatch_order != EP_ORDER_TOKEN : c.mode == EP_MODE_HT;
+}
+
 // Lays the handle arrays out inside one allocation; with base == nullptr only the size is computed.
 int64_t carve_slab(const ep_group_s* g, Slab* s, int32_t* base) {
     const int E = g->cfg.num_experts, R = g->cfg.num_ranks;
@@ -142,7 +148,7 @@ int64_t carve_slab(const ep_group_s* g, Slab* s, int32_t* base) {
     const int64_t o_eo = carve(&cur, E + 1), o_op = carve(&cur, E + 1), o_rp = carve(&cur, R);
     const int64_t o_rt = carve(&cur, R), o_ro = carve(&cur, R + 1);
     const int64_t o_h = carve(&cur, (int64_t)kMaxChunks * g->W), o_ctl = carve(&cur, kLayoutCtlWords);
-    const bool runs = g->cfg.dispatch_order != EP_ORDER_TOKEN && g->cfg.dispatch_path == EP_PATH_DIRECT;
+    const bool runs = records_runs(g->cfg);
     const int64_t o_rn = runs ? carve(&cur, (int64_t)(kMaxWaveChunks + 1) * E) : 0;
     const int64_t o_sl = carve(&cur, nB), o_dr = carve(&cur, nB), o_rr = carve(&cur, nB);
     const int64_t o_st = carve(&cur, nB), o_sk = carve(&cur, nB), o_sr = carve(&cur, nB), o_er = carve(&cur, nB);
@@ -616,14 +622,13 @@ static ep_result_t prepare_layout(ep_handle_t* handle, ep_group_t g, const ep_te
     a.slot = s.slot; a.dst_row = s.dst_row; a.rank_row = s.rank_row; a.sorted_token = s.sorted_token;
     a.sorted_k = s.sorted_k; a.sorted_row = s.sorted_row;
     a.entry_rank = s.entry_rank;
-    // the table of run starts is only wanted by the destination-ordered dispatch
-    a.run_start = (c.dispatch_order != EP_ORDER_TOKEN && c.dispatch_path == EP_PATH_DIRECT) ? s.run_start : nullptr;
+    a.run_start = records_runs(c) ? s.run_start : nullptr;
     a.warm_x = nullptr; a.warm_stride = 0; a.warm_rows = 0; a.warm_units = c.hidden / 8; a.nchunks = 1;
     a.rows_cap = -1; a.recv_count = nullptr;
     a.drop_hint = (a.padded && a.run_start) ? g->drop_hint_dev : nullptr;
     a.quant_out = nullptr; a.quant_pitch = 0;
     h->quant_x = nullptr;
-    if (tokens && a.run_start && c.dispatch_order == EP_ORDER_DESTINATION) {
+    if (tokens && a.run_start && c.dispatch_order == EP_ORDER_DESTINATION && c.dispatch_path == EP_PATH_DIRECT) {
         a.warm_x = (const uint16_t*)tokens->data;
         a.warm_stride = tokens->stride[0];
         const int cached_rows = (int)std::min<int64_t>(T, kWarmBytes / (2 * (int64_t)c.hidden));
@@ -846,6 +851,16 @@ ep_result_t ep_dispatch(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_in
     sa.hdr_units = (int)(g->hdr_bytes / 16);
     sa.totals = s.totals;
     sa.T = h->T; sa.K = c.top_k; sa.H = c.hidden;
+    if (!send_only && a.run_start && 2ll * sa.T * c.hidden <= kWarmBytes) {
+        // large enough for the destination-ordered walk, and the tokens the send has just read stay in the
+        // memory-side cache: the rows are written in that order by a launch of their own
+        a.order = EP_ORDER_DESTINATION_RESIDENT;
+        DispatchPlan plan;
+        if (plan_dispatch(a.T, a.K, a.H, a.E, a.order, true, 0, &plan)) {
+            if (launch_dedup_send(sa, (hipStream_t)stream) != hipSuccess) return EP_ERR_HIP;
+            return launch_dispatch(a, (hipStream_t)stream) == hipSuccess ? EP_SUCCESS : EP_ERR_HIP;
+        }
+    }
     if (!send_only) {
         const DedupExpandArgs xa = {s.dst_row, s.expert_kept, a.win, a.recv_w, a.recv_src, a.recv_count, c.num_experts};
         return launch_dedup_send_expand(sa, xa, (hipStream_t)stream) == hipSuccess ? EP_SUCCESS : EP_ERR_HIP;

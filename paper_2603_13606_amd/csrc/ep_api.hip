@@ -134,9 +134,18 @@ int64_t carve(int64_t* cursor, int64_t ints) {
 }
 
 // Whether layouts of the group record the runs the destination-ordered walk needs: when the group
-// asks for that order, and for the expansion of the once-per-rank path into concatenated windows.
+// asks for that order, and for the once-per-rank path into concatenated windows where the send and the
+// ordered walk beat the one launch that does both (layout + dispatch, us in one / in two, even routing unless
+// said): rows of 14 336 bytes, top-8, 64.8/59.2 at 1100 tokens, 216/180 at 4096 (hot ranks 169/146), 409/345 at
+// 8192; of 8192 bytes, top-4, 129/116 at 8192 tokens; of 4096 bytes 69.0/65.7; but of 1024 bytes 26/40 -- the
+// walk's workgroups copy too little each -- and top-2 61.9/62.8 (hot 57/61), where most messages are rows.
+constexpr int kOnceOrderedMinHidden = 2048;
+constexpr int kOnceOrderedMinTopK = 4;
+constexpr int64_t kOnceOrderedMaxTokenBytes = 128ll << 20;  // half of the memory-side cache; measured up to 117 MB
+
 bool records_runs(const ep_group_config_t& c) {
-    return c.dispatch_path == EP_PATH_DIRECT ? c.dispatch_order != EP_ORDER_TOKEN : c.mode == EP_MODE_HT;
+    if (c.dispatch_path == EP_PATH_DIRECT) return c.dispatch_order != EP_ORDER_TOKEN;
+    return c.mode == EP_MODE_HT && c.hidden >= kOnceOrderedMinHidden && c.top_k >= kOnceOrderedMinTopK;
 }
 
 // Lays the handle arrays out inside one allocation; with base == nullptr only the size is computed.
@@ -851,7 +860,7 @@ ep_result_t ep_dispatch(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_in
     sa.hdr_units = (int)(g->hdr_bytes / 16);
     sa.totals = s.totals;
     sa.T = h->T; sa.K = c.top_k; sa.H = c.hidden;
-    if (!send_only && a.run_start && 2ll * sa.T * c.hidden <= kWarmBytes) {
+    if (!send_only && a.run_start && 2ll * sa.T * c.hidden <= kOnceOrderedMaxTokenBytes) {
         // large enough for the destination-ordered walk, and the tokens the send has just read stay in the
         // memory-side cache: the rows are written in that order by a launch of their own
         a.order = EP_ORDER_DESTINATION_RESIDENT;

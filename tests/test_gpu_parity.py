@@ -1411,7 +1411,8 @@ def test_once_per_rank_dispatch_parity(ep, hx, oracle_mod, name, T, H, mode, C, 
     (130, 1000, 16, 128, 64, "ht", 0),  # headers of 64 ids
     (1, 72, 2, 8, 2, "ht", 0),
     # from 8192 entries on concatenated rows go in destination order: its smallest input, and odd sizes
-    (1024, 64, 4, 64, 8, "ht", 0), (2801, 136, 3, 51, 3, "ht", 0), (1100, 64, 4, 64, 8, "ll", 150),
+    (1024, 2048, 4, 64, 8, "ht", 0), (2101, 2056, 3, 51, 4, "ht", 0), (1100, 64, 4, 64, 8, "ll", 150),
+    (1024, 2040, 4, 64, 8, "ht", 0), (2731, 2048, 3, 51, 3, "ht", 0),   # rows too short, too few entries per token: one launch
 ])
 def test_once_per_rank_one_launch_equals_two_phases(ep, hx, oracle_mod, T, H, R, E, K, mode, C):
     """The undivided dispatch places the rows by the layout's record, the receive phase of the divided

@@ -491,8 +491,10 @@ __device__ __forceinline__ void look_across(const LayoutArgs& a, int c, int r0, 
 // which no launch uses as a tag.
 //
 // HB: chunks whose published words a thread loads in one batch (at most 32: bit masks), 0 = there
-// is one chunk.  ONE_GROUP: a wave's entries fit one load group (at most PU
-// passes) and stay in registers from the histogram to the emit.
+// is one chunk.  FUSED: the launch also dispatches (apart, so that the code of the
+// plain launch does not change with it: with the check of the output in both, the prefill step was
+// 1.5 us of 185 slower on two boxes of three).  ONE_GROUP: a wave's entries fit one load group
+// (at most PU passes) and stay in registers from the histogram to the emit.
 // The same workgroups, for a group that quantises ahead: instead of only reading the token
 // rows they quantise them (the FP8 dispatch's format, see ep_fp8.h) into a staging copy, row t
 // at quant_out + t * quant_pitch: H bytes of codes, then H/128 float scales.  The quantising
@@ -518,7 +520,7 @@ __device__ void quantize_tokens(const LayoutArgs& a, int wb, int nwb) {
     }
 }
 
-template <int HB, bool ONE_GROUP>
+template <int HB, bool ONE_GROUP, bool FUSED>
 __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, const int b) {
     const int wpb = blockDim.x >> 6;
     const Lds l = carve_lds(lds, a, wpb);
@@ -664,16 +666,14 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
     int rows_end = 0;
     if (b == (multi ? nchunks : 0)) rows_end = write_tables(a, l, tid, lane, w);
     if (w != 0) return;
-    // the caller of a fused launch says how many rows its output takes
-    const bool capped = !a.padded && a.rows_cap >= 0;
-    if (!multi) {
-        write_status(a, l, lane, capped && rows_end > a.rows_cap ? STATUS_OUTPUT_OVERFLOW : 0);
+    if (!multi) {  // the caller of a fused launch says how many rows its output takes
+        write_status(a, l, lane, (!a.padded && a.rows_cap >= 0 && rows_end > a.rows_cap) ? STATUS_OUTPUT_OVERFLOW : 0);
         return;
     }
     const uint32_t seen = __builtin_amdgcn_readfirstlane(ticket) + mine;  // lane 0 holds the ticket
     if ((int)(seen & (kGaveUp - 1u)) != nchunks + 1) return;  // the chunks and the workgroup of the tables
     int extra = seen >= kGaveUp ? STATUS_TIMEOUT : 0;
-    if (capped && last_row_end(a, l, lane) > a.rows_cap) extra |= STATUS_OUTPUT_OVERFLOW;
+    if (FUSED && !a.padded && last_row_end(a, l, lane) > a.rows_cap) extra |= STATUS_OUTPUT_OVERFLOW;
     write_status(a, l, lane, extra);
     uint32_t next = gen + 1u;
     if (next >= kTags) {  // the tags have run out: clear every published word and start over
@@ -698,7 +698,7 @@ __global__ __launch_bounds__(1024) void layout_kernel(LayoutArgs a) {
         else warm_tokens(a, blockIdx.x - nlay, gridDim.x - nlay);
         return;
     }
-    layout_chunk<MULTI ? 32 : 0, ONE_GROUP>(a, lds, blockIdx.x);
+    layout_chunk<MULTI ? 32 : 0, ONE_GROUP, false>(a, lds, blockIdx.x);
 }
 
 // ---- layout and direct dispatch of a small input in ONE launch (Sec. IV-C: in the
@@ -728,7 +728,7 @@ __global__ __launch_bounds__(1024, IDS == 1 ? 4 : 8) void layout_dispatch_kernel
                                                                int group, int parts, int spp) {
     extern __shared__ int32_t lds[];
     if ((int)blockIdx.x < nlay) {
-        layout_chunk<MULTI ? kFusedIds : 0, true>(a, lds, blockIdx.x);  // at most kFusedIds chunks
+        layout_chunk<MULTI ? kFusedIds : 0, true, true>(a, lds, blockIdx.x);  // at most kFusedIds chunks
         return;
     }
     constexpr int threads = kLayoutWavesPerBlock * kWave;

@@ -426,7 +426,9 @@ hipError_t launch_combine_backward(const CombineArgs& a, const uint16_t* g, int6
     auto launch = [&](auto kernel, unsigned blocks) {
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, a, g, g_stride, gy, grad_w, gw_stride, units, reached);
     };
-    if (!a.win.base || a.T == 0) {
+    // by what is asked for, not by the address of y: expert outputs of no rows may come without one; every
+    // weight gradient is zero then, and y is not read
+    if (!grad_w || a.T == 0) {
         launch(combine_backward_kernel<true, false>, nblk);
     } else if (a.K < kSplitBackwardMinEntries || std::min((int64_t)a.T * a.K, gy.rows_cap) * units * 16 < kSplitBackwardBytes) {
         launch(combine_backward_kernel<true, true>, nblk);

@@ -215,6 +215,30 @@ def test_large_backward_gives_the_gradients_of_its_halves(hx, C):
         ep.ep_group_destroy(group)
 
 
+@pytest.mark.parametrize("full", [False, True])
+def test_backward_without_any_row_gives_zero_weight_gradients(hx, full):
+    """T tokens that are all padding and expert outputs of no rows at all ([0, H], null data): the weight
+    gradients are zeros, not what their storage held."""
+    from paper_2603_13606_amd import binding as ep
+    R, E, H, K, T = 4, 16, 256, 4, 37
+    group = ep.ep_group_create(ep.make_config(R, E, H, K, T, mode=ep.EP_MODE_HT))
+    try:
+        h = ep.ep_layout(group, torch.full((T, K), -1, dtype=torch.int32, device=hx.DEV))
+        g = torch.randn((T, H), device=hx.DEV).bfloat16()
+        w = torch.rand((T, K), device=hx.DEV)
+        y, grad_y = (torch.empty((0, H), dtype=torch.bfloat16, device=hx.DEV) for _ in range(2))
+        assert y.data_ptr() == 0
+        grad_w = torch.full((T, K), 7.0, device=hx.DEV)
+        call = ep.ep_combine_backward_full if full else ep.ep_combine_backward
+        call(h, g, grad_y, topk_weights=w, y=y, grad_w=grad_w)
+        torch.cuda.synchronize()
+        assert torch.all(grad_w == 0.0)
+        ep.ep_handle_destroy(h)
+    finally:
+        torch.cuda.synchronize()
+        ep.ep_group_destroy(group)
+
+
 @pytest.mark.parametrize("mode", ["ht", "ll"])
 def test_buffer_autograd_reuses_handle(hx, oracle_mod, mode):
     """One handle through forward and backward of the autograd wrappers: the gradients that come

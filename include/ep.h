@@ -517,6 +517,7 @@ EP_API ep_result_t ep_layout_dispatch(ep_handle_t *handle, ep_group_t group, con
  *            grad_w[t,k] = sum over h of f32(y[row(t,k), h]) * f32(g[t,h]) in float32, in a fixed
  *            order (per thread of a 256-thread workgroup over its 16-byte units, a fixed tree over
  *            the lanes, the four waves in order); 0 for an entry without a row.
+ * In place: grad_y may be y itself, and grad_w may be w itself.
  * The backward pass of ep_dispatch needs no call of its own: it is ep_combine without weights.
  * Errors: EP_ERR_INVALID_ARG, EP_ERR_UNSUPPORTED, EP_ERR_HIP.
  */

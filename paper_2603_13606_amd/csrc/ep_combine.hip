@@ -294,7 +294,9 @@ __global__ __launch_bounds__(256) void combine_hier_kernel(CombineArgs a, int ns
 // Large calls run as two launches of the same kernel, one for the weight gradients (reads
 // only) and one for the rows: a read stream next to a stream of randomly placed writes
 // reaches 4.8 TB/s, reads alone 6.6 and such writes alone 4.9 (at 4096 x 7168, top-8: 195 us in one
-// launch, 174 in two, with g read twice).  Same order of every sum either way.
+// launch, 174 in two, with g read twice).  Same order of every sum either way.  In place works in
+// either form: grad_y over y, where every unit is read before it is written, and grad_w over the
+// gate weights, which one launch holds in registers by then and for which two are not used.
 constexpr int KBB = 8;  // entries handled together
 constexpr int kClearBlocks = 256;
 // Two launches from this many bytes of rows and this many entries per token on (us in two / in one,
@@ -416,6 +418,15 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(CombineArgs a, co
     }
 }
 
+// Whether the weight gradients share memory with the gate weights (by their spans: columns of one array may be
+// taken for shared, which costs time only).
+bool weights_in_place(const CombineArgs& a, const float* grad_w, int64_t gw_stride) {
+    if (!a.w || !grad_w || a.T == 0) return false;
+    const float* w_end = a.w + (int64_t)(a.T - 1) * a.w_stride + a.K;
+    const float* gw_end = grad_w + (int64_t)(a.T - 1) * gw_stride + a.K;
+    return grad_w < w_end && a.w < gw_end;
+}
+
 }  // namespace
 
 hipError_t launch_combine_backward(const CombineArgs& a, const uint16_t* g, int64_t g_stride, const WindowDesc& gy,
@@ -430,7 +441,8 @@ hipError_t launch_combine_backward(const CombineArgs& a, const uint16_t* g, int6
     // weight gradient is zero then, and y is not read
     if (!grad_w || a.T == 0) {
         launch(combine_backward_kernel<true, false>, nblk);
-    } else if (a.K < kSplitBackwardMinEntries || std::min((int64_t)a.T * a.K, gy.rows_cap) * units * 16 < kSplitBackwardBytes) {
+    } else if (a.K < kSplitBackwardMinEntries || std::min((int64_t)a.T * a.K, gy.rows_cap) * units * 16 < kSplitBackwardBytes ||
+               weights_in_place(a, grad_w, gw_stride)) {
         launch(combine_backward_kernel<true, true>, nblk);
     } else {
         launch(combine_backward_kernel<false, true>, (unsigned)a.T);

@@ -239,6 +239,36 @@ def test_backward_without_any_row_gives_zero_weight_gradients(hx, full):
         ep.ep_group_destroy(group)
 
 
+@pytest.mark.parametrize("T,H", [(300, 512), (1500, 4096)])
+def test_backward_in_place(hx, T, H):
+    """Weight gradients written over the gate weights, row gradients over the expert outputs: as into tensors of
+    their own, also where a call is large enough for two launches (12 000 rows of 8 KiB)."""
+    from paper_2603_13606_amd import binding as ep
+    E, K = 128, 8
+    gen = torch.Generator(hx.DEV).manual_seed(T)
+    topk = torch.randint(0, E, (T, K), generator=gen, device=hx.DEV, dtype=torch.int32)
+    topk[::7, 3] = -1
+    w = torch.rand((T, K + 2), generator=gen, device=hx.DEV)
+    g = torch.randn((T, H), generator=gen, device=hx.DEV).bfloat16()
+    y = torch.randn((T * K, H), generator=gen, device=hx.DEV).bfloat16()
+    group = ep.ep_group_create(ep.make_config(8, E, H, K, T, mode=ep.EP_MODE_HT))
+    try:
+        h = ep.ep_layout(group, topk)
+        want_y, want_w = y.clone(), torch.empty((T, K), device=hx.DEV)
+        ep.ep_combine_backward(h, g, want_y, topk_weights=w[:, :K], y=y, grad_w=want_w)
+        for over_w, over_y in ((True, False), (False, True), (True, True)):
+            w2, y2 = w.clone(), y.clone()
+            gw, gy = (w2[:, :K] if over_w else torch.empty((T, K), device=hx.DEV)), (y2 if over_y else y.clone())
+            ep.ep_combine_backward(h, g, gy, topk_weights=w2[:, :K], y=y2, grad_w=gw)
+            torch.cuda.synchronize()
+            assert torch.equal(gw, want_w) and torch.equal(gy, want_y), (over_w, over_y)
+            assert torch.equal(w2[:, K:], w[:, K:])
+        ep.ep_handle_destroy(h)
+    finally:
+        torch.cuda.synchronize()
+        ep.ep_group_destroy(group)
+
+
 @pytest.mark.parametrize("mode", ["ht", "ll"])
 def test_buffer_autograd_reuses_handle(hx, oracle_mod, mode):
     """One handle through forward and backward of the autograd wrappers: the gradients that come

@@ -173,7 +173,14 @@ class EPBuffer:
                 store = torch.empty((rows, self.H), dtype=torch.bfloat16, device=self.device)
                 grad_y = store.view(self.E, self.C, self.H) if self.ll else store
             grad_w = torch.empty((handle.num_tokens, self.K), dtype=torch.float32, device=self.device) if y is not None else None
-            ep.ep_combine_backward_full(handle.raw, grad_out, grad_y, topk_weights=topk_weights, y=y, grad_w=grad_w, stream=sp)
+            try:
+                ep.ep_combine_backward_full(handle.raw, grad_out, grad_y, topk_weights=topk_weights, y=y, grad_w=grad_w, stream=sp)
+            except ep.EpError as err:
+                if err.code != ep.EP_ERR_UNSUPPORTED:
+                    raise
+                # a handle whose rows lie among another source's (expert_base): the whole window is cleared first
+                grad_y.zero_()
+                ep.ep_combine_backward(handle.raw, grad_out, grad_y, topk_weights=topk_weights, y=y, grad_w=grad_w, stream=sp)
             grad_out.record_stream(self.comm_stream)
             if y is not None:
                 y.record_stream(self.comm_stream)

@@ -269,6 +269,37 @@ def test_backward_in_place(hx, T, H):
         ep.ep_group_destroy(group)
 
 
+def test_buffer_backward_with_rows_among_another_source(hx):
+    """A handle made with expert_base, wrapped for the buffer: combine_backward fills every row without an entry
+    with zeros, as it does for the buffer's own handles."""
+    from paper_2603_13606_amd import binding as ep
+    from paper_2603_13606_amd.buffer import EPBuffer, EPHandle
+    R, E, H, K, T = 4, 16, 256, 4, 60
+    gen = torch.Generator(hx.DEV).manual_seed(4)
+    topk = torch.randint(0, E, (T, K), generator=gen, device=hx.DEV, dtype=torch.int32)
+    count = torch.bincount(topk.reshape(-1).long(), minlength=E)
+    base = (torch.cumsum(count + 3, 0) - count).to(torch.int32)  # three rows of another source ahead of each expert's
+    buf = EPBuffer(R, E, H, K, max_tokens_per_rank=T, mode="ht")
+    try:
+        raw = ep.ep_layout(buf.group, topk, expert_base=base)
+        torch.cuda.synchronize()
+        h = EPHandle(raw, topk, T)
+        rows = T * K + 3 * E + 5
+        g = torch.randn((T, H), generator=gen, device=hx.DEV).bfloat16()
+        y = torch.randn((rows, H), generator=gen, device=hx.DEV).bfloat16()
+        w = torch.rand((T, K), generator=gen, device=hx.DEV)
+        poison = torch.full((rows, H), 7.0, dtype=torch.bfloat16, device=hx.DEV)  # what the allocator hands out next may hold
+        del poison
+        grad_y, grad_w, _ = buf.combine_backward(g, h, w, y)
+        want_y, want_w = torch.zeros_like(y), torch.empty((T, K), device=hx.DEV)
+        ep.ep_combine_backward(raw, g, want_y, topk_weights=w, y=y, grad_w=want_w)
+        torch.cuda.synchronize()
+        assert torch.equal(grad_y, want_y) and torch.equal(grad_w, want_w)
+        buf.destroy_handle(h)
+    finally:
+        buf.close()
+
+
 @pytest.mark.parametrize("mode", ["ht", "ll"])
 def test_buffer_autograd_reuses_handle(hx, oracle_mod, mode):
     """One handle through forward and backward of the autograd wrappers: the gradients that come

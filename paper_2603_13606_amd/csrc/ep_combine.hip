@@ -299,13 +299,19 @@ __global__ __launch_bounds__(256) void combine_hier_kernel(CombineArgs a, int ns
 // gate weights, which one launch holds in registers by then and for which two are not used.
 constexpr int KBB = 8;  // entries handled together
 constexpr int kClearBlocks = 256;
-// Two launches from this many bytes of rows and this many entries per token on (us in two / in one,
-// rows of 14 336 bytes unless given): top-8 26.3/26.7 at 59 MB, 40.2/42.0 at 98 MB, 46.8/50.1 at
-// 117 MB; rows of 2048 bytes 32.0/30.5 at 67 MB, of 5760 top-6 42.6/43.9 at 104 MB; top-4 43.1/44.6 at
-// 98 MB, 94/102 at 235 MB; top-3 75.3/73.3 at 176 MB, top-2 62/54 at 117 MB: there g, read once
-// more, is too large a part.
+// Two launches where they are the faster ones (us in two / in one at 94, 140 and 230 MB of rows):
+// - rows of whole 128-byte lines that start on one: 4160 channels top-8 41.5/44.2, 56.9/60.7, 92.5/99.3, but 4104
+//   channels 49.2/49.3, 69.3/68.9, 112.7/113.5 and 2056 52.5/50.3, 73.0/67.5, 118.6/113.7;
+// - 16384 channels of rows per token, or else g, read once more, is too large a part: top-8 2048 channels 39.7/41.8,
+//   54.6/56.1, 91.2/96.2, top-5 3328 41.1/43.2, 56.5/58.2, 92/98, top-4 4096 41.4/42.1, 60.5/60.2, 94/96.3;
+//   but top-4 2048 59.7/53.6 at 134 MB, top-8 1024 57.8/53.4, top-3 7168 75.3/73.3, top-2 7168 62/53;
+// - rows of 3 KiB: top-12 1536 43.4/44.1, 59.8/58.7, 95/98, top-16 1536 42.5/44.5, 57.2/59.3, 91.7/98.7; 768 83/79
+//   at 150 MB;
+// - up to 32 entries per token: top-32 1536 42.2/44.2, 59.2/64; top-64 2048, few tokens, 56.8/55.1, 72.3/70;
+// - and 88 MiB: top-8 26.3/26.7 at 59 MB of 14 336-byte rows, 40.2/42.0 at 98 MB, 46.8/50.1 at 117 MB.
 constexpr int64_t kSplitBackwardBytes = 88ll << 20;
-constexpr int kSplitBackwardMinEntries = 4;
+constexpr int kSplitBackwardMinHidden = 1536, kSplitBackwardMinEntries = 4, kSplitBackwardMaxEntries = 32;
+constexpr int64_t kSplitBackwardMinToken = 16384;  // channels of a token's rows: K * H
 
 __device__ void clear_unreached_rows(const WindowDesc& gy, const int32_t* reached, int units, int b) {
     const u32x4 zero = {0u, 0u, 0u, 0u};
@@ -423,6 +429,12 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(CombineArgs a, co
     }
 }
 
+bool splits_backward(const CombineArgs& a, const WindowDesc& gy) {
+    const uint64_t line = (uint64_t)(uintptr_t)gy.base | (uint64_t)gy.stride0 * 2 | (uint64_t)gy.stride1 * 2 | (uint64_t)a.H * 2;
+    return line % 128 == 0 && a.K >= kSplitBackwardMinEntries && a.K <= kSplitBackwardMaxEntries && a.H >= kSplitBackwardMinHidden && (int64_t)a.K * a.H >= kSplitBackwardMinToken &&
+           std::min((int64_t)a.T * a.K, gy.rows_cap) * a.H * 2 >= kSplitBackwardBytes;
+}
+
 // Whether the weight gradients share memory with the gate weights (by their spans: columns of one array may be
 // taken for shared, which costs time only).
 bool weights_in_place(const CombineArgs& a, const float* grad_w, int64_t gw_stride) {
@@ -446,8 +458,7 @@ hipError_t launch_combine_backward(const CombineArgs& a, const uint16_t* g, int6
     // weight gradient is zero then, and y is not read
     if (!grad_w || a.T == 0) {
         launch(combine_backward_kernel<true, false>, nblk);
-    } else if (a.K < kSplitBackwardMinEntries || std::min((int64_t)a.T * a.K, gy.rows_cap) * units * 16 < kSplitBackwardBytes ||
-               weights_in_place(a, grad_w, gw_stride)) {
+    } else if (!splits_backward(a, gy) || weights_in_place(a, grad_w, gw_stride)) {
         launch(combine_backward_kernel<true, true>, nblk);
     } else {
         launch(combine_backward_kernel<false, true>, (unsigned)a.T);

@@ -286,7 +286,7 @@ __global__ __launch_bounds__(256) void combine_hier_kernel(CombineArgs a, int ns
 // grad_w = 0 and write nothing.  Bound by HBM: per entry one row read and one written.
 //
 // A caller that wants the rows no entry reaches to be zero has them cleared by the last
-// kClearBlocks workgroups of the launch (`reached` given): only those rows, which are the
+// workgroups of the launch (`reached` given): only those rows, which are the
 // tail of concatenated windows and the slots beyond the kept entries of padded ones.
 // Clearing whole windows before the launch took 58 us at 32768 rows of 14 336 bytes, all of
 // which were then written again; with every row reached these workgroups read one word.
@@ -298,7 +298,14 @@ __global__ __launch_bounds__(256) void combine_hier_kernel(CombineArgs a, int ns
 // either form: grad_y over y, where every unit is read before it is written, and grad_w over the
 // gate weights, which one launch holds in registers by then and for which two are not used.
 constexpr int KBB = 8;  // entries handled together
-constexpr int kClearBlocks = 256;
+// Clearing workgroups: 256 where the rows known to be without an entry are few, more as they are more, and one per
+// piece from three quarters of the windows on, so that the pieces are written front to back.  Pieces of 16 KiB:
+// at 8 KiB a workgroup's start costs more than its stores (101 us), at 64 KiB they are written less in order
+// (98 us; 89 us at 16 KiB: 128 tokens top-8 in 470 MB of windows).  Measured against a fill of the whole windows and
+// the backward after it: 470 MB 91/92 us, 201 MB of 6144-byte rows 38/43, 134 MB of 512-byte rows 26/30, 2 MB 7.5/9.3,
+// half reached 152/187, four fifths 199/285; windows of 1 GB with 128 tokens in them 193/177.
+constexpr int64_t kClearBlocks = 256, kClearMaxBlocks = 1 << 20;
+constexpr int64_t kClearPiece = 1024;  // 16-byte units
 // Two launches where they are the faster ones (us in two / in one at 94, 140 and 230 MB of rows):
 // - rows of whole 128-byte lines that start on one: 4160 channels top-8 41.5/44.2, 56.9/60.7, 92.5/99.3, but 4104
 //   channels 49.2/49.3, 69.3/68.9, 112.7/113.5 and 2056 52.5/50.3, 73.0/67.5, 118.6/113.7;
@@ -313,22 +320,36 @@ constexpr int64_t kSplitBackwardBytes = 88ll << 20;
 constexpr int kSplitBackwardMinHidden = 1536, kSplitBackwardMinEntries = 4, kSplitBackwardMaxEntries = 32;
 constexpr int64_t kSplitBackwardMinToken = 16384;  // channels of a token's rows: K * H
 
-__device__ void clear_unreached_rows(const WindowDesc& gy, const int32_t* reached, int units, int b) {
+// How the clearing workgroups share the windows (see plan_clear): `share` workgroups per window, or, with
+// fewer workgroups than windows, one for every `step`-th window.
+struct ClearPlan {
+    unsigned windows, share, step;
+};
+
+// Clearing workgroup b.  A window (the rows, where there is one window) is cut into pieces of kClearPiece
+// 16-byte units whatever its rows; a workgroup takes the pieces of its window that hold unreached units in turn.
+__device__ void clear_unreached_rows(const WindowDesc& gy, const int32_t* reached, int units, const ClearPlan& c, unsigned b) {
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    if (!gy.padded) {  // *reached = one past the last row
-        const int64_t first = max(*reached, 0);
-        for (int64_t r = first + b; r < gy.rows_cap; r += kClearBlocks) {
-            u32x4* row = (u32x4*)(gy.base + r * gy.stride0);
-            for (int u = threadIdx.x; u < units; u += blockDim.x) __builtin_nontemporal_store(zero, row + u);
-        }
-        return;
-    }
-    const int E = (int)(gy.rows_cap / gy.C);     // reached[e] = slots of expert e in use
-    const int share = max(1, kClearBlocks / E);  // workgroups per expert
-    for (int e = b / share; e < E; e += kClearBlocks / share) {
-        for (int s = reached[e] + b % share; s < gy.C; s += share) {
-            u32x4* row = (u32x4*)(gy.base + (int64_t)e * gy.stride0 + (int64_t)s * gy.stride1);
-            for (int u = threadIdx.x; u < units; u += blockDim.x) __builtin_nontemporal_store(zero, row + u);
+    const int64_t total = (gy.padded ? gy.C : gy.rows_cap) * units;  // of a window
+    const int64_t pitch = gy.padded ? gy.stride1 : gy.stride0;
+    const bool dense = pitch == (int64_t)units * 8;  // rows back to back: no division
+    const unsigned e0 = b / c.share, part = b - e0 * c.share;
+    for (unsigned e = e0; e < c.windows; e += c.step) {
+        const int64_t first = (int64_t)max(reached[e], 0) * units;  // slots of window e in use; one past the last row
+        uint16_t* win = gy.base + e * gy.stride0;
+        unsigned p = (unsigned)(first / kClearPiece);  // the first piece that is not all in use, then the first of this workgroup
+        const unsigned turn = p < c.share ? p : p % c.share;
+        p += part >= turn ? part - turn : part + c.share - turn;
+        for (; (int64_t)p * kClearPiece < total; p += c.share) {
+            const int64_t end = min(total, ((int64_t)p + 1) * kClearPiece);
+            for (int64_t u = max(first, (int64_t)p * kClearPiece) + threadIdx.x; u < end; u += blockDim.x) {
+                int64_t at = u * 8;
+                if (!dense) {
+                    const int64_t row = total >> 32 ? u / units : (int64_t)((uint32_t)u / (uint32_t)units);
+                    at = row * pitch + (u - row * units) * 8;
+                }
+                __builtin_nontemporal_store(zero, (u32x4*)(win + at));
+            }
         }
     }
 }
@@ -339,11 +360,11 @@ __device__ void clear_unreached_rows(const WindowDesc& gy, const int32_t* reache
 template <bool ROWS, bool WEIGHTS>
 __global__ __launch_bounds__(256) void combine_backward_kernel(CombineArgs a, const uint16_t* g, int64_t g_stride,
                                                                WindowDesc gy, float* grad_w, int64_t gw_stride, int units,
-                                                               const int32_t* reached) {
+                                                               const int32_t* reached, ClearPlan clear) {
     __shared__ float part[4][KBB];
     const int t = blockIdx.x;
     if (t >= a.T) {  // a whole workgroup
-        clear_unreached_rows(gy, reached, units, t - a.T);
+        clear_unreached_rows(gy, reached, units, clear, t - a.T);
         return;
     }
     const bool reads_y = WEIGHTS && (!ROWS || a.win.base);
@@ -429,6 +450,19 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(CombineArgs a, co
     }
 }
 
+// Returns the number of clearing workgroups of a launch.
+unsigned plan_clear(const CombineArgs& a, const WindowDesc& gy, ClearPlan* plan) {
+    const int64_t windows = gy.padded ? gy.rows_cap / gy.C : 1, slots = gy.padded ? gy.C : gy.rows_cap, units = a.H / 8;
+    const int64_t per_window = (slots * units + kClearPiece - 1) / kClearPiece, pieces = windows * per_window;
+    const int64_t unreached = gy.rows_cap - std::min((int64_t)a.T * a.K, gy.rows_cap);  // at least
+    int64_t n = std::max(kClearBlocks, 4 * unreached >= 3 * gy.rows_cap ? pieces : unreached * units / kClearPiece);
+    n = std::min(n, std::min(pieces, kClearMaxBlocks));
+    const int64_t share = std::max<int64_t>(1, (n + windows - 1) / windows);  // the same number for every window
+    if (n > windows) n = share * windows;
+    *plan = {(unsigned)windows, (unsigned)share, (unsigned)(share > 1 ? windows : std::max<int64_t>(n, 1))};
+    return (unsigned)n;
+}
+
 bool splits_backward(const CombineArgs& a, const WindowDesc& gy) {
     const uint64_t line = (uint64_t)(uintptr_t)gy.base | (uint64_t)gy.stride0 * 2 | (uint64_t)gy.stride1 * 2 | (uint64_t)a.H * 2;
     return line % 128 == 0 && a.K >= kSplitBackwardMinEntries && a.K <= kSplitBackwardMaxEntries && a.H >= kSplitBackwardMinHidden && (int64_t)a.K * a.H >= kSplitBackwardMinToken &&
@@ -448,11 +482,12 @@ bool weights_in_place(const CombineArgs& a, const float* grad_w, int64_t gw_stri
 
 hipError_t launch_combine_backward(const CombineArgs& a, const uint16_t* g, int64_t g_stride, const WindowDesc& gy,
                                    float* grad_w, int64_t gw_stride, const int32_t* reached, hipStream_t s) {
-    const unsigned nblk = (unsigned)a.T + (reached ? kClearBlocks : 0);
+    ClearPlan clear = {};
+    const unsigned nblk = (unsigned)a.T + (reached ? plan_clear(a, gy, &clear) : 0);
     if (nblk == 0) return hipSuccess;
     const int units = a.H / 8;
     auto launch = [&](auto kernel, unsigned blocks) {
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, a, g, g_stride, gy, grad_w, gw_stride, units, reached);
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, a, g, g_stride, gy, grad_w, gw_stride, units, reached, clear);
     };
     // by what is asked for, not by the address of y: expert outputs of no rows may come without one; every
     // weight gradient is zero then, and y is not read

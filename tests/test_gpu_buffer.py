@@ -130,13 +130,19 @@ def test_backward_calls_match_the_oracle_composition(hx, oracle_mod, name, T, H,
         buf.close()
 
 
-@pytest.mark.parametrize("E,T,C", [(8, 40, 0), (8, 40, 3), (8, 40, 90), (96, 7, 5), (768, 30, 4), (8, 0, 0), (8, 0, 4)])
-def test_backward_clears_exactly_the_rows_without_an_entry(hx, oracle_mod, E, T, C):
+@pytest.mark.parametrize("E,T,C,H,gap,extra", [
+    (8, 40, 0, 136, 8, 3), (8, 40, 3, 136, 8, 0), (8, 40, 90, 136, 8, 0), (96, 7, 5, 136, 8, 0), (768, 30, 4, 136, 8, 0),
+    (8, 0, 0, 136, 8, 3), (8, 0, 4, 136, 8, 0),
+    # rows back to back: several pieces per window, rows that straddle them; rows of one unit; one piece per window
+    (16, 3, 200, 2056, 0, 0), (16, 10, 700, 8, 0, 0), (16, 10, 700, 8, 8, 0), (304, 2, 3, 64, 0, 0),
+    (8, 40, 0, 520, 0, 3000), (8, 900, 0, 2056, 8, 500), (8, 900, 1100, 512, 0, 0), (8, 900, 60, 512, 8, 0),
+])
+def test_backward_clears_exactly_the_rows_without_an_entry(hx, oracle_mod, E, T, C, H, gap, extra):
     """ep_combine_backward_full into poisoned windows: rows of entries as ep_combine_backward leaves them,
     every other row zero, nothing outside the rows (a strided window); C = 0 is the concatenated layout.  More
     experts than the clearing workgroups (768), a number that does not divide them (96), empty inputs."""
     from paper_2603_13606_amd import binding as ep
-    H, K, B = 136, 4, max(T, 1)
+    K, B = 4, max(T, 1)
     gen = torch.Generator(hx.DEV).manual_seed(E + T)
     topk = torch.randint(0, E, (T, K), generator=gen, device=hx.DEV, dtype=torch.int32)
     topk[::5, 1] = -1
@@ -145,11 +151,11 @@ def test_backward_clears_exactly_the_rows_without_an_entry(hx, oracle_mod, E, T,
     group = ep.ep_group_create(cfg)
     try:
         h = ep.ep_layout(group, topk)
-        rows = E * C if C else B * K + 3
+        rows = E * C if C else B * K + extra
         g = torch.randn((T, H), generator=gen, device=hx.DEV).bfloat16()
-        store = torch.full((rows, H + 8), 7.0, dtype=torch.bfloat16, device=hx.DEV)
+        store = torch.full((rows, H + gap), 7.0, dtype=torch.bfloat16, device=hx.DEV)
         plain = store.clone()
-        win = lambda s: (s.view(E, C, H + 8) if C else s)[..., :H]
+        win = lambda s: (s.view(E, C, H + gap) if C else s)[..., :H]
         ep.ep_combine_backward_full(h, g, win(store))
         ep.ep_combine_backward(h, g, win(plain))
         torch.cuda.synchronize()

@@ -133,19 +133,29 @@ int64_t carve(int64_t* cursor, int64_t ints) {
     return at;
 }
 
-// Whether layouts of the group record the runs the destination-ordered walk needs: when the group
-// asks for that order, and for the once-per-rank path into concatenated windows where the send and the
+// Whether a layout of T tokens records the runs the destination-ordered walk needs: from kRunOrderMinEntries
+// entries on, when the group asks for that order, and for the once-per-rank path into concatenated windows where the send and the
 // ordered walk beat the one launch that does both (layout + dispatch, us in one / in two, even routing unless
 // said): rows of 14 336 bytes, top-8, 64.8/59.2 at 1100 tokens, 216/180 at 4096 (hot ranks 169/146), 409/345 at
 // 8192; of 8192 bytes, top-4, 129/116 at 8192 tokens; of 4096 bytes 69.0/65.7; but of 1024 bytes 26/40 -- the
-// walk's workgroups copy too little each -- and top-2 61.9/62.8 (hot 57/61), where most messages are rows.
+// walk's workgroups copy too little each -- and top-2 61.9/62.8 (hot 57/61), where most messages are rows.  The
+// table costs a layout 0.2 to 1.1 us, so inputs that the walk does not take have none; that a call will be split
+// into phases, which do not walk either, the layout cannot know.
 constexpr int kOnceOrderedMinHidden = 2048;
 constexpr int kOnceOrderedMinTopK = 4;
 constexpr int64_t kOnceOrderedMaxTokenBytes = 128ll << 20;  // half of the memory-side cache; measured up to 117 MB
 
-bool records_runs(const ep_group_config_t& c) {
+bool records_runs(const ep_group_config_t& c, int64_t T) {
+    if (T * c.top_k < kRunOrderMinEntries) return false;
     if (c.dispatch_path == EP_PATH_DIRECT) return c.dispatch_order != EP_ORDER_TOKEN;
-    return c.mode == EP_MODE_HT && c.hidden >= kOnceOrderedMinHidden && c.top_k >= kOnceOrderedMinTopK;
+    return c.mode == EP_MODE_HT && c.hidden >= kOnceOrderedMinHidden && c.top_k >= kOnceOrderedMinTopK &&
+           2 * T * c.hidden <= kOnceOrderedMaxTokenBytes;
+}
+
+// Whether any layout of the group does: from the smallest input that can on.
+bool may_record_runs(const ep_group_config_t& c) {
+    const int64_t least = (kRunOrderMinEntries + c.top_k - 1) / c.top_k;
+    return least <= c.max_tokens_per_rank && records_runs(c, least);
 }
 
 // Lays the handle arrays out inside one allocation; with base == nullptr only the size is computed.
@@ -157,7 +167,7 @@ int64_t carve_slab(const ep_group_s* g, Slab* s, int32_t* base) {
     const int64_t o_eo = carve(&cur, E + 1), o_op = carve(&cur, E + 1), o_rp = carve(&cur, R);
     const int64_t o_rt = carve(&cur, R), o_ro = carve(&cur, R + 1);
     const int64_t o_h = carve(&cur, (int64_t)kMaxChunks * g->W), o_ctl = carve(&cur, kLayoutCtlWords);
-    const bool runs = records_runs(g->cfg);
+    const bool runs = may_record_runs(g->cfg);
     const int64_t o_rn = runs ? carve(&cur, (int64_t)(kMaxWaveChunks + 1) * E) : 0;
     const int64_t o_sl = carve(&cur, nB), o_dr = carve(&cur, nB), o_rr = carve(&cur, nB);
     const int64_t o_st = carve(&cur, nB), o_sk = carve(&cur, nB), o_sr = carve(&cur, nB), o_er = carve(&cur, nB);
@@ -381,7 +391,7 @@ ep_result_t ep_dispatch_plan(const ep_group_config_t* cfg, int64_t num_tokens, i
         num_tokens * cfg->top_k > (1 << 28))
         return EP_ERR_INVALID_ARG;
     DispatchPlan d;
-    // layouts of more than 1024 entries record the runs whenever the group asks for them
+    // whenever the group asks for the order and the input is large enough for it, its layout records the runs
     const bool have_runs = cfg->dispatch_order != EP_ORDER_TOKEN && cfg->dispatch_path == EP_PATH_DIRECT;
     plan_dispatch((int)num_tokens, cfg->top_k, cfg->hidden, cfg->num_experts, cfg->dispatch_order, have_runs,
                   (int)std::min<int64_t>(prefetched_rows, num_tokens), &d);
@@ -631,10 +641,10 @@ static ep_result_t prepare_layout(ep_handle_t* handle, ep_group_t g, const ep_te
     a.slot = s.slot; a.dst_row = s.dst_row; a.rank_row = s.rank_row; a.sorted_token = s.sorted_token;
     a.sorted_k = s.sorted_k; a.sorted_row = s.sorted_row;
     a.entry_rank = s.entry_rank;
-    a.run_start = records_runs(c) ? s.run_start : nullptr;
+    a.run_start = records_runs(c, T) ? s.run_start : nullptr;
     a.warm_x = nullptr; a.warm_stride = 0; a.warm_rows = 0; a.warm_units = c.hidden / 8; a.nchunks = 1;
     a.rows_cap = -1; a.recv_count = nullptr;
-    a.drop_hint = (a.padded && a.run_start) ? g->drop_hint_dev : nullptr;
+    a.drop_hint = g->drop_hint_dev;  // there for padded windows in destination order
     a.quant_out = nullptr; a.quant_pitch = 0;
     h->quant_x = nullptr;
     if (tokens && a.run_start && c.dispatch_order == EP_ORDER_DESTINATION && c.dispatch_path == EP_PATH_DIRECT) {
@@ -860,7 +870,7 @@ ep_result_t ep_dispatch(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_in
     sa.hdr_units = (int)(g->hdr_bytes / 16);
     sa.totals = s.totals;
     sa.T = h->T; sa.K = c.top_k; sa.H = c.hidden;
-    if (!send_only && a.run_start && 2ll * sa.T * c.hidden <= kOnceOrderedMaxTokenBytes) {
+    if (!send_only && a.run_start) {
         // large enough for the destination-ordered walk, and the tokens the send has just read stay in the
         // memory-side cache: the rows are written in that order by a launch of their own
         a.order = EP_ORDER_DESTINATION_RESIDENT;

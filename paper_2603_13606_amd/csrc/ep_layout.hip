@@ -862,7 +862,8 @@ bool layout_prefetches(const LayoutArgs& a) {
 constexpr int64_t kFusedMaxBytes = 176ll << 20;
 
 bool layout_dispatch_fusable(const LayoutArgs& a, const DispatchArgs& d) {
-    if (d.order != EP_ORDER_TOKEN && a.run_start && a.n >= kRunOrderMinEntries) return false;  // may go in destination order
+    // may go in destination order; and the runs are recorded by the cut of the plan, which this launch may change
+    if (a.run_start) return false;
     if (((int64_t)a.n + a.T) * d.H * 2 > kFusedMaxBytes) return false;
     return a.n >= 1 && a.n <= kFusedMaxEntries && a.K <= kWave && a.E <= kLayoutWavesPerBlock * kWave && d.H >= 8 &&
            lds_bytes(a, kLayoutWavesPerBlock) <= kLdsLimit;

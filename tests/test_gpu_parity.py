@@ -1229,6 +1229,36 @@ def test_allocator_callbacks_and_lifecycle(ep, hx):
     assert not held
 
 
+@pytest.mark.parametrize("path", ["direct", "once"])
+def test_handles_hold_a_run_table_only_where_a_dispatch_can_read_it(ep, hx, path):
+    """What a handle takes, by the allocator callback: the table of run starts, 513 * E words, is part of it from
+    the smallest group that can dispatch in destination order on (8192 routed entries), in no other."""
+    E, R, K = 64, 4, 8
+    once = path == "once"
+
+    def slab_bytes(B, H, order):
+        sizes, held = [], {}
+
+        def alloc(pp, nbytes):
+            t = torch.empty(int(nbytes), dtype=torch.uint8, device=hx.DEV)
+            held[t.data_ptr()], pp[0] = t, t.data_ptr()
+            sizes.append(int(nbytes))
+            return 0
+
+        def free(p):
+            return 0 if held.pop(p, None) is not None else 1
+        a, f = ep.ALLOC_FN(alloc), ep.FREE_FN(free)
+        cfg = ep.make_config(R, E, H, K, B, max_handles=3, dispatch_order=order,
+                             dispatch_path=ep.EP_PATH_RANK_DEDUP if once else ep.EP_PATH_DIRECT)
+        ep.ep_group_destroy(ep.ep_group_create(cfg, alloc_fn=a, free_fn=f))
+        assert not held and len(set(sizes[-3:])) == 1  # the slabs come last
+        return sizes[-1]
+    without = dict(H=2040, order=0) if once else dict(H=2048, order=0)
+    with_runs = dict(H=2048, order=0) if once else dict(H=2048, order=1)
+    assert slab_bytes(1023, **with_runs) == slab_bytes(1023, **without)
+    assert slab_bytes(1024, **with_runs) >= slab_bytes(1024, **without) + 513 * E * 4
+
+
 @pytest.mark.parametrize("nbytes", [16, 4096 + 16, (3 << 20) + 48, 17 * 4096 * 16 + 16 * 1023])
 def test_measurement_kernels(ep, hx, nbytes):
     """The copy, fill and read kernels the bandwidth figures are measured against: the copy moves

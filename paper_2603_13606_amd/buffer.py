@@ -90,7 +90,13 @@ class EPBuffer:
             self.comm_stream.wait_stream(compute)
         return compute
 
-    def _leave(self, compute: torch.cuda.Stream) -> torch.cuda.Event:
+    def _leave(self, compute: torch.cuda.Stream, *outputs: Optional[torch.Tensor]) -> torch.cuda.Event:
+        """Makes the compute stream wait.  The outputs were allocated on the communication stream and are used on the
+        compute stream: their memory must not come back to a later call, which may be told to wait for an earlier
+        event only, before that use has ended."""
+        for t in outputs:
+            if t is not None:
+                t.record_stream(compute)
         ev = torch.cuda.Event()
         ev.record(self.comm_stream)
         compute.wait_event(ev)  # compute waits for communication
@@ -140,11 +146,10 @@ class EPBuffer:
                 handle = EPHandle(raw, topk_idx, T)
             else:
                 ep._check(ep.load().ep_dispatch(handle.raw, ins, n_in, outs, len(outs), 0, sp), "ep_dispatch")
-            # the outputs were allocated on this stream, the inputs were not
             x.record_stream(self.comm_stream)
             if topk_weights is not None:
                 topk_weights.record_stream(self.comm_stream)
-        ev = self._leave(compute)
+        ev = self._leave(compute, store, recv_w, recv_src, scales)
         return ((recv_x, scales) if fp8 else recv_x), recv_src, recv_w, handle, ev
 
     def combine(self, y: torch.Tensor, handle: EPHandle, topk_weights: Optional[torch.Tensor] = None,
@@ -156,7 +161,7 @@ class EPBuffer:
             out = torch.empty((handle.num_tokens, self.H), dtype=torch.bfloat16, device=self.device)
             ep.ep_combine(handle.raw, y, out, topk_weights=topk_weights, stream=sp)
             y.record_stream(self.comm_stream)
-        return out, self._leave(compute)
+        return out, self._leave(compute, out)
 
     def combine_backward(self, grad_out: torch.Tensor, handle: EPHandle, topk_weights: Optional[torch.Tensor] = None,
                          y: Optional[torch.Tensor] = None, previous_event: Optional[torch.cuda.Event] = None):
@@ -184,7 +189,7 @@ class EPBuffer:
             grad_out.record_stream(self.comm_stream)
             if y is not None:
                 y.record_stream(self.comm_stream)
-        return grad_y, grad_w, self._leave(compute)
+        return grad_y, grad_w, self._leave(compute, grad_y, grad_w)
 
     def get_tokens_per_expert_list(self) -> List[int]:
         """Rows placed per expert by the last dispatch, read from the pinned counter."""

@@ -306,6 +306,49 @@ def test_buffer_backward_with_rows_among_another_source(hx):
         buf.close()
 
 
+def test_outputs_dropped_while_compute_still_reads_them_are_not_handed_out_again(hx):
+    """Work on the results of three calls is queued, the results are dropped, and the next calls wait for an
+    earlier event only (overlap): they get other memory while that work is pending, and it reads what it was given."""
+    from paper_2603_13606_amd.buffer import EPBuffer
+    R, E, H, K, T = 4, 16, 512, 4, 256
+    gen = torch.Generator(hx.DEV).manual_seed(8)
+    topk = torch.randint(0, E, (T, K), generator=gen, device=hx.DEV, dtype=torch.int32)
+    gate = torch.rand((T, K), generator=gen, device=hx.DEV)
+    xs = [torch.randn((T, H), generator=gen, device=hx.DEV).bfloat16() for _ in range(2)]
+    buf = EPBuffer(R, E, H, K, max_tokens_per_rank=T, mode="ht")
+    try:
+        torch.cuda.synchronize()
+        early = buf.capture()
+        y = torch.randn((T * K, H), generator=gen, device=hx.DEV).bfloat16()
+        recv_x, recv_src, recv_w, h, _ = buf.dispatch(xs[0], topk, gate)
+        out, _ = buf.combine(recv_x, h, gate)
+        grad_y, grad_w, _ = buf.combine_backward(xs[1], h, gate, y)
+        first = [recv_x, recv_src, recv_w, out, grad_y, grad_w]
+        want, got = [t.clone() for t in first], [torch.empty_like(t) for t in first]
+        spans = [(t.data_ptr(), t.data_ptr() + t.numel() * t.element_size()) for t in first]
+        torch.cuda.synchronize()
+        torch.cuda._sleep(100_000_000)  # the compute stream is behind from here on
+        for a, b in zip(got, first):
+            a.copy_(b)
+        end = buf.capture()
+        del recv_x, recv_src, recv_w, out, grad_y, grad_w, first, b
+        second = buf.dispatch(xs[1], topk, gate, previous_event=early)
+        h2 = second[3]
+        again = [*second[:3], buf.combine(y, h, gate, previous_event=early)[0],
+                 *buf.combine_backward(xs[0], h, gate, y, previous_event=early)[:2]]
+        assert not end.query(), "the reads were over too early for this test to say anything"
+        for t in again:
+            lo, hi = t.data_ptr(), t.data_ptr() + t.numel() * t.element_size()
+            assert all(hi <= a or b <= lo for a, b in spans)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+        buf.destroy_handle(h)
+        buf.destroy_handle(h2)
+    finally:
+        torch.cuda.synchronize()
+        buf.close()
+
+
 @pytest.mark.parametrize("mode", ["ht", "ll"])
 def test_buffer_autograd_reuses_handle(hx, oracle_mod, mode):
     """One handle through forward and backward of the autograd wrappers: the gradients that come

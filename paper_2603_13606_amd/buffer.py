@@ -146,9 +146,9 @@ class EPBuffer:
                 handle = EPHandle(raw, topk_idx, T)
             else:
                 ep._check(ep.load().ep_dispatch(handle.raw, ins, n_in, outs, len(outs), 0, sp), "ep_dispatch")
-            x.record_stream(self.comm_stream)
-            if topk_weights is not None:
-                topk_weights.record_stream(self.comm_stream)
+            for t in (x, ids, topk_weights):
+                if t is not None:
+                    t.record_stream(self.comm_stream)
         ev = self._leave(compute, store, recv_w, recv_src, scales)
         return ((recv_x, scales) if fp8 else recv_x), recv_src, recv_w, handle, ev
 
@@ -161,6 +161,8 @@ class EPBuffer:
             out = torch.empty((handle.num_tokens, self.H), dtype=torch.bfloat16, device=self.device)
             ep.ep_combine(handle.raw, y, out, topk_weights=topk_weights, stream=sp)
             y.record_stream(self.comm_stream)
+            if topk_weights is not None:
+                topk_weights.record_stream(self.comm_stream)
         return out, self._leave(compute, out)
 
     def combine_backward(self, grad_out: torch.Tensor, handle: EPHandle, topk_weights: Optional[torch.Tensor] = None,
@@ -186,9 +188,9 @@ class EPBuffer:
                 # a handle whose rows lie among another source's (expert_base): the whole window is cleared first
                 grad_y.zero_()
                 ep.ep_combine_backward(handle.raw, grad_out, grad_y, topk_weights=topk_weights, y=y, grad_w=grad_w, stream=sp)
-            grad_out.record_stream(self.comm_stream)
-            if y is not None:
-                y.record_stream(self.comm_stream)
+            for t in (grad_out, topk_weights, y):
+                if t is not None:
+                    t.record_stream(self.comm_stream)
         return grad_y, grad_w, self._leave(compute, grad_y, grad_w)
 
     def get_tokens_per_expert_list(self) -> List[int]:

@@ -349,6 +349,61 @@ def test_outputs_dropped_while_compute_still_reads_them_are_not_handed_out_again
         buf.close()
 
 
+@pytest.mark.parametrize("call", ["dispatch", "combine", "combine_backward"])
+def test_inputs_of_a_third_stream_dropped_behind_a_call_are_not_handed_out_again(hx, call):
+    """Every input comes from a stream that is neither the compute nor the communication stream and is dropped once the
+    call is queued: that stream gets other memory until the call has run, and the results are those of a call alone."""
+    from paper_2603_13606_amd.buffer import EPBuffer
+    R, E, H, K, T = 4, 16, 512, 4, 256
+    side = torch.cuda.Stream()
+    buf = EPBuffer(R, E, H, K, max_tokens_per_rank=T, mode="ht")
+
+    def inputs():
+        with torch.cuda.stream(side):
+            gen = torch.Generator(hx.DEV).manual_seed(9)
+            topk = torch.randint(0, E, (T, K), generator=gen, device=hx.DEV, dtype=torch.int32)
+            w = torch.rand((T, K), generator=gen, device=hx.DEV)
+            x, y = (torch.randn((n, H), generator=gen, device=hx.DEV).bfloat16() for n in (T, T * K))
+        side.synchronize()
+        return topk, w, x, y
+
+    def run(topk, w, x, y, h):
+        if call == "dispatch":
+            r = buf.dispatch(x, topk, w)
+            r[3].topk_idx = None  # the handle would keep the ids
+            return r[:3], r[3]
+        return (buf.combine(y, h, w)[:1] if call == "combine" else buf.combine_backward(x, h, w, y)[:2]), None
+
+    try:
+        made = inputs()
+        h = buf.dispatch(made[2], made[0], made[1])[3]
+        h.topk_idx = None
+        alone, h1 = run(*made, h)
+        want = [t.clone() for t in alone]
+        torch.cuda.synchronize()
+        del made
+        made = inputs()
+        used = {"dispatch": made[:3], "combine": (made[1], made[3]), "combine_backward": made[1:]}[call]
+        spans = [(t.data_ptr(), t.data_ptr() + t.numel() * t.element_size()) for t in used]
+        torch.cuda._sleep(100_000_000)
+        end = buf.capture()
+        got, h2 = run(*made, h)
+        del used, made
+        taken = inputs()
+        assert not end.query(), "the call ran too early for this test to say anything"
+        for t in taken:
+            lo, hi = t.data_ptr(), t.data_ptr() + t.numel() * t.element_size()
+            assert all(hi <= a or b <= lo for a, b in spans)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+        for made in (h, h1, h2):
+            if made is not None:
+                buf.destroy_handle(made)
+    finally:
+        torch.cuda.synchronize()
+        buf.close()
+
+
 @pytest.mark.parametrize("mode", ["ht", "ll"])
 def test_buffer_autograd_reuses_handle(hx, oracle_mod, mode):
     """One handle through forward and backward of the autograd wrappers: the gradients that come

@@ -404,6 +404,67 @@ def test_inputs_of_a_third_stream_dropped_behind_a_call_are_not_handed_out_again
         buf.close()
 
 
+@pytest.mark.parametrize("C", [0, 100])
+def test_large_backward_through_strided_windows_and_special_values(hx, C):
+    """12 000 rows of 8 KiB in windows with a pitch: 128 bytes more per row (two launches) and 16 more (rows that start
+    anywhere in a line, one launch).  Same bits, infinities and NaN among gradients, weights and expert outputs
+    included; the row gradients are the float32 product rounded once, the weight gradients the float64 sums within
+    the bound of a float32 sum of 4096 terms added 16 to a thread, 64 threads, 4 waves."""
+    from paper_2603_13606_amd import binding as ep
+    from test_gpu_parity import _kernel_launches
+    E, T, H, K = 128, 1500, 4096, 8
+    gen = torch.Generator(hx.DEV).manual_seed(C + 1)
+    topk = torch.randint(0, E, (T, K), generator=gen, device=hx.DEV, dtype=torch.int32)
+    topk[::7, 3] = -1
+    w = torch.rand((T, K), generator=gen, device=hx.DEV)
+    w[5, 1], w[6, 2], w[7, 0] = float("inf"), float("nan"), 0.0
+    gs = torch.randn((T, H + 64), generator=gen, device=hx.DEV).bfloat16()
+    g = gs[:, :H]
+    g[9, 100], g[10, 200], g[11, 4095] = float("inf"), float("nan"), float("-inf")
+    rows = E * C if C else T * K
+    y = torch.randn((rows, H), generator=gen, device=hx.DEV).bfloat16()
+    y[40, 7], y[41, 8] = float("inf"), float("nan")
+    group = ep.ep_group_create(ep.make_config(8, E, H, K, T, mode=ep.EP_MODE_LL if C else ep.EP_MODE_HT, slots_per_subregion=C))
+    try:
+        h = ep.ep_layout(group, topk)
+        dst = ep.read_device_i32(ep.ep_handle_query(h).dst_row, T * K).view(T, K).to(hx.DEV).long()
+        got = []
+        for gap, launches in ((64, 2), (8, 1)):
+            def win(fill):
+                s = torch.full((rows, H + gap), 7.0, dtype=torch.bfloat16, device=hx.DEV)
+                s[:, :H] = fill
+                return s, (s.view(E, C, H + gap) if C else s)[..., :H]
+            ys, gys = win(y), win(7.0)
+            gw = torch.full((T, K), 7.0, device=hx.DEV)
+            call = lambda s=None: ep.ep_combine_backward(h, g, gys[1], topk_weights=w, y=ys[1], grad_w=gw, stream=s)
+            call()
+            torch.cuda.synchronize()
+            assert torch.all(gys[0][:, H:] == 7.0)
+            got.append((gys[0][:, :H].clone(), gw))
+            assert _kernel_launches(ep, call) == launches
+        assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16))
+        assert torch.equal(got[0][1].view(torch.int32), got[1][1].view(torch.int32))
+        gy, gw = got[0]
+        has = dst >= 0
+        want = torch.full((rows, H), 7.0, dtype=torch.bfloat16, device=hx.DEV)
+        for k in range(K):
+            m = has[:, k]
+            want[dst[m, k]] = (w[m, k, None] * g[m].float()).bfloat16()
+        assert torch.equal(torch.isnan(gy), torch.isnan(want)) and torch.equal(gy.nan_to_num(nan=3.0), want.nan_to_num(nan=3.0))
+        assert torch.all(gw[~has] == 0.0)
+        for k in range(K):
+            m = has[:, k]
+            terms = y[dst[m, k]].double() * g[m].double()
+            ref, mag, out = terms.sum(1), terms.abs().sum(1), gw[m, k].double()
+            fin = torch.isfinite(ref)
+            assert torch.equal(torch.isnan(out), torch.isnan(ref)) and torch.equal(out[torch.isinf(ref)], ref[torch.isinf(ref)])
+            assert torch.all((out - ref).abs()[fin] <= (16 + 6 + 3 + 1) * 2.0 ** -24 * mag[fin])
+        ep.ep_handle_destroy(h)
+    finally:
+        torch.cuda.synchronize()
+        ep.ep_group_destroy(group)
+
+
 @pytest.mark.parametrize("mode", ["ht", "ll"])
 def test_buffer_autograd_reuses_handle(hx, oracle_mod, mode):
     """One handle through forward and backward of the autograd wrappers: the gradients that come

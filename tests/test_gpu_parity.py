@@ -640,7 +640,7 @@ def test_dispatch_combine_parity(ep, hx, oracle_mod, name, T, H, mode, C):
 
 
 FUSED_CASES = [
-    # inputs of at most 1024 routed entries: ep_layout_dispatch lays out and dispatches in one launch
+    # small inputs: ep_layout_dispatch lays out and dispatches in one launch
     ("ll_decode", None, None, "ll", 0, 0),     # the decode shape, padded windows
     ("ll_decode", None, None, "ht", 0, 0),     # concatenated windows
     ("ll_decode", 127, None, "ll", 16, 0),     # capacity drops, ragged last wave
@@ -651,7 +651,7 @@ FUSED_CASES = [
     ("tiny", 1, None, "ht", 0, 0),             # one token
     ("skew", 100, None, "ll", 7, 0),           # 800 entries on 128 experts, most of them dropped
     ("skew", 128, 4096, "ht", 0, 0),           # exactly 1024 entries
-    ("ll_decode", 129, 512, "ht", 0, 0),       # 1032 entries: falls back to two launches
+    ("ll_decode", 129, 512, "ht", 0, 0),       # 1032 entries: more than one id per thread
     ("ht_prefill", 1500, 256, "ht", 0, 1),     # large input: two launches, destination order with read-ahead
 ]
 
@@ -761,7 +761,8 @@ def test_layout_dispatch_one_call_errors_and_overflow(ep, hx, oracle_mod):
     (1023, 8, 128, 1032, 90, False, 0), (1024, 8, 64, 256, 0, True, 0),  # three tokens per workgroup; the most entries
     (8192, 1, 8, 64, 0, False, 0), (4095, 2, 32, 8, 0, False, 0),        # eighteen, and nine, tokens per workgroup
     (127, 64, 64, 200, 0, False, 0), (480, 17, 51, 128, 60, False, 0),   # a token fills the lanes; three tokens are 51 lanes
-    (97, 33, 1020, 1024, 0, False, 0), (700, 8, 256, 64, 0, False, 100), (700, 8, 256, 64, 0, True, 100),  # output too short
+    (97, 33, 1020, 1024, 0, False, 0), (97, 33, 810, 1024, 0, False, 0),  # too many bins for one launch, and about the most
+    (700, 8, 256, 64, 0, False, 100), (700, 8, 256, 64, 0, True, 100),  # output too short
 ])
 def test_layout_dispatch_one_launch_of_up_to_8192_entries(ep, hx, T, K, E, H, C, base, cut):
     """ep_layout_dispatch against ep_layout + ep_dispatch on the same input (masked and invalid ids,
@@ -799,6 +800,64 @@ def test_layout_dispatch_one_launch_of_up_to_8192_entries(ep, hx, T, K, E, H, C,
             ep.ep_handle_destroy(h)
         for a, b in zip(*got):
             assert torch.equal(a, b)
+    finally:
+        torch.cuda.synchronize()
+        ep.ep_group_destroy(group)
+
+
+def _kernel_launches(ep, call) -> int:
+    """Nodes of the HIP graph that `call(stream)` is captured into (nothing of it runs)."""
+    st = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=st):
+        call(st.cuda_stream)
+    n = ctypes.c_size_t(0)
+    assert ep._hip_runtime().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return int(n.value)
+
+
+@pytest.mark.parametrize("T,K,E,H,C,order,one", [
+    (700, 8, 256, 520, 0, 1, True), (700, 8, 256, 520, 20, 2, True),   # several layout workgroups in a group with an order
+    (1023, 8, 64, 264, 0, 2, True), (1024, 8, 64, 264, 0, 1, False),   # the last without a run table, the first with one
+    (1024, 8, 64, 264, 0, 0, True), (1025, 8, 64, 264, 0, 0, False),   # 8192 entries, and more
+    (500, 10, 790, 72, 0, 0, True), (500, 10, 820, 72, 0, 0, False),   # bins that fit LDS, and not
+    (1024, 8, 64, 10008, 0, 0, True), (1024, 8, 64, 10016, 0, 0, False),  # 176 MiB
+    (480, 8, 64, 16392, 0, 0, True),                                    # more copying workgroups than run at once
+])
+def test_layout_dispatch_launches_strides_and_second_dispatch(ep, hx, T, K, E, H, C, order, one):
+    """Which inputs ep_layout_dispatch takes in one launch, and that it gives what the two calls give through
+    strided tokens and windows, also for a second dispatch of other tokens with the handle it returns."""
+    gen = torch.Generator(hx.DEV).manual_seed(H + E)
+    topk = torch.randint(0, E, (T, K), generator=gen, device=hx.DEV, dtype=torch.int32)
+    topk[::9, 0] = -1
+    w = torch.rand((T, K), generator=gen, device=hx.DEV)
+    xs = [torch.randn((T, H + 8), generator=gen, device=hx.DEV).bfloat16()[:, :H] for _ in range(2)]
+    rows = E * C if C else T * K
+    group = ep.ep_group_create(ep.make_config(1, E, H, K, T, mode=ep.EP_MODE_LL if C else ep.EP_MODE_HT, slots_per_subregion=C,
+                                              dispatch_order=order, max_handles=2))
+    try:
+        def windows():
+            store = hx.poison_bf16((rows, H + 16))
+            return store, (store.view(E, C, H + 16) if C else store)[..., :H]
+        stores = []
+        h1 = h2 = None
+        for i, x in enumerate(xs):
+            a, b = windows(), windows()
+            if i == 0:
+                h1 = ep.ep_layout_dispatch(group, topk, x, a[1], topk_weights=w)
+                h2 = ep.ep_layout(group, topk)
+            else:
+                ep.ep_dispatch(h1, x, a[1], topk_weights=w)
+            ep.ep_dispatch(h2, x, b[1], topk_weights=w)
+            torch.cuda.synchronize()
+            assert torch.equal(a[0].view(torch.int16), b[0].view(torch.int16)), "first dispatch" if i == 0 else "second dispatch"
+            stores.append(a[1])
+        ep.ep_handle_destroy(h1)
+        ep.ep_handle_destroy(h2)
+
+        def call(stream):
+            ep.ep_handle_destroy(ep.ep_layout_dispatch(group, topk, xs[0], stores[0], topk_weights=w, stream=stream))
+        assert (_kernel_launches(ep, call) == 1) == one
     finally:
         torch.cuda.synchronize()
         ep.ep_group_destroy(group)
@@ -1011,7 +1070,8 @@ def test_ll_windows_as_strided_view_of_receiver_tensor(ep, hx, oracle_mod):
         ep.ep_group_destroy(g)
 
 
-@pytest.mark.parametrize("variant", ["order 1 + read-ahead", "order 1", "order 2", "fp8", "fp8 ahead", "once per rank"])
+@pytest.mark.parametrize("variant", ["order 1 + read-ahead", "order 1", "order 2", "fp8", "fp8 ahead", "once per rank",
+                                     "once per rank, long rows"])
 @pytest.mark.parametrize("mode", ["ht", "ll"])
 def test_large_inputs_through_strided_tensors(ep, hx, oracle_mod, mode, variant):
     """The kernels of large inputs (8800 entries: destination-ordered copy, token read-ahead, quantising
@@ -1019,7 +1079,9 @@ def test_large_inputs_through_strided_tensors(ep, hx, oracle_mod, mode, variant)
     pitch larger than H, concatenated windows likewise, padded windows as this source's sub-regions of
     a receiver-shaped [E, R*C, H] tensor.  Everything outside the slices keeps its fill."""
     _say(f"strided large input mode={mode} variant={variant}")
-    w = wl.make_workload("skew", T=1100, H=1024)
+    # rows of 4 KiB: from there on the once-per-rank dispatch writes concatenated rows in destination order
+    w = wl.make_workload("skew", T=1100, H=2048 if variant.endswith("long rows") else 1024)
+    once = variant.startswith("once per rank")
     spec = w.spec
     T, H, E, R = spec.T, spec.H, spec.E, spec.R
     ll = mode == "ll"
@@ -1029,7 +1091,7 @@ def test_large_inputs_through_strided_tensors(ep, hx, oracle_mod, mode, variant)
     fp8 = variant.startswith("fp8")
     kw = {"order 1 + read-ahead": dict(dispatch_order=1), "order 1": dict(dispatch_order=1), "order 2": dict(dispatch_order=2),
           "fp8": {}, "fp8 ahead": dict(dispatch_order=1, quantize_ahead=1),
-          "once per rank": dict(dispatch_path=ep.EP_PATH_RANK_DEDUP)}[variant]
+          "once per rank": dict(dispatch_path=ep.EP_PATH_RANK_DEDUP)}[variant.split(",")[0]]
     announce = variant in ("order 1 + read-ahead", "fp8 ahead")
     g = _group(ep, spec, T, ep.EP_MODE_LL if ll else ep.EP_MODE_HT, C=C if ll else 0, my_rank=my_rank, **kw)
     try:
@@ -1055,7 +1117,7 @@ def test_large_inputs_through_strided_tensors(ep, hx, oracle_mod, mode, variant)
             scales = torch.full((rows, G), -2.0, dtype=torch.float32, device=hx.DEV)
             ep.ep_dispatch(h, x, recv_t, topk_weights=gate, recv_scales=scales)
         else:
-            ep.ep_dispatch(h, x, recv_t, topk_weights=gate, topk_idx=d_topk if variant == "once per rank" else None)
+            ep.ep_dispatch(h, x, recv_t, topk_weights=gate, topk_idx=d_topk if once else None)
         torch.cuda.synchronize()
         got = full.cpu().numpy()
         if fp8:

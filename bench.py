@@ -137,7 +137,7 @@ class StepBench:
     """One workload prepared for timing: `nsets` rotated input/window sets resident in HBM, the
     expert outputs that combine reads computed once, the call descriptors built once.  A step is
     then three or four foreign-function calls:
-        inputs of at most 1024 routed entries:  ep_layout_dispatch, ep_combine, ep_handle_destroy
+        inputs of at most 8192 routed entries:  ep_layout_dispatch, ep_combine, ep_handle_destroy
         larger ones:  ep_layout[_prefetch], ep_dispatch, ep_combine, ep_handle_destroy"""
 
     def __init__(self, ep, hx, wl, torch, np, workload: str, mode: str = "ht", slots: int = 0, order: int = 1,
@@ -150,7 +150,7 @@ class StepBench:
         self.C = (slots or max(1, 2 * T * K // E)) if self.ll else 0
         self.order = order
         self.nsets = nsets
-        self.fused = T * K <= 1024
+        self.fused = T * K <= 8192
         cfg = ep.make_config(spec.R, E, H, K, T, mode=ep.EP_MODE_LL if self.ll else ep.EP_MODE_HT,
                              slots_per_subregion=self.C, max_handles=nsets + 2,  # no allocation later
                              dispatch_order=order)

@@ -457,10 +457,16 @@ EP_API ep_result_t ep_handle_destroy(ep_handle_t handle);
  * operations, round to nearest even, magnitudes above 448 saturate; amax == 0 gives scale 1.
  * The quantising dispatch walks the tokens whatever the group's dispatch_order, except in a
  * group with quantize_ahead, after an ep_layout_prefetch that announced the same tokens.
- * EP_PATH_RANK_DEDUP runs three steps on the stream -- send to the group's staging
- * windows, receiver-side ranking of the header entries, fan-out -- and produces the
- * same outputs; dispatches of one group must then not overlap (they share the
- * staging windows).  An expert_base given to ep_layout must stay valid until then.
+ * EP_PATH_RANK_DEDUP sends to the group's staging windows and produces the same outputs.
+ * With send_only = 1 the receive phase (ep_complete) ranks the header entries of the messages
+ * that have arrived and fans the messages out.  An undivided call writes the same messages
+ * and takes the rows from the tokens, to the places the handle's layout has recorded: nothing
+ * reads its messages, they are there for whoever looks at the windows.  Either form writes the
+ * windows of the group (an undivided call buffer set 0), so dispatches of one group must not
+ * overlap on this path, and none, undivided or not, may use a buffer set between a
+ * send_only dispatch on it and its ep_complete.  An expert_base given to ep_layout must stay
+ * valid until the rows are written.
+ * No output may share memory with an input.
  */
 EP_API ep_result_t ep_dispatch(ep_handle_t handle, const ep_tensor_t *inputs, int32_t num_inputs,
                         const ep_tensor_t *outputs, int32_t num_outputs, int32_t send_only,
@@ -491,7 +497,8 @@ EP_API ep_result_t ep_combine(ep_handle_t handle, const ep_tensor_t *inputs, int
  * tokens it was made for, in one call.  In the paper's low-latency kernels the token count
  * runs next to the send (Sec. IV-C); here an input of at most 8192 routed entries on the
  * direct path with bf16 rows (176 MiB of tokens and rows at most, not one that goes in
- * destination order) is laid out and dispatched by ONE kernel launch: every
+ * destination order, num_experts + num_ranks up to about 800) is laid out and dispatched by ONE
+ * kernel launch: every
  * workgroup derives the layout from the few KB of ids in its own LDS and copies its share
  * of the rows, further workgroups write the handle's arrays.  Any other input runs the two
  * calls one after the other (the layout with the tokens announced, as ep_layout_prefetch
@@ -526,7 +533,7 @@ EP_API ep_result_t ep_combine_backward(ep_handle_t handle, const ep_tensor_t *in
 
 /*
  * ep_combine_backward_full -- ep_combine_backward whose grad_y may come uninitialised: the rows
- * that no entry reaches become zero in the same launch (the tail of the concatenated layout, the
+ * that no entry reaches become zero along with it (the tail of the concatenated layout, the
  * unused slots of padded windows).  EP_ERR_UNSUPPORTED for a handle made with expert_base, whose
  * rows lie among those of other sources.
  */

@@ -23,7 +23,7 @@
 //                  staged message: loaded once, stored to each local expert row.
 // Pure data movement: HBM bound, by randomly placed writes.  At 4096 tokens of 14 336 bytes,
 // 8 of 256 experts on 32 ranks: send 90 us, ranking 10 us, fan-out 164 us (the messages,
-// 416 MB, are read back); send and expansion in one launch 198 us (945 MB, 4.8 TB/s); send 81 us, then
+// 429 MB, are read back); send and expansion in one launch 198 us (958 MB, 4.8 TB/s); send 81 us, then
 // the rows by the destination-ordered walk of the direct dispatch 83 us.
 #include "ep_internal.h"
 

@@ -888,7 +888,9 @@ hipError_t launch_layout_dispatch(const LayoutArgs& a_in, const DispatchArgs& d,
     const int nlay = multi ? a.nchunks + 1 : 1;
     const int units = d.H / 8;
     const int nseg = (units + kWave - 1) / kWave;
-    // tokens per workgroup: so many that all copying workgroups run at once, no more than 64 entries
+    // tokens per workgroup: so many that all copying workgroups run at once if a row takes one of them, no more than
+    // 64 entries.  Rows of more than 16 segments take several, the later ones after the first have ended (480 tokens of
+    // 32 768 bytes, top-8: 29.5 us, in two launches 43.5).
     const int group = std::max(1, std::min((a.T + kFusedCopyBlocks - 1) / kFusedCopyBlocks, kWave / a.K));
     const int ngroups = (a.T + group - 1) / group;
     // workgroups per group: enough of them to put every compute unit to work, at most 16 segments of a token each

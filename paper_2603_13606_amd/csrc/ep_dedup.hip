@@ -54,7 +54,8 @@ __global__ __launch_bounds__(256) void dedup_send_kernel(DedupSendArgs a, DedupE
     // an ordinary load: a destination-ordered expansion reads the tokens again from the cache
     if (active) v = *((const u32x4*)(a.x + (int64_t)t * a.x_stride) + unit);
     const int my_slot = lane < a.K ? a.rank_row[(int64_t)t * a.K + lane] : -1;
-    const int my_row = EXPAND && lane < a.K ? x.dst_row[(int64_t)t * a.K + lane] : -1;
+    int my_row = EXPAND && lane < a.K ? x.dst_row[(int64_t)t * a.K + lane] : -1;
+    const float my_w = EXPAND && seg == 0 && x.recv_w && a.w && lane < a.K ? a.w[(int64_t)t * a.w_stride + lane] : 1.0f;
     const bool header = seg == 0 && lane < a.hdr_units;  // this lane holds 16 bytes of the header
     if (header) {
         const int32_t* route = a.topk + (int64_t)t * a.topk_stride;
@@ -81,19 +82,12 @@ __global__ __launch_bounds__(256) void dedup_send_kernel(DedupSendArgs a, DedupE
         if (active) __builtin_nontemporal_store(v, msg + a.hdr_units + unit);
     }
     if (!EXPAND) return;
+    my_row = deliver_sides(x.win, x.recv_w, x.recv_src, a.totals, seg == 0, my_row, my_w, t);
     for (int k = 0; k < a.K; ++k) {
         const int row = __builtin_amdgcn_readlane(my_row, k);
         if (row < 0) continue;
-        if (row >= x.win.rows_cap) {
-            if (seg == 0 && lane == 0) atomicOr(&a.totals[TOT_STATUS], STATUS_OUTPUT_OVERFLOW);
-            continue;
-        }
         uint16_t* dst = x.win.base + window_offset(x.win, row);
         if (active) __builtin_nontemporal_store(v, (u32x4*)dst + unit);
-        if (seg == 0 && lane == 0) {
-            if (x.recv_w) x.recv_w[row] = a.w ? a.w[(int64_t)t * a.w_stride + k] : 1.0f;
-            if (x.recv_src) x.recv_src[row] = t;
-        }
     }
 }
 
@@ -120,20 +114,15 @@ __global__ __launch_bounds__(256) void dedup_fanout_kernel(DedupFanoutArgs a, in
     const int32_t* hdr = (const int32_t*)msg;
     u32x4 v = {0u, 0u, 0u, 0u};
     if (active) v = __builtin_nontemporal_load((const u32x4*)(msg + a.hdr_bytes) + unit);
-    const int my_row = lane < a.K ? a.recv_dst_row[(int64_t)m * a.K + lane] : -1;
+    int my_row = lane < a.K ? a.recv_dst_row[(int64_t)m * a.K + lane] : -1;
+    const float my_w = seg == 0 && a.recv_w && lane < a.K ? __uint_as_float((uint32_t)hdr[1 + a.K + lane]) : 1.0f;
+    const int t = seg == 0 && a.recv_src ? hdr[0] : 0;
+    my_row = deliver_sides(a.win, a.recv_w, a.recv_src, a.totals, seg == 0, my_row, my_w, t);
     for (int k = 0; k < a.K; ++k) {
         const int row = __builtin_amdgcn_readlane(my_row, k);
         if (row < 0) continue;
-        if (row >= a.win.rows_cap) {
-            if (seg == 0 && lane == 0) atomicOr(&a.totals[TOT_STATUS], STATUS_OUTPUT_OVERFLOW);
-            continue;
-        }
         uint16_t* dst = a.win.base + window_offset(a.win, row);
         if (active) __builtin_nontemporal_store(v, (u32x4*)dst + unit);
-        if (seg == 0 && lane == 0) {
-            if (a.recv_w) a.recv_w[row] = __uint_as_float((uint32_t)hdr[1 + a.K + k]);
-            if (a.recv_src) a.recv_src[row] = hdr[0];
-        }
     }
 }
 

@@ -21,7 +21,13 @@ namespace {
 struct TokenSegment {
     u32x4 v;     // the 16 bytes of this lane
     int my_row;  // lane k: destination row of the token's k-th entry
+    float my_w;  // first segment: its gate weight, where one is delivered
 };
+
+// Lane k: the gate weight delivered with entry k of token t (1 without gate weights).
+__device__ __forceinline__ float entry_weight(const DispatchArgs& a, int t, int lane, bool first) {
+    return first && a.recv_w && a.w && lane < a.K ? a.w[(int64_t)t * a.w_stride + lane] : 1.0f;
+}
 
 __device__ __forceinline__ TokenSegment load_token_segment(const DispatchArgs& a, int t, int seg, int units, int lane) {
     TokenSegment s;
@@ -30,6 +36,7 @@ __device__ __forceinline__ TokenSegment load_token_segment(const DispatchArgs& a
     if (unit < units) s.v = __builtin_nontemporal_load((const u32x4*)(a.x + (int64_t)t * a.x_stride) + unit);
     // lane k fetches the k-th destination row of the token: one load for all K entries
     s.my_row = lane < a.K ? a.dst_row[(int64_t)t * a.K + lane] : -1;
+    s.my_w = entry_weight(a, t, lane, seg == 0);
     return s;
 }
 
@@ -37,19 +44,12 @@ __device__ __forceinline__ void store_token_segment(const DispatchArgs& a, const
                                                     int lane) {
     const int unit = seg * kWave + lane;
     const bool active = unit < units;
+    const int my_row = deliver_sides(a.win, a.recv_w, a.recv_src, a.totals, seg == 0, s.my_row, s.my_w, t);
     for (int k = 0; k < a.K; ++k) {
-        const int row = __builtin_amdgcn_readlane(s.my_row, k);
+        const int row = __builtin_amdgcn_readlane(my_row, k);
         if (row < 0) continue;
-        if (row >= a.win.rows_cap) {
-            if (seg == 0 && lane == 0) atomicOr(&a.totals[TOT_STATUS], STATUS_OUTPUT_OVERFLOW);
-            continue;
-        }
         uint16_t* dst = a.win.base + window_offset(a.win, row);
         if (active) __builtin_nontemporal_store(s.v, (u32x4*)dst + unit);
-        if (seg == 0 && lane == 0) {
-            if (a.recv_w) a.recv_w[row] = a.w ? a.w[(int64_t)t * a.w_stride + k] : 1.0f;
-            if (a.recv_src) a.recv_src[row] = t;
-        }
     }
 }
 
@@ -295,25 +295,19 @@ __global__ __launch_bounds__(256) void dispatch_fp8_kernel(DispatchArgs a, float
         in0 = __builtin_nontemporal_load(src);
         in1 = __builtin_nontemporal_load(src + 1);
     }
+    int my_row = lane < a.K ? a.dst_row[(int64_t)t * a.K + lane] : -1;
+    const float my_w = entry_weight(a, t, lane, seg == 0);
     float scale;
     const u32x4 q = quantize16(in0, in1, &scale);
     const int groups = a.H >> 7;
-    const int my_row = lane < a.K ? a.dst_row[(int64_t)t * a.K + lane] : -1;
+    my_row = deliver_sides(a.win, a.recv_w, a.recv_src, a.totals, seg == 0, my_row, my_w, t);
     uint8_t* base = (uint8_t*)a.win.base;  // window strides are in one-byte elements here
     for (int k = 0; k < a.K; ++k) {
         const int row = __builtin_amdgcn_readlane(my_row, k);
         if (row < 0) continue;
-        if (row >= a.win.rows_cap) {
-            if (seg == 0 && lane == 0) atomicOr(&a.totals[TOT_STATUS], STATUS_OUTPUT_OVERFLOW);
-            continue;
-        }
         if (active) {
             __builtin_nontemporal_store(q, (u32x4*)(base + window_offset(a.win, row) + ch0));
             if ((lane & 7) == 0) recv_scales[(int64_t)row * groups + (ch0 >> 7)] = scale;
-        }
-        if (seg == 0 && lane == 0) {
-            if (a.recv_w) a.recv_w[row] = a.w ? a.w[(int64_t)t * a.w_stride + k] : 1.0f;
-            if (a.recv_src) a.recv_src[row] = t;
         }
     }
 }

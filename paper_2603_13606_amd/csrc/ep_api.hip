@@ -18,11 +18,11 @@ constexpr int kSlabAlign = 64;  // ints; every device array starts on a 256-byte
 struct Slab {
     int32_t* base = nullptr;
     // carved arrays
-    int32_t *totals, *expert_count, *expert_kept, *expert_offset, *own_prefix;
+    int32_t *totals, *expert_count, *expert_kept, *expert_offset;
     int32_t *rank_pair_count, *rank_token_count, *rank_offset;
     uint32_t* pub;   // per-chunk bin sums of the layout kernel (kMaxChunks rows of W words)
     uint32_t* ctl;   // its generation / arrival words; pub and ctl are zeroed when the slab is made
-    int32_t *slot, *dst_row, *rank_row, *sorted_token, *sorted_k, *sorted_row, *entry_rank, *run_start;
+    int32_t *slot, *dst_row, *rank_row, *sorted_token, *sorted_k, *sorted_row, *entry_rank, *walk;
     uint8_t* quant;  // FP8 staging copy of the tokens (groups that quantise ahead), or nullptr
     // receiving side of the once-per-rank path (only carved for EP_PATH_RANK_DEDUP)
     int32_t *recv_count, *recv_kept, *recv_dst_row;
@@ -79,9 +79,7 @@ struct ep_handle_s {
     int T;
     hipStream_t last_stream;
     const int32_t* expert_base;  // as given to ep_layout (borrowed), or nullptr
-    bool has_runs = false;       // the layout filled slab.run_start
-    int nwc = 0;                 // wave-chunks of the layout plan
-    int chunk_entries = 0;       // entries per wave-chunk
+    bool has_walk = false;       // the layout filled slab.walk
     const void* warm_x = nullptr;  // tokens the layout launch has read into cache (ep_layout_prefetch)
     int64_t warm_stride = 0;
     int warm_rows = 0;
@@ -133,19 +131,19 @@ int64_t carve(int64_t* cursor, int64_t ints) {
     return at;
 }
 
-// Whether a layout of T tokens records the runs the destination-ordered walk needs: from kRunOrderMinEntries
+// Whether a layout of T tokens makes the walk list the destination-ordered dispatch needs: from kRunOrderMinEntries
 // entries on, when the group asks for that order, and for the once-per-rank path into concatenated windows where the send and the
 // ordered walk beat the one launch that does both (layout + dispatch, us in one / in two, even routing unless
 // said): rows of 14 336 bytes, top-8, 64.8/59.2 at 1100 tokens, 216/180 at 4096 (hot ranks 169/146), 409/345 at
 // 8192; of 8192 bytes, top-4, 129/116 at 8192 tokens; of 4096 bytes 69.0/65.7; but of 1024 bytes 26/40 -- the
 // walk's workgroups copy too little each -- and top-2 61.9/62.8 (hot 57/61), where most messages are rows.  The
-// table costs a layout 0.2 to 1.1 us, so inputs that the walk does not take have none; that a call will be split
+// list costs a layout 0.4 to 1 us, so inputs that the walk does not take have none; that a call will be split
 // into phases, which do not walk either, the layout cannot know.
 constexpr int kOnceOrderedMinHidden = 2048;
 constexpr int kOnceOrderedMinTopK = 4;
 constexpr int64_t kOnceOrderedMaxTokenBytes = 128ll << 20;  // half of the memory-side cache; measured up to 117 MB
 
-bool records_runs(const ep_group_config_t& c, int64_t T) {
+bool makes_walk(const ep_group_config_t& c, int64_t T) {
     if (T * c.top_k < kRunOrderMinEntries) return false;
     if (c.dispatch_path == EP_PATH_DIRECT) return c.dispatch_order != EP_ORDER_TOKEN;
     return c.mode == EP_MODE_HT && c.hidden >= kOnceOrderedMinHidden && c.top_k >= kOnceOrderedMinTopK &&
@@ -153,9 +151,9 @@ bool records_runs(const ep_group_config_t& c, int64_t T) {
 }
 
 // Whether any layout of the group does: from the smallest input that can on.
-bool may_record_runs(const ep_group_config_t& c) {
+bool may_make_walk(const ep_group_config_t& c) {
     const int64_t least = (kRunOrderMinEntries + c.top_k - 1) / c.top_k;
-    return least <= c.max_tokens_per_rank && records_runs(c, least);
+    return least <= c.max_tokens_per_rank && makes_walk(c, least);
 }
 
 // Lays the handle arrays out inside one allocation; with base == nullptr only the size is computed.
@@ -164,11 +162,12 @@ int64_t carve_slab(const ep_group_s* g, Slab* s, int32_t* base) {
     const int64_t nB = (int64_t)g->cfg.max_tokens_per_rank * g->cfg.top_k;
     int64_t cur = 0;
     const int64_t o_tot = carve(&cur, kTotalsWords), o_ec = carve(&cur, E), o_ek = carve(&cur, E);
-    const int64_t o_eo = carve(&cur, E + 1), o_op = carve(&cur, E + 1), o_rp = carve(&cur, R);
+    const int64_t o_eo = carve(&cur, E + 1), o_rp = carve(&cur, R);
     const int64_t o_rt = carve(&cur, R), o_ro = carve(&cur, R + 1);
     const int64_t o_h = carve(&cur, (int64_t)kMaxChunks * g->W), o_ctl = carve(&cur, kLayoutCtlWords);
-    const bool runs = may_record_runs(g->cfg);
-    const int64_t o_rn = runs ? carve(&cur, (int64_t)(kMaxWaveChunks + 1) * E) : 0;
+    const bool walk = may_make_walk(g->cfg);
+    // a list is two words per entry; a slab that holds one has always had kMaxWaveChunks + 1 words per expert for its walk
+    const int64_t o_wk = walk ? carve(&cur, std::max<int64_t>(2 * (nB + kWalkPad), (int64_t)(kMaxWaveChunks + 1) * E)) : 0;
     const int64_t o_sl = carve(&cur, nB), o_dr = carve(&cur, nB), o_rr = carve(&cur, nB);
     const int64_t o_st = carve(&cur, nB), o_sk = carve(&cur, nB), o_sr = carve(&cur, nB), o_er = carve(&cur, nB);
     const bool dedup = g->cfg.dispatch_path == EP_PATH_RANK_DEDUP;
@@ -180,11 +179,11 @@ int64_t carve_slab(const ep_group_s* g, Slab* s, int32_t* base) {
     if (base && s) {
         s->base = base;
         s->totals = base + o_tot; s->expert_count = base + o_ec; s->expert_kept = base + o_ek;
-        s->expert_offset = base + o_eo; s->own_prefix = base + o_op; s->rank_pair_count = base + o_rp;
+        s->expert_offset = base + o_eo; s->rank_pair_count = base + o_rp;
         s->rank_token_count = base + o_rt; s->rank_offset = base + o_ro;
         s->pub = (uint32_t*)(base + o_h); s->ctl = (uint32_t*)(base + o_ctl); s->slot = base + o_sl; s->dst_row = base + o_dr; s->rank_row = base + o_rr;
         s->sorted_token = base + o_st; s->sorted_k = base + o_sk; s->sorted_row = base + o_sr;
-        s->entry_rank = base + o_er; s->run_start = runs ? base + o_rn : nullptr;
+        s->entry_rank = base + o_er; s->walk = walk ? base + o_wk : nullptr;
         s->recv_count = dedup ? base + o_vc : nullptr; s->recv_kept = dedup ? base + o_vk : nullptr;
         s->recv_dst_row = dedup ? base + o_vr : nullptr;
         s->recv_rank_count = base + o_rc; s->recv_rank_offset = base + o_rf;
@@ -321,10 +320,9 @@ ep_result_t sync_and_read_totals(ep_handle_s* h, int32_t* tot) {
 // ---- scratch of ep_layout_static: one array per GPU, part of the library image, so the
 // entry point never allocates.  It holds what ep_layout keeps in the handle's slab beyond
 // the arrays a caller asks for: the per-chunk bin sums through which the layout workgroups
-// talk to each other, their generation words, and the per-expert positions in the
-// expert-sorted entry list.
+// talk to each other and their generation words.
 constexpr int64_t kStaticPubInts = (int64_t)kMaxChunks * (2 * kMaxExperts + 2);
-constexpr int64_t kStaticScratchInts = kStaticPubInts + kSlabAlign + kMaxExperts + 1 + kSlabAlign;
+constexpr int64_t kStaticScratchInts = kStaticPubInts + kSlabAlign;
 static __device__ __align__(256) int32_t scratch[kStaticScratchInts];
 
 constexpr int kMaxDevices = 64;
@@ -391,9 +389,9 @@ ep_result_t ep_dispatch_plan(const ep_group_config_t* cfg, int64_t num_tokens, i
         num_tokens * cfg->top_k > (1 << 28))
         return EP_ERR_INVALID_ARG;
     DispatchPlan d;
-    // whenever the group asks for the order and the input is large enough for it, its layout records the runs
-    const bool have_runs = cfg->dispatch_order != EP_ORDER_TOKEN && cfg->dispatch_path == EP_PATH_DIRECT;
-    plan_dispatch((int)num_tokens, cfg->top_k, cfg->hidden, cfg->num_experts, cfg->dispatch_order, have_runs,
+    // whenever the group asks for the order and the input is large enough for it, its layout makes the walk list
+    const bool have_walk = cfg->dispatch_order != EP_ORDER_TOKEN && cfg->dispatch_path == EP_PATH_DIRECT;
+    plan_dispatch((int)num_tokens, cfg->top_k, cfg->hidden, cfg->num_experts, cfg->num_ranks, cfg->dispatch_order, have_walk,
                   (int)std::min<int64_t>(prefetched_rows, num_tokens), &d);
     plan->run_order = d.run_order; plan->group = d.group; plan->blocks = d.blocks;
     plan->block_entries = d.block_entries; plan->splits = d.splits; plan->slice_units = d.piece;
@@ -636,18 +634,24 @@ static ep_result_t prepare_layout(ep_handle_t* handle, ep_group_t g, const ep_te
     a.W = g->W; a.bits_e = g->bits_e; a.bits_r = g->bits_r;
     const Slab& s = h->slab;
     a.pub = s.pub; a.ctl = s.ctl; a.expert_count = s.expert_count; a.expert_kept = s.expert_kept;
-    a.expert_offset = s.expert_offset; a.own_prefix = s.own_prefix; a.rank_pair_count = s.rank_pair_count;
+    a.expert_offset = s.expert_offset; a.rank_pair_count = s.rank_pair_count;
     a.rank_token_count = s.rank_token_count; a.rank_offset = s.rank_offset; a.totals = s.totals;
     a.slot = s.slot; a.dst_row = s.dst_row; a.rank_row = s.rank_row; a.sorted_token = s.sorted_token;
     a.sorted_k = s.sorted_k; a.sorted_row = s.sorted_row;
     a.entry_rank = s.entry_rank;
-    a.run_start = records_runs(c, T) ? s.run_start : nullptr;
+    a.walk = nullptr; a.walk_group = 1; a.walk_waves = 0;
+    if (makes_walk(c, T)) {
+        DispatchPlan plan;
+        const bool there = c.quantize_ahead ? plan_dispatch_fp8_staged(a.T, a.K, c.hidden, a.E, a.R, true, &plan)
+                                            : plan_dispatch(a.T, a.K, c.hidden, a.E, a.R, EP_ORDER_DESTINATION_RESIDENT, true, 0, &plan);
+        if (there) { a.walk = (int2*)s.walk; a.walk_group = plan.group; a.walk_waves = plan.waves; }
+    }
     a.warm_x = nullptr; a.warm_stride = 0; a.warm_rows = 0; a.warm_units = c.hidden / 8; a.nchunks = 1;
     a.rows_cap = -1; a.recv_count = nullptr;
     a.drop_hint = g->drop_hint_dev;  // there for padded windows in destination order
     a.quant_out = nullptr; a.quant_pitch = 0;
     h->quant_x = nullptr;
-    if (tokens && a.run_start && c.dispatch_order == EP_ORDER_DESTINATION && c.dispatch_path == EP_PATH_DIRECT) {
+    if (tokens && a.walk && c.dispatch_order == EP_ORDER_DESTINATION && c.dispatch_path == EP_PATH_DIRECT) {
         a.warm_x = (const uint16_t*)tokens->data;
         a.warm_stride = tokens->stride[0];
         const int cached_rows = (int)std::min<int64_t>(T, kWarmBytes / (2 * (int64_t)c.hidden));
@@ -662,9 +666,7 @@ static ep_result_t prepare_layout(ep_handle_t* handle, ep_group_t g, const ep_te
             a.warm_x = nullptr;
         }
     }
-    h->has_runs = layout_writes_runs(a);
-    h->nwc = a.nwc;
-    h->chunk_entries = a.passes * kWave;
+    h->has_walk = a.walk != nullptr;
     *args = a;
     *handle = h;
     return EP_SUCCESS;
@@ -791,8 +793,7 @@ static ep_result_t parse_dispatch(ep_group_s* g, int T, const Slab& slab, const 
     a.totals = slab.totals;
     a.T = T; a.K = c.top_k; a.H = c.hidden; a.E = c.num_experts;
     a.sorted_token = slab.sorted_token; a.sorted_k = slab.sorted_k; a.sorted_row = slab.sorted_row;
-    a.own_prefix = slab.own_prefix;
-    a.run_start = nullptr; a.nwc = 0; a.chunk_entries = 0; a.order = c.dispatch_order; a.prefetched_rows = 0;
+    a.walk = nullptr; a.R = c.num_ranks; a.order = c.dispatch_order; a.prefetched_rows = 0;
     call->fp8 = fp8;
     call->scales = rq ? (float*)rq->data : nullptr;
     call->x = x;
@@ -814,13 +815,12 @@ ep_result_t ep_dispatch(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_in
     DispatchArgs& a = call.a;
     const bool fp8 = call.fp8;
     const ep_tensor_t* x = call.x;
-    a.run_start = h->has_runs ? h->slab.run_start : nullptr;
-    if (a.run_start && a.win.padded && g->drop_hint) {  // capacity cut most entries last time: walk the tokens
+    a.walk = h->has_walk ? (const int2*)h->slab.walk : nullptr;
+    if (a.walk && a.win.padded && g->drop_hint) {  // capacity cut most entries last time: walk the tokens
         const int64_t v = __atomic_load_n(g->drop_hint, __ATOMIC_RELAXED);
         const int64_t kept = v & 0xffffffffLL, dropped = v >> 32;
-        if (2 * dropped > kept) a.run_start = nullptr;
+        if (2 * dropped > kept) a.walk = nullptr;
     }
-    a.nwc = h->nwc; a.chunk_entries = h->chunk_entries;
     // the read-ahead of the layout call is good for the dispatch that follows it, once
     a.prefetched_rows = (h->warm_x == x->data && h->warm_stride == x->stride[0]) ? h->warm_rows : 0;
     h->warm_x = nullptr;
@@ -870,12 +870,12 @@ ep_result_t ep_dispatch(ep_handle_t h, const ep_tensor_t* inputs, int32_t num_in
     sa.hdr_units = (int)(g->hdr_bytes / 16);
     sa.totals = s.totals;
     sa.T = h->T; sa.K = c.top_k; sa.H = c.hidden;
-    if (!send_only && a.run_start) {
+    if (!send_only && a.walk) {
         // large enough for the destination-ordered walk, and the tokens the send has just read stay in the
         // memory-side cache: the rows are written in that order by a launch of their own
         a.order = EP_ORDER_DESTINATION_RESIDENT;
         DispatchPlan plan;
-        if (plan_dispatch(a.T, a.K, a.H, a.E, a.order, true, 0, &plan)) {
+        if (plan_dispatch(a.T, a.K, a.H, a.E, a.R, a.order, true, 0, &plan)) {
             if (launch_dedup_send(sa, (hipStream_t)stream) != hipSuccess) return EP_ERR_HIP;
             return launch_dispatch(a, (hipStream_t)stream) == hipSuccess ? EP_SUCCESS : EP_ERR_HIP;
         }
@@ -1075,13 +1075,12 @@ ep_result_t ep_layout_static(const ep_group_config_t* cfg, const ep_tensor_t* to
     // which its workgroups talk to each other ready for the next one
     a.pub = (uint32_t*)sc;
     a.ctl = (uint32_t*)(sc + kStaticPubInts);
-    a.own_prefix = sc + kStaticPubInts + kSlabAlign;
     a.expert_count = out->expert_count; a.expert_kept = out->expert_kept; a.expert_offset = out->expert_offset;
     a.rank_pair_count = out->rank_pair_count; a.rank_token_count = out->rank_token_count;
     a.rank_offset = out->rank_offset; a.totals = out->totals;
     a.slot = out->slot; a.dst_row = out->dst_row; a.rank_row = out->rank_row; a.entry_rank = out->entry_rank;
     a.sorted_token = out->sorted_token; a.sorted_k = out->sorted_k; a.sorted_row = out->sorted_row;
-    a.run_start = nullptr; a.drop_hint = nullptr; a.quant_out = nullptr; a.quant_pitch = 0;
+    a.walk = nullptr; a.walk_group = 1; a.walk_waves = 0; a.drop_hint = nullptr; a.quant_out = nullptr; a.quant_pitch = 0;
     a.warm_x = nullptr; a.warm_stride = 0; a.warm_rows = 0; a.warm_units = c.hidden / 8; a.nchunks = 1;
     a.rows_cap = -1; a.recv_count = nullptr;
     return launch_layout(a, (hipStream_t)stream) == hipSuccess ? EP_SUCCESS : EP_ERR_HIP;

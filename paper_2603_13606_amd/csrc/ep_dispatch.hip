@@ -70,33 +70,34 @@ __global__ __launch_bounds__(256) void dispatch_direct_kernel(DispatchArgs a, in
     copy_token_segment(a, t, (int)(u - (int64_t)t * nseg), units, lane);
 }
 
-// ---- run-ordered variant for large inputs
+// ---- destination-ordered variant for large inputs
 //
 // Writes that land next to each other within a short time are served much faster by the
 // memory system than rows scattered at random (measured on this part: 6.3 TB/s against
-// 4.9 TB/s), so large inputs are walked in the order of the destination rows instead of
-// the order of the tokens.  The layout's expert-sorted entry list is cut into runs: the
-// entries of one expert that come from one block of consecutive wave-chunks of the input
-// (the layout records where those start).  A run is copied by `splits` workgroups, a few
-// rows each per step; consecutive workgroups take the runs of one block expert by expert,
-// so the copy sweeps over all expert regions once per block and every region grows by about
-// a dozen adjacent rows each time.
+// 4.9 TB/s; 4096 tokens of 14 336 bytes, top-8, take 82 us this way and 108 in token order), so large inputs are walked in the order of the destination rows instead of
+// the order of the tokens.  The layout has made a walk list for it: {token, row} of every entry
+// that has a row, block of the input by block, expert by expert within a block.  The copy
+// sweeps over all expert regions once per block and every region grows by about a dozen
+// adjacent rows each time.
 //
 // A row is read once from HBM and up to K-1 more times from the L2 cache: the 16-byte
 // units of a row are split into kSlices equal pieces and workgroup index mod kSlices picks
 // the piece, which on this part is also the accelerator die the workgroup runs on, so each
 // die's L2 only ever holds its own piece of the tokens of the current block.
 constexpr int kSlices = 8;
-constexpr int kRunUnroll = 2;
+// Rows per thread: how much is on its way at a time.  The writes of all resident workgroups should stay close together
+// in memory, and the chain from a workgroup's start to its stores be covered: one row of a piece that takes two
+// waves or more (4096 rows of 1792-byte pieces: dispatch of 4096 x 14 336 bytes, top-8, 82 us; with two rows 94, with four
+// 94), two of shorter ones (8192 x 1024 bytes, top-8: 26.2 us, with one 28.2; 8192-byte rows 47.4/48.0).
+constexpr int walk_unroll(int tpr_shift) { return tpr_shift >= 7 ? 1 : 2; }
 
-struct RunPlan {
-    int group;      // wave-chunks per block
-    int nblocks;    // blocks of the input
+struct WalkPlan {
     int piece;      // 16-byte units per slice
     int units;      // 16-byte units per row
     int tpr_shift;  // log2(threads that share one row piece)
-    int first_block;  // this launch covers blocks first_block .. first_block + gridDim.y - 1
-    int splits;       // workgroups that share one run
+    int first, last;  // places of the walk list this launch covers
+    int side_blocks;  // leading workgroups that fill the side arrays, a multiple of 8 (the dies stay aligned with the slices)
+    int entries;      // routed entries of the input, at most
 };
 
 // What the walk copies when the rows were quantised ahead of the dispatch (FP8 codes and scales
@@ -115,129 +116,114 @@ struct StagedRows {
     int groups;          // H / 128
 };
 
+// Fills the side arrays in the order of the expert-sorted list, that is of the rows: 64 neighbouring
+// words per store, by workgroups of their own.  Done by the copying workgroups of one slice, one word per row,
+// all of it fell to one die, and its workgroups were the last to end (101 us for 82).
+__device__ void walk_sides(const DispatchArgs& a, int i, int entries) {
+    if (i >= min(entries, a.totals[TOT_SORTED])) return;
+    const int row = a.sorted_row[i];
+    if (row < 0 || row >= a.win.rows_cap) return;
+    const int t = a.sorted_token[i];
+    if (a.recv_src) a.recv_src[row] = t;
+    if (a.recv_w) a.recv_w[row] = a.w ? a.w[(int64_t)t * a.w_stride + a.sorted_k[i]] : 1.0f;
+}
+
 // TPR_SHIFT = log2(threads that share one row piece); PADDED = window addressing mode; FP8 =
 // rows come from a staging copy of quantised rows instead of the bf16 tokens.
+//
+// A workgroup takes the next 256 / 2^TPR_SHIFT * walk_unroll places of the list: every workgroup but the last has all
+// its rows, and the chain from its start to its stores is one list load and one token load.  (Cut by runs -- the
+// entries of one expert in one block, at positions read from a table first -- a third of the workgroups had
+// fewer rows than they could take, some looped, and the chain was one load longer: 87 us where this takes 82, and 96/80 with
+// Zipf routing, 55/45 with rows of 8192 bytes, 32/22 of 5760, 41/17 of 1024; all in us.)
 //
 // The vector-memory counter of this part counts loads and stores alike, in order, and the
 // compiler waits for it to reach zero wherever control flow stands between an access and the
 // use of its result -- which, between two row stores, means waiting for the first store to
 // reach memory before the second is issued.  So the rows of a step are copied by straight-line
 // code (loads, then stores, nothing conditional in between) whenever every lane of the wave has
-// all its rows, with the general code kept for the ragged end of a run, and the side arrays
-// are read before the rows and written after them.
+// all its rows, with the general code kept for the end of the list.
 template <int TPR_SHIFT, bool PADDED, bool FP8>
-__global__ __launch_bounds__(256) void dispatch_runs_kernel(DispatchArgs a, RunPlan p, StagedRows f) {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && p.first_block == 0 && a.recv_count) {
+__global__ __launch_bounds__(256) void dispatch_walk_kernel(DispatchArgs a, WalkPlan p, StagedRows f) {
+    if (blockIdx.x == 0 && p.first == 0 && a.recv_count) {
         for (int e = threadIdx.x; e < a.E; e += blockDim.x) a.recv_count[e] = a.expert_kept[e];
     }
-    constexpr int tpr = 1 << TPR_SHIFT, nsub = 256 >> TPR_SHIFT;
+    if ((int)blockIdx.x < p.side_blocks) {
+        walk_sides(a, blockIdx.x * 256 + threadIdx.x, p.entries);
+        return;
+    }
+    constexpr int tpr = 1 << TPR_SHIFT, nsub = 256 >> TPR_SHIFT, U = walk_unroll(TPR_SHIFT);
     constexpr int slices = FP8 ? kFp8Slices : kSlices;
     constexpr int elem_bytes = FP8 ? 1 : 2;  // size of the elements the window strides count
-    // grid = (slices * splits * E, blocks): x runs fastest, so workgroups are handed out
-    // slice by slice, then share by share of a run, expert by expert, block by block
-    const int xs = blockIdx.x & (slices - 1);
-    const int es = blockIdx.x / slices;
-    const int e = es / p.splits, sp = es - e * p.splits;
-    const int blk = p.first_block + blockIdx.y;
-    const int c0 = blk * p.group, c1 = min(c0 + p.group, a.nwc);
-    // wave-uniform: the run of expert e in block blk, as positions of the sorted entry list
-    const int lo = __builtin_amdgcn_readfirstlane(max(a.run_start[(int64_t)c0 * a.E + e], 0));
-    int hi = __builtin_amdgcn_readfirstlane(min(a.run_start[(int64_t)c1 * a.E + e], a.T * a.K));
-    // padded windows keep the first C entries of an expert: the rest of its sorted range has no row
-    if (PADDED) hi = min(hi, __builtin_amdgcn_readfirstlane(a.own_prefix[e]) + a.win.C);
-    if (lo >= hi) return;
-    const int sub = threadIdx.x >> TPR_SHIFT, u = threadIdx.x & (tpr - 1);
+    // workgroups are handed out slice by slice, then along the list
+    const int b = blockIdx.x - p.side_blocks;
+    const int xs = b & (slices - 1);
+    int sub = threadIdx.x >> TPR_SHIFT;
+    if (TPR_SHIFT >= 6) sub = __builtin_amdgcn_readfirstlane(sub);  // a row piece takes whole waves: token and row, and with
+                                                                    // them the row addresses, live in scalar registers
+    const int u = threadIdx.x & (tpr - 1);
+    const int pos0 = p.first + ((b / slices) * nsub + sub) * U;
+    const int end = min(p.last, a.totals[TOT_KEPT]);
+    int2 en[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) en[q] = a.walk[pos0 + q];  // the list is followed by kWalkPad unused places
     const int u0 = xs * p.piece, u1 = min(p.units, u0 + p.piece);
     const int cend = FP8 ? min(u1, f.code_units) : u1;  // units of the row proper end here
-    const bool side = xs == 0 && u == 0;  // one lane per row fills the side arrays
     const uint8_t* src_base = FP8 ? f.staged : (const uint8_t*)a.x;
     const int64_t src_pitch = FP8 ? f.pitch : a.x_stride * 2;
-    uint8_t* dst_base = (uint8_t*)a.win.base;
-    for (int pos0 = lo + sp * (nsub * kRunUnroll) + sub; pos0 < hi; pos0 += p.splits * nsub * kRunUnroll) {
-        int t[kRunUnroll], row[kRunUnroll];
+    int row[U];
+    const uint8_t* src[U];
+    uint8_t* dst[U];
+    bool have_all = true;
 #pragma unroll
-        for (int q = 0; q < kRunUnroll; ++q) {
-            const int pos = pos0 + q * nsub;
-            t[q] = 0;
+    for (int q = 0; q < U; ++q) {
+        row[q] = pos0 + q < end ? en[q].y : -1;
+        if (row[q] >= a.win.rows_cap) {
+            if (xs == 0 && u == 0) atomicOr(&a.totals[TOT_STATUS], STATUS_OUTPUT_OVERFLOW);
             row[q] = -1;
-            if (pos < hi) {
-                t[q] = a.sorted_token[pos];
-                row[q] = a.sorted_row[pos];
-                if (row[q] >= a.win.rows_cap) {
-                    if (side) atomicOr(&a.totals[TOT_STATUS], STATUS_OUTPUT_OVERFLOW);
-                    row[q] = -1;
-                }
-            }
-            if (TPR_SHIFT >= 6) {  // a row piece takes whole waves: token and row, and with them the row
-                                   // addresses, are the same for every lane and live in scalar registers
-                t[q] = __builtin_amdgcn_readfirstlane(t[q]);
-                row[q] = __builtin_amdgcn_readfirstlane(row[q]);
-            }
         }
-        float wq[kRunUnroll];
-        if (side && a.recv_w) {
+        const int t = row[q] >= 0 ? en[q].x : 0, r = max(row[q], 0);
+        const int64_t off = PADDED ? window_offset(a.win, r) : (int64_t)r * a.win.stride0;
+        src[q] = src_base + (int64_t)t * src_pitch;
+        dst[q] = (uint8_t*)a.win.base + off * elem_bytes;
+        have_all = have_all && row[q] >= 0;
+    }
+    if (FP8 && u1 > f.code_units) {  // the slice that holds the scales (workgroup-uniform), a few lanes of it
+        for (int col = max(u0, f.code_units) + u; col < u1; col += tpr) {
+            const int j = (col - f.code_units) * 4;  // up to four scales; the last unit may be part padding
 #pragma unroll
-            for (int q = 0; q < kRunUnroll; ++q) {
-                wq[q] = 1.0f;
-                if (row[q] >= 0 && a.w) wq[q] = a.w[(int64_t)t[q] * a.w_stride + a.sorted_k[pos0 + q * nsub]];
-            }
-        }
-        const uint8_t* src[kRunUnroll];
-        uint8_t* dst[kRunUnroll];
-        bool have_all = true;
-#pragma unroll
-        for (int q = 0; q < kRunUnroll; ++q) {
-            const int r = max(row[q], 0);
-            const int64_t off = PADDED ? window_offset(a.win, r) : (int64_t)r * a.win.stride0;
-            src[q] = src_base + (int64_t)t[q] * src_pitch;
-            dst[q] = dst_base + off * elem_bytes;
-            have_all = have_all && row[q] >= 0;
-        }
-        if (FP8 && u1 > f.code_units) {  // the slice that holds the scales (workgroup-uniform), a few lanes of it
-            for (int col = max(u0, f.code_units) + u; col < u1; col += tpr) {
-                const int j = (col - f.code_units) * 4;  // up to four scales; the last unit may be part padding
-#pragma unroll
-                for (int q = 0; q < kRunUnroll; ++q) {
-                    if (row[q] < 0) continue;
-                    const u32x4 v = *((const u32x4*)src[q] + col);
-                    float* sdst = f.recv_scales + (int64_t)row[q] * f.groups + j;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (j + c < f.groups) sdst[c] = __uint_as_float(v[c]);
-                }
-            }
-        }
-        if (__builtin_amdgcn_ballot_w64(!have_all) == 0) {
-            for (int col = u0 + u; col < cend; col += tpr) {
-                u32x4 v[kRunUnroll];
-#pragma unroll
-                for (int q = 0; q < kRunUnroll; ++q) v[q] = *((const u32x4*)src[q] + col);
-#pragma unroll
-                for (int q = 0; q < kRunUnroll; ++q) __builtin_nontemporal_store(v[q], (u32x4*)dst[q] + col);
-            }
-        } else {
-            for (int col = u0 + u; col < cend; col += tpr) {
-                u32x4 v[kRunUnroll];
-#pragma unroll
-                for (int q = 0; q < kRunUnroll; ++q)
-                    if (row[q] >= 0) v[q] = *((const u32x4*)src[q] + col);
-#pragma unroll
-                for (int q = 0; q < kRunUnroll; ++q)
-                    if (row[q] >= 0) __builtin_nontemporal_store(v[q], (u32x4*)dst[q] + col);
-            }
-        }
-        if (side) {
-#pragma unroll
-            for (int q = 0; q < kRunUnroll; ++q) {
+            for (int q = 0; q < U; ++q) {
                 if (row[q] < 0) continue;
-                if (a.recv_src) a.recv_src[row[q]] = t[q];
-                if (a.recv_w) a.recv_w[row[q]] = wq[q];
+                const u32x4 v = *((const u32x4*)src[q] + col);
+                float* sdst = f.recv_scales + (int64_t)row[q] * f.groups + j;
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (j + c < f.groups) sdst[c] = __uint_as_float(v[c]);
             }
+        }
+    }
+    if (__builtin_amdgcn_ballot_w64(!have_all) == 0) {
+        for (int col = u0 + u; col < cend; col += tpr) {
+            u32x4 v[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) v[q] = *((const u32x4*)src[q] + col);
+#pragma unroll
+            for (int q = 0; q < U; ++q) __builtin_nontemporal_store(v[q], (u32x4*)dst[q] + col);
+        }
+    } else {
+        for (int col = u0 + u; col < cend; col += tpr) {
+            u32x4 v[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (row[q] >= 0) v[q] = *((const u32x4*)src[q] + col);
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (row[q] >= 0) __builtin_nontemporal_store(v[q], (u32x4*)dst[q] + col);
         }
     }
 }
 
-// Reads token rows [t0, t1) (and, when asked, the index arrays of the layout) once, front
+// Reads token rows [t0, t1) (and, when asked, the walk list) once, front
 // to back, with ordinary cached loads, so that the run-ordered copy that follows finds
 // them in the memory-side cache and the DRAM sees a read phase and then a write phase.
 __global__ __launch_bounds__(256) void dispatch_warm_kernel(DispatchArgs a, int units, int t0, int t1, int with_index) {
@@ -252,19 +238,10 @@ __global__ __launch_bounds__(256) void dispatch_warm_kernel(DispatchArgs a, int 
         acc ^= v[0] ^ v[1] ^ v[2] ^ v[3];
     }
     if (with_index) {
-        const int n = a.T * a.K, table = (a.nwc + 1) * a.E;
-        for (int64_t i = gid; i < n; i += stride) acc ^= (uint32_t)(a.sorted_token[i] ^ a.sorted_row[i]);
-        for (int64_t i = gid; i < table; i += stride) acc ^= (uint32_t)a.run_start[i];
+        const int n = a.T * a.K;
+        for (int64_t i = gid; i < n; i += stride) acc ^= (uint32_t)(a.walk[i].x ^ a.walk[i].y);
     }
     asm volatile("" ::"v"(acc));  // the loads are the point: keep them
-}
-
-template <int TPR_SHIFT>
-void launch_runs(const DispatchArgs& a, const RunPlan& p, int nblocks, hipStream_t s) {
-    const dim3 grid((unsigned)(kSlices * a.E * p.splits), (unsigned)nblocks);
-    const StagedRows none = {nullptr, 0, nullptr, 0, 0};
-    if (a.win.padded) hipLaunchKernelGGL((dispatch_runs_kernel<TPR_SHIFT, true, false>), grid, dim3(256), 0, s, a, p, none);
-    else hipLaunchKernelGGL((dispatch_runs_kernel<TPR_SHIFT, false, false>), grid, dim3(256), 0, s, a, p, none);
 }
 
 // ---- quantising dispatch: FP8 (OCP E4M3) rows with one float scale per 128 channels
@@ -377,38 +354,35 @@ hipError_t launch_calibration_copy(void* dst, const void* src, size_t bytes, hip
     return hipGetLastError();
 }
 
-// Inputs from kRunOrderMinEntries entries on can be copied in run order (when the layout
-// recorded the runs); smaller ones are bound by latency and keep the shorter token-ordered
+// Inputs from kRunOrderMinEntries entries on can be copied in destination order (when the layout
+// made the list); smaller ones are bound by latency and keep the shorter token-ordered
 // kernel.  A read pass covers kWarmBytes of tokens: a piece must stay in the 256 MiB
 // memory-side cache, next to whatever else lives there, while the copy of that piece runs.
 //
-// A block holds about 12 rows per expert, and no more tokens than keep one slice of them
-// (2H/8 bytes each) within 2 MiB, half of an XCD's L2.  Longer runs are rewarded by the
-// memory system when the routing is even (32 rows per expert: 86 instead of 88 us at the
-// prefill shape) but lose more when a few experts are hot, because the workgroups of a long
-// hot run then loop while the others idle; 8 to 16 rows are within 1 % of the best on every
-// shape measured.  A workgroup copies nsub * kRunUnroll rows at a time, so a run of average
-// length is shared by `splits` workgroups, one step each.
+// A block holds as many tokens as keep one slice of them (2H/8 bytes each) within 2 MiB, half of an XCD's L2: the
+// longer its runs, the closer together the writes (dispatch of 4096 tokens, top-8, of 14 336 bytes, 256 experts: 85.0 us
+// with 16 rows per expert and block, 83.0 with 32, 82.3 with 36, which is 2 MiB, and 87 with 64; of 8192 bytes, 128 experts, 47.7
+// with 16, 46.6 with 64, 45.3 with 128, 2 MiB).  Blocks end where workgroups of the layout end, or at an even part of one.
 // `units` 16-byte units per copied row, cut into `slices` slices; H = channels of a token row
 // (what a read pass reads).
-static bool plan_rows(int T, int K, int H, int units, int slices, int E, int order, bool have_runs, int prefetched_rows,
+static bool plan_rows(int T, int K, int H, int units, int slices, int E, int R, int order, bool have_walk, int prefetched_rows,
                       DispatchPlan* out) {
     DispatchPlan d = {};
     const int64_t n = (int64_t)T * K;
-    d.run_order = order != EP_ORDER_TOKEN && have_runs && n >= kRunOrderMinEntries && units >= slices;
+    d.run_order = order != EP_ORDER_TOKEN && have_walk && n >= kRunOrderMinEntries && units >= slices;
     if (!d.run_order) { *out = d; return false; }
     int passes = 0, nwc = 0;
     plan_layout((int)n, &passes, &nwc);
     const int chunk_entries = passes * kWave;
     const int64_t l2_tokens = (2ll << 20) / std::max(16 * units / slices, 1);
-    const int want = (int)std::max<int64_t>(768, std::min<int64_t>(12ll * E, l2_tokens * K));
-    d.group = std::max(1, want / chunk_entries);
+    const int64_t most = std::max<int64_t>(768, l2_tokens * K);
+    d.group = plan_walk(E, R, (int)std::min<int64_t>(std::max<int64_t>(1, most / chunk_entries), kMaxWaveChunks), &d.waves);
     d.blocks = (nwc + d.group - 1) / d.group;
     d.piece = (units + slices - 1) / slices;
     if (d.piece >= 8) d.piece = (d.piece + 7) / 8 * 8;  // whole 128-byte lines per slice (the last slices get less)
     d.tpr_shift = 4;
     while ((1 << d.tpr_shift) < d.piece && d.tpr_shift < 8) ++d.tpr_shift;
-    const int rows_per_step = (256 >> d.tpr_shift) * kRunUnroll;
+    const int rows_per_step = (256 >> d.tpr_shift) * walk_unroll(d.tpr_shift);
     const int avg_run = (int)(((int64_t)d.group * chunk_entries + E - 1) / E);
     d.splits = std::max(1, (avg_run + rows_per_step - 1) / rows_per_step);
     d.block_entries = d.group * chunk_entries;
@@ -428,43 +402,57 @@ static bool plan_rows(int T, int K, int H, int units, int slices, int E, int ord
     return true;
 }
 
-bool plan_dispatch(int T, int K, int H, int E, int order, bool have_runs, int prefetched_rows, DispatchPlan* out) {
-    return plan_rows(T, K, H, H / 8, kSlices, E, order, have_runs, prefetched_rows, out);
+// Units of a staged FP8 row: H/16 of codes, then the scales rounded up to whole units.
+static int fp8_code_units(int H) { return H / 16; }
+static int fp8_row_units(int H) { return H / 16 + (H / 32 + 15) / 16; }
+
+bool plan_dispatch(int T, int K, int H, int E, int R, int order, bool have_walk, int prefetched_rows, DispatchPlan* out) {
+    return plan_rows(T, K, H, H / 8, kSlices, E, R, order, have_walk, prefetched_rows, out);
 }
 
-// The copy launches of the run order (with their read passes): `launch(plan, blocks)` starts
-// the copy of `blocks` blocks from plan.first_block on.
-template <typename Launch>
-static void launch_run_order(const DispatchArgs& a, const DispatchPlan& d, RunPlan p, hipStream_t s, Launch launch) {
-    const int units = a.H / 8;
-    for (int b0 = 0; b0 < d.blocks; b0 += d.blocks_per_launch) {
-        const int nb = std::min(d.blocks_per_launch, d.blocks - b0);
-        const int t0 = (int)std::min<int64_t>(a.T, (int64_t)b0 * d.block_entries / a.K);
-        const int t1 = (int)std::min<int64_t>(a.T, ((int64_t)(b0 + nb) * d.block_entries + a.K - 1) / a.K);
-        // a read pass, unless the layout launch has read these rows already
-        if (a.order == EP_ORDER_DESTINATION && t1 > a.prefetched_rows)
-            hipLaunchKernelGGL(dispatch_warm_kernel, dim3(2048), dim3(256), 0, s, a, units, t0, t1, b0 == 0 ? 1 : 0);
-        p.first_block = b0;
-        launch(p, nb);
+bool plan_dispatch_fp8_staged(int T, int K, int H, int E, int R, bool have_walk, DispatchPlan* out) {
+    return plan_rows(T, K, H, fp8_row_units(H), kFp8Slices, E, R, EP_ORDER_DESTINATION_RESIDENT, have_walk, 0, out);
+}
+
+template <int TPR_SHIFT, bool FP8>
+static void launch_walk_kernel(const DispatchArgs& a, const WalkPlan& p, const StagedRows& f, hipStream_t s) {
+    const int rows = (256 >> TPR_SHIFT) * walk_unroll(TPR_SHIFT);
+    const dim3 grid((unsigned)p.side_blocks + (unsigned)(FP8 ? kFp8Slices : kSlices) * (unsigned)((p.last - p.first + rows - 1) / rows));
+    if (a.win.padded) hipLaunchKernelGGL((dispatch_walk_kernel<TPR_SHIFT, true, FP8>), grid, dim3(256), 0, s, a, p, f);
+    else hipLaunchKernelGGL((dispatch_walk_kernel<TPR_SHIFT, false, FP8>), grid, dim3(256), 0, s, a, p, f);
+}
+
+// One launch of the walk over the places [first, last) of the list.  The first one also fills the side arrays.
+template <bool FP8>
+static void launch_walk(const DispatchArgs& a, const DispatchPlan& d, int units, int first, int last, const StagedRows& f,
+                        hipStream_t s) {
+    WalkPlan p;
+    p.piece = d.piece; p.units = units; p.tpr_shift = d.tpr_shift; p.first = first; p.last = last;
+    p.entries = a.T * a.K;
+    p.side_blocks = first == 0 && (a.recv_w || a.recv_src) ? (p.entries + 2047) / 2048 * 8 : 0;
+    switch (d.tpr_shift) {
+        case 4: launch_walk_kernel<4, FP8>(a, p, f, s); break;
+        case 5: launch_walk_kernel<5, FP8>(a, p, f, s); break;
+        case 6: launch_walk_kernel<6, FP8>(a, p, f, s); break;
+        case 7: launch_walk_kernel<7, FP8>(a, p, f, s); break;
+        default: launch_walk_kernel<8, FP8>(a, p, f, s); break;
     }
 }
 
 hipError_t launch_dispatch(const DispatchArgs& a, hipStream_t s) {
     const int units = a.H / 8;  // 16-byte units per row
     DispatchPlan d;
-    if (plan_dispatch(a.T, a.K, a.H, a.E, a.order, a.run_start != nullptr, a.prefetched_rows, &d)) {
-        RunPlan p;
-        p.group = d.group; p.nblocks = d.blocks; p.units = units; p.piece = d.piece; p.tpr_shift = d.tpr_shift;
-        p.splits = d.splits;
-        launch_run_order(a, d, p, s, [&](const RunPlan& q, int nb) {
-            switch (q.tpr_shift) {
-                case 4: launch_runs<4>(a, q, nb, s); break;
-                case 5: launch_runs<5>(a, q, nb, s); break;
-                case 6: launch_runs<6>(a, q, nb, s); break;
-                case 7: launch_runs<7>(a, q, nb, s); break;
-                default: launch_runs<8>(a, q, nb, s); break;
-            }
-        });
+    if (plan_dispatch(a.T, a.K, a.H, a.E, a.R, a.order, a.walk != nullptr, a.prefetched_rows, &d)) {
+        const int n = a.T * a.K;
+        for (int b0 = 0; b0 < d.blocks; b0 += d.blocks_per_launch) {
+            const int nb = std::min(d.blocks_per_launch, d.blocks - b0);
+            const int64_t e0 = (int64_t)b0 * d.block_entries, e1 = std::min<int64_t>(n, (int64_t)(b0 + nb) * d.block_entries);
+            const int t0 = (int)(e0 / a.K), t1 = (int)((e1 + a.K - 1) / a.K);
+            // a read pass, unless the layout launch has read these rows already
+            if (a.order == EP_ORDER_DESTINATION && t1 > a.prefetched_rows)
+                hipLaunchKernelGGL(dispatch_warm_kernel, dim3(2048), dim3(256), 0, s, a, units, t0, t1, b0 == 0 ? 1 : 0);
+            launch_walk<false>(a, d, units, (int)e0, (int)e1, StagedRows{}, s);
+        }
         return hipGetLastError();
     }
     const int nseg = (units + kWave - 1) / kWave;
@@ -493,41 +481,18 @@ hipError_t launch_dispatch_fp8(const DispatchArgs& a, float* recv_scales, hipStr
     return hipGetLastError();
 }
 
-// Units of a staged FP8 row: H/16 of codes, then the scales rounded up to whole units.
-static int fp8_code_units(int H) { return H / 16; }
-static int fp8_row_units(int H) { return H / 16 + (H / 32 + 15) / 16; }
-
 bool dispatch_fp8_staged_possible(const DispatchArgs& a) {
     DispatchPlan d;
-    return a.H % 128 == 0 && plan_rows(a.T, a.K, a.H, fp8_row_units(a.H), kFp8Slices, a.E, EP_ORDER_DESTINATION_RESIDENT,
-                                       a.run_start != nullptr, 0, &d);
-}
-
-template <int TPR_SHIFT>
-static void launch_runs_fp8(const DispatchArgs& a, const RunPlan& p, int nblocks, const uint8_t* staged, int64_t pitch,
-                            float* recv_scales, hipStream_t s) {
-    const dim3 grid((unsigned)(kFp8Slices * a.E * p.splits), (unsigned)nblocks);
-    const StagedRows f = {staged, pitch, recv_scales, fp8_code_units(a.H), a.H / 128};
-    if (a.win.padded) hipLaunchKernelGGL((dispatch_runs_kernel<TPR_SHIFT, true, true>), grid, dim3(256), 0, s, a, p, f);
-    else hipLaunchKernelGGL((dispatch_runs_kernel<TPR_SHIFT, false, true>), grid, dim3(256), 0, s, a, p, f);
+    return a.H % 128 == 0 && plan_dispatch_fp8_staged(a.T, a.K, a.H, a.E, a.R, a.walk != nullptr, &d);
 }
 
 hipError_t launch_dispatch_fp8_staged(const DispatchArgs& a, float* recv_scales, const uint8_t* staged, int64_t pitch,
                                       hipStream_t s) {
     DispatchPlan d;
-    if (a.H % 128 != 0 || !plan_rows(a.T, a.K, a.H, fp8_row_units(a.H), kFp8Slices, a.E, EP_ORDER_DESTINATION_RESIDENT,
-                                     a.run_start != nullptr, 0, &d))
-        return hipErrorInvalidValue;
-    RunPlan p;
-    p.group = d.group; p.nblocks = d.blocks; p.units = fp8_row_units(a.H); p.piece = d.piece; p.tpr_shift = d.tpr_shift;
-    p.splits = d.splits; p.first_block = 0;
-    switch (p.tpr_shift) {  // every block in one launch: the staged rows were written just before, nothing to read ahead
-        case 4: launch_runs_fp8<4>(a, p, d.blocks, staged, pitch, recv_scales, s); break;
-        case 5: launch_runs_fp8<5>(a, p, d.blocks, staged, pitch, recv_scales, s); break;
-        case 6: launch_runs_fp8<6>(a, p, d.blocks, staged, pitch, recv_scales, s); break;
-        case 7: launch_runs_fp8<7>(a, p, d.blocks, staged, pitch, recv_scales, s); break;
-        default: launch_runs_fp8<8>(a, p, d.blocks, staged, pitch, recv_scales, s); break;
-    }
+    if (a.H % 128 != 0 || !plan_dispatch_fp8_staged(a.T, a.K, a.H, a.E, a.R, a.walk != nullptr, &d)) return hipErrorInvalidValue;
+    const StagedRows f = {staged, pitch, recv_scales, fp8_code_units(a.H), a.H / 128};
+    // the whole list in one launch: the staged rows were written just before, nothing to read ahead
+    launch_walk<true>(a, d, fp8_row_units(a.H), 0, a.T * a.K, f, s);
     return hipGetLastError();
 }
 

@@ -47,7 +47,6 @@ struct LayoutArgs {
     int32_t* expert_count;    // [E]
     int32_t* expert_kept;     // [E]
     int32_t* expert_offset;   // [E+1]
-    int32_t* own_prefix;      // [E+1]
     int32_t* rank_pair_count; // [R]
     int32_t* rank_token_count;// [R]
     int32_t* rank_offset;     // [R+1]
@@ -69,8 +68,10 @@ struct LayoutArgs {
     int64_t rows_cap;         // a launch that also dispatches: rows its output takes (more are flagged); else -1
     int32_t* recv_count;      // such a launch: where the caller wants the rows placed per expert [E]; else nullptr
     int64_t* drop_hint;       // mapped host word or nullptr: gets kept | dropped << 32 (rows of padded windows)
-    int32_t* run_start;       // [nwc+1, E] or nullptr: first sorted position of expert e among the entries
-                              // of wave-chunks >= c (row c); only the histogram kernels fill it
+    int2* walk;               // or nullptr: {token, row} of every entry that has a row, block of walk_group wave-chunks
+                              // by block, within a block expert by expert, within an expert in entry order, no gaps
+    int walk_group;           // a multiple or a divisor of walk_waves
+    int walk_waves;           // wavefronts per workgroup of a layout that makes a walk list
 };
 
 // Addressing of the receive windows: element offset of logical row r is
@@ -127,15 +128,12 @@ struct DispatchArgs {
     const int32_t* expert_kept;
     int32_t* totals;
     int T, K, H, E;
-    // run-ordered kernel only (see launch_dispatch): the expert-sorted entry list of the
-    // layout and the table of where each wave-chunk's entries start inside it
+    // destination order only (see launch_dispatch): the walk list and the expert-sorted entry list of the layout
+    const int2* walk;             // or nullptr: the layout did not make one
     const int32_t* sorted_token;  // [n]
     const int32_t* sorted_k;      // [n]
     const int32_t* sorted_row;    // [n]
-    const int32_t* own_prefix;    // [E+1] first sorted position of each expert
-    const int32_t* run_start;     // [nwc+1, E], or nullptr: the layout did not produce one
-    int nwc;                      // wave-chunks of the layout
-    int chunk_entries;            // entries per wave-chunk
+    int R;
     int order;                    // EP_ORDER_*
     int prefetched_rows;          // leading token rows the layout launch has already read into cache
 };
@@ -267,21 +265,27 @@ void plan_layout(int n, int* passes, int* nwc);
 struct DispatchPlan {
     int run_order;          // 1: destination order; 0: token order (nothing else is set then)
     int group;              // wave-chunks of the layout per block
+    int waves;              // wavefronts per workgroup of the layout
     int blocks;             // blocks of the input
     int block_entries;      // routed entries per block
-    int splits;             // workgroups that share the run of one (block, expert)
+    int splits;             // workgroups that a run of average length -- the entries of one expert in one block -- takes
     int piece;              // 16-byte units of a row per XCD slice
     int tpr_shift;          // log2(threads that share one row piece)
     int blocks_per_launch;  // blocks per copy launch
     int launches;           // copy launches
     int read_passes;        // token read passes (at most one per copy launch)
 };
-bool plan_dispatch(int T, int K, int H, int E, int order, bool have_runs, int prefetched_rows, DispatchPlan* out);
-// True when launch_layout fills LayoutArgs::run_start for this plan.
-bool layout_writes_runs(const LayoutArgs& a);
+bool plan_dispatch(int T, int K, int H, int E, int R, int order, bool have_walk, int prefetched_rows, DispatchPlan* out);
+// The same for FP8 rows copied from a staging copy (destination order).
+bool plan_dispatch_fp8_staged(int T, int K, int H, int E, int R, bool have_walk, DispatchPlan* out);
+// How a layout that makes a walk list in blocks of up to `most` wave-chunks is cut: returns the wave-chunks per block,
+// and in *waves the wavefronts per workgroup.
+int plan_walk(int E, int R, int most, int* waves);
+constexpr int kWalkPad = 32;  // entries behind the list that a copy may read (and does not use)
 // True when launch_layout reads LayoutArgs::warm_x for this plan.
 bool layout_prefetches(const LayoutArgs& a);
-// Token bytes one read pass of the destination-ordered dispatch covers.
+// Token bytes one read pass of the destination-ordered dispatch covers, and those a layout launch reads ahead (117 MB
+// of tokens read ahead at once and copied in one launch: 373 for 373 us on one box, 387 for 378 on another).
 constexpr int64_t kWarmBytes = 64ll << 20;
 // Inputs from this many routed entries on may be dispatched in destination order.
 constexpr int kRunOrderMinEntries = 8192;

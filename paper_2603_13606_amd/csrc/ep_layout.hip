@@ -52,11 +52,6 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-}
-
 __device__ __forceinline__ int lane_id() {
     return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
@@ -124,7 +119,7 @@ struct Entry {
     bool lead;     // first k of its token that names destination rank d
 };
 
-// LDS carve-up shared by the kernels.  wh .. flag are contiguous (zeroed in one sweep).
+// LDS carve-up shared by the kernels.  wh .. flag are contiguous.
 struct Lds {
     int32_t *wh;      // [nw+1][W] per-wave histograms, later "entries of the bin in the earlier waves of the
                       //     chunk"; row nw stands in for the rows a smaller workgroup does not have, so that
@@ -135,8 +130,12 @@ struct Lds {
                       //     concatenated layout unless the caller gave the first rows; the rank bins are the
                       //     last R bins: for compact staging windows rank_offset[d] = S[E+2+d] - S[E+2]
     int32_t *before;  // [W] entries of each bin in earlier chunks
-    int32_t *wsum;    // [kLayoutWavesPerBlock] per-wave sums of the scan (0 for waves the workgroup does not have)
     int32_t *flag;    // [1] set when a thread of the workgroup gave up waiting for another chunk
+    // with a walk list only
+    int32_t *first;   // [kLayoutWavesPerBlock] where each block of the chunk starts in the list
+    int32_t *bstart;  // [E] entries of the expert before the block of this chunk (before the chunk, if it holds several blocks)
+    int32_t *bcount;  // [E] entries of the expert in the block (in the chunk)
+    int32_t *walk;    // [blocks of the chunk][E] place of an entry in the list, less its slot and the block's start
 };
 
 __device__ __forceinline__ Lds carve_lds(int32_t* base, const LayoutArgs& a, int nw) {
@@ -145,14 +144,22 @@ __device__ __forceinline__ Lds carve_lds(int32_t* base, const LayoutArgs& a, int
     l.tot = l.wh + (nw + 1) * a.W;
     l.S = l.tot + a.W;
     l.before = l.S + a.W;
-    l.wsum = l.before + a.W;
-    l.flag = l.wsum + kLayoutWavesPerBlock;
+    l.flag = l.before + a.W;
+    l.first = l.flag + 1;
+    l.bstart = l.first + kLayoutWavesPerBlock;
+    l.bcount = l.bstart + a.E;
+    l.walk = l.bcount + a.E;
     return l;
 }
 
-constexpr int lds_ints(int W, int nw) { return (nw + 1) * W + 3 * W + kLayoutWavesPerBlock + 1; }
+constexpr int lds_ints(int W, int nw) { return (nw + 1) * W + 3 * W + 1; }
 
-size_t lds_bytes(const LayoutArgs& a, int nw) { return sizeof(int32_t) * (size_t)lds_ints(a.W, nw); }
+// What the walk list adds, with blocks of `group` wave-chunks.
+constexpr int walk_lds_ints(int E, int nw, int group) { return kLayoutWavesPerBlock + (2 + (nw > group ? nw / group : 1)) * E; }
+
+size_t lds_bytes(const LayoutArgs& a, int nw) {
+    return sizeof(int32_t) * (size_t)(lds_ints(a.W, nw) + (a.walk ? walk_lds_ints(a.E, nw, a.walk_group) : 0));
+}
 
 // Marks the entries that are the first of their token to name their destination
 // rank.  The entries of a token sit in consecutive lanes, so lane l compares its
@@ -250,7 +257,10 @@ __device__ __forceinline__ int first_slot(const LayoutArgs& a, const Lds& l, int
 // Writes what the layout records for one entry, given its rank inside the chunk among the
 // entries of its expert and (for a leader) among the tokens of its destination rank; the
 // entries of earlier chunks (l.before) turn the ranks into slots.
-__device__ __forceinline__ void emit_entry(const LayoutArgs& a, const Entry& x, int slot, int rslot, const Lds& l) {
+// walk: the places of the wave's block, walk_base: where the block starts in the walk list.
+template <bool WALK>
+__device__ __forceinline__ void emit_entry(const LayoutArgs& a, const Entry& x, int slot, int rslot, const Lds& l,
+                                           const int32_t* walk, int walk_base) {
     int row = -1, rrow = -1;
     if (x.ok) {
         slot += l.before[x.e];
@@ -262,6 +272,7 @@ __device__ __forceinline__ void emit_entry(const LayoutArgs& a, const Entry& x, 
             a.sorted_k[pos] = x.k;
             a.sorted_row[pos] = row;
         }
+        if (WALK && row >= 0) a.walk[walk_base + walk[x.e] + slot] = make_int2(x.t, row);
     }
     if (x.lead) rrow = first_slot(a, l, x.d) + l.before[a.E + 2 + x.d] + rslot;
     if (x.i >= 0) {
@@ -317,37 +328,73 @@ __device__ __forceinline__ void place_group(const LayoutArgs& a, const Entry (&e
     }
 }
 
+template <bool WALK>
 __device__ __forceinline__ void emit_group(const LayoutArgs& a, const Entry (&en)[PU], int p0, const int (&slot)[PU],
-                                           const int (&rslot)[PU], const Lds& l) {
+                                           const int (&rslot)[PU], const Lds& l, const int32_t* walk, int walk_base) {
 #pragma unroll
-    for (int j = 0; j < PU; ++j)
-        if (p0 + j < a.passes) emit_entry(a, en[j], slot[j], rslot[j], l);  // wave-uniform condition
+    for (int j = 0; j < PU; ++j)  // wave-uniform condition
+        if (p0 + j < a.passes) emit_entry<WALK>(a, en[j], slot[j], rslot[j], l, walk, walk_base);
 }
 
-// Exclusive scan of the totals tot[0..W) over all bins into S, by the whole workgroup
-// (thread = bin; with more bins than threads, in rounds).  Starts with a barrier (tot and
-// whatever else was written to LDS before become visible) and ends with one (S is final).
-// Must be called by every thread of the workgroup.
-__device__ void block_scan_totals(const LayoutArgs& a, const Lds& l, int tid, int lane, int w, int nw) {
+// The scans over the bins are done by one wavefront each, while the others wait: done by all 16, every wave adds up the
+// sums of all waves, and 16 waves share the four instruction streams of a compute unit (0.3 us of the layout).
+constexpr int kScanRows = 4;  // rows of 64 bins whose loads are issued together
+
+// Exclusive scan of the totals tot[0..W) over all bins into S.
+__device__ void scan_totals(const LayoutArgs& a, const Lds& l, int lane) {
     int carry = 0;
-    lds_barrier();
-    for (int c0 = 0; c0 < a.W; c0 += blockDim.x) {
-        const int c = c0 + tid;
-        const int v = c < a.W ? l.tot[c] : 0;
-        const int inc = wave_inclusive_scan(v);
-        if (lane == kWave - 1) l.wsum[w] = inc;
-        lds_barrier();
-        int below = 0, all = 0;
+    for (int c0 = 0; c0 < a.W; c0 += kScanRows * kWave) {
+        int v[kScanRows];
 #pragma unroll
-        for (int r = 0; r < kLayoutWavesPerBlock; ++r) {  // waves the workgroup does not have left 0
-            const int s = l.wsum[r];
-            below += r < w ? s : 0;
-            all += s;
+        for (int r = 0; r < kScanRows; ++r) {
+            const int c = c0 + r * kWave + lane;
+            v[r] = c < a.W ? l.tot[c] : 0;
         }
-        if (c < a.W) l.S[c] = carry + below + inc - v;
-        carry += all;
-        lds_barrier();
+#pragma unroll
+        for (int r = 0; r < kScanRows; ++r) {
+            const int c = c0 + r * kWave + lane;
+            const int inc = wave_inclusive_scan(v[r]);
+            if (c < a.W) l.S[c] = carry + inc - v[r];
+            carry += __builtin_amdgcn_readlane(inc, kWave - 1);
+        }
     }
+}
+
+// The places of block sb of this chunk (the only one, or one of several) in the walk list:
+// l.walk[sb][e] + slot is the place, counted from the start of the block, of the entry of expert e with that slot;
+// l.first[sb] is where the block starts: the rows of all earlier blocks.  A row count of an expert is its entry count
+// cut at the capacity.
+template <bool ONE_GROUP>
+__device__ void scan_walk(const LayoutArgs& a, const Lds& l, int sb, int nsub, int lane) {
+    const int E = a.E, cap = a.padded ? a.C : 0x7fffffff;
+    // the wave histograms hold, per bin, the entries of the chunk before a wave, or, once a single load group has been
+    // placed, those up to and including it
+    const int32_t* lo = l.wh + (sb * a.walk_group - (ONE_GROUP ? 1 : 0)) * a.W;
+    const int32_t* hi = lo + a.walk_group * a.W;
+    int base = 0, carry = 0;
+    for (int c0 = 0; c0 < E; c0 += kScanRows * kWave) {
+        int start[kScanRows], rows[kScanRows];
+#pragma unroll
+        for (int r = 0; r < kScanRows; ++r) {
+            const int c = c0 + r * kWave + lane;
+            start[r] = rows[r] = 0;
+            if (c < E) {
+                const int bstart = l.bstart[c];
+                start[r] = bstart + (sb == 0 ? 0 : lo[c]);
+                rows[r] = bstart + (sb == nsub - 1 ? l.bcount[c] : hi[c]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kScanRows; ++r) {
+            const int c = c0 + r * kWave + lane;
+            const int before = min(start[r], cap), n = min(rows[r], cap) - before;
+            const int inc = wave_inclusive_scan(n);
+            base += __builtin_amdgcn_readlane(wave_inclusive_scan(before), kWave - 1);
+            if (c < E) l.walk[sb * E + c] = carry + inc - n - start[r];
+            carry += __builtin_amdgcn_readlane(inc, kWave - 1);
+        }
+    }
+    if (lane == 0) l.first[sb] = base;
 }
 
 // The per-expert / per-rank arrays and the totals block (all but the status word) in
@@ -363,8 +410,6 @@ __device__ int write_tables(const LayoutArgs& a, const Lds& l, int tid, int lane
         a.expert_kept[e] = a.padded ? min(v, a.C) : v;
         if (a.recv_count) a.recv_count[e] = a.padded ? min(v, a.C) : v;
         a.expert_offset[e] = first_row(a, l, e);
-        a.own_prefix[e] = S[e];
-        if (a.run_start) a.run_start[e] = S[e];  // row 0: nothing precedes the first wave-chunk
     }
     if (a.rank_pair_count) {
         for (int d = tid; d <= R; d += blockDim.x) {
@@ -392,7 +437,6 @@ __device__ int write_tables(const LayoutArgs& a, const Lds& l, int tid, int lane
     const int rows_end = a.padded ? E * a.C : (a.expert_base ? rend : total_e);
     if (lane == 0) {
         a.expert_offset[E] = rows_end;
-        a.own_prefix[E] = total_e;
         a.totals[TOT_KEPT] = kept;
         a.totals[TOT_DROPPED] = dropped;
         a.totals[TOT_MASKED] = tot[E];
@@ -520,7 +564,7 @@ __device__ void quantize_tokens(const LayoutArgs& a, int wb, int nwb) {
     }
 }
 
-template <int HB, bool ONE_GROUP, bool FUSED>
+template <int HB, bool ONE_GROUP, bool FUSED, bool WALK>
 __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, const int b) {
     const int wpb = blockDim.x >> 6;
     const Lds l = carve_lds(lds, a, wpb);
@@ -592,12 +636,14 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
     //     chunk repeat its words, and the chunk's own word is among them: no exceptions to
     //     test for).  Which words of a batch count, and which belong to earlier chunks, are
     //     wave-uniform bit masks.
+    const int nsub = WALK && wpb > a.walk_group ? wpb / a.walk_group : 1;  // blocks of the walk list in this chunk
     if constexpr (multi) {
+        const int gchunks = WALK ? max(a.walk_group / wpb, 1) : 1, g0 = WALK ? b / gchunks * gchunks : 0;  // or chunks in its block
         int rounds = 0;  // of this thread, over all its batches
         bool gave_up = false;
         bool have = true;  // hv holds the batch (tid, 0)
         for (int c = tid; c < W; c += blockDim.x) {
-            int before = 0, total = 0;
+            int before = 0, total = 0, bstart = 0, bcount = 0;
             for (int r0 = 0; r0 < nchunks; r0 += HB) {
                 for (;;) {
                     if (!have) look_across(a, c, r0, hv);
@@ -612,23 +658,39 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
                     }
                     __builtin_amdgcn_s_sleep(1);
                 }
-                const int nvalid = min(nchunks - r0, HB), nbefore = min(max(b - r0, 0), HB);
-                const uint32_t valid = nvalid >= 32 ? ~0u : (1u << nvalid) - 1u;
-                const uint32_t earlier = nbefore >= 32 ? ~0u : (1u << nbefore) - 1u;
+                auto up_to = [&](int chunk) {  // the chunks of the batch that come before this one
+                    const int m = min(max(chunk - r0, 0), HB);
+                    return m >= 32 ? ~0u : (1u << m) - 1u;
+                };
+                const uint32_t valid = up_to(nchunks), earlier = up_to(b);
+                const uint32_t blk_earlier = WALK ? up_to(g0) : 0u, blk = WALK ? up_to(g0 + gchunks) & ~blk_earlier : 0u;
 #pragma unroll
                 for (int j = 0; j < HB; ++j) {
                     const uint32_t cnt = hv[j] & kCountMask & (0u - ((valid >> j) & 1u));
                     total += (int)cnt;
                     before += (int)(cnt & (0u - ((earlier >> j) & 1u)));
+                    if (WALK) bstart += (int)(cnt & (0u - ((blk_earlier >> j) & 1u)));
+                    if (WALK) bcount += (int)(cnt & (0u - ((blk >> j) & 1u)));
                 }
+            }
+            if (WALK && c < a.E) {
+                l.bstart[c] = bstart;
+                l.bcount[c] = bcount;
             }
             l.tot[c] = total;  // the chunk's own sum is one of the words
             l.before[c] = before;
         }
         if (gave_up) atomicOr(l.flag, 1);
     }
-    // (6) the scan over the bins (its first barrier also makes tot, before and flag final)
-    block_scan_totals(a, l, tid, lane, w, wpb);
+    // (6) the scans over the bins: the totals by wave 0, the walk list by the others (the workgroup of the tables has none)
+    lds_barrier();
+    if (w == 0) scan_totals(a, l, lane);
+    else if (WALK && b < nchunks) {
+        for (int sb = w - 1; sb < nsub; sb += wpb - 1) scan_walk<ONE_GROUP>(a, l, sb, nsub, lane);
+    }
+    lds_barrier();
+    const int sb = nsub > 1 ? w / a.walk_group : 0;  // the block of this wave
+    const int walk_base = WALK ? __builtin_amdgcn_readfirstlane(l.first[sb]) : 0;
     // thread 0 reports for the workgroup: the value it gets back tells wave 0 whether this
     // workgroup is the last to have looked across (then every chunk is done with pub and ctl,
     // and it may advance the generation) and whether any workgroup gave up waiting
@@ -646,15 +708,7 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
                 rank_group(a, en, p0, lane, iw);
                 place_group(a, en, iw, p0, l.wh + w * W, sl, rsl);
             }
-            emit_group(a, en, p0, sl, rsl, l);
-        }
-        // the walk has advanced the wave's prefixes past its own entries: they are now the
-        // positions at which the next wave-chunk's entries start in the expert-sorted list
-        if (a.run_start) {
-            wave_lds_fence();
-            int32_t* rs = a.run_start + (int64_t)(wc + 1) * a.E;
-            const int32_t* h = l.wh + w * W;
-            for (int e = lane; e < a.E; e += kWave) rs[e] = l.S[e] + l.before[e] + h[e];
+            emit_group<WALK>(a, en, p0, sl, rsl, l, l.walk + sb * a.E, walk_base);
         }
     }
     // (8) the per-expert / per-rank arrays and the totals.  With several chunks they come from a
@@ -686,7 +740,7 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
     }
 }
 
-template <bool MULTI, bool ONE_GROUP>
+template <bool MULTI, bool ONE_GROUP, bool WALK>
 __global__ __launch_bounds__(1024) void layout_kernel(LayoutArgs a) {
     extern __shared__ int32_t lds[];
     const int nlay = a.nchunks + (MULTI ? 1 : 0);  // workgroups that lay out: the chunks and, with several, the one of the tables
@@ -698,7 +752,7 @@ __global__ __launch_bounds__(1024) void layout_kernel(LayoutArgs a) {
         else warm_tokens(a, blockIdx.x - nlay, gridDim.x - nlay);
         return;
     }
-    layout_chunk<MULTI ? 32 : 0, ONE_GROUP, false>(a, lds, blockIdx.x);
+    layout_chunk<MULTI ? 32 : 0, ONE_GROUP, false, WALK>(a, lds, blockIdx.x);
 }
 
 // ---- layout and direct dispatch of a small input in ONE launch (Sec. IV-C: in the
@@ -728,7 +782,7 @@ __global__ __launch_bounds__(1024, IDS == 1 ? 4 : 8) void layout_dispatch_kernel
                                                                int group, int parts, int spp) {
     extern __shared__ int32_t lds[];
     if ((int)blockIdx.x < nlay) {
-        layout_chunk<MULTI ? kFusedIds : 0, true, true>(a, lds, blockIdx.x);  // at most kFusedIds chunks
+        layout_chunk<MULTI ? kFusedIds : 0, true, true, false>(a, lds, blockIdx.x);  // at most kFusedIds chunks
         return;
     }
     constexpr int threads = kLayoutWavesPerBlock * kWave;
@@ -844,7 +898,23 @@ void plan_layout(int n, int* passes, int* nwc) {
     *nwc = (n + kWave * p - 1) / (kWave * p);
 }
 
-bool layout_writes_runs(const LayoutArgs& a) { return a.run_start != nullptr; }
+// A block of the walk list is a whole number of chunks (workgroups of the layout) or a whole part of one; the workgroup
+// is as large as the tables in LDS allow.
+int plan_walk(int E, int R, int most, int* waves) {
+    const int W = E + 2 + R;
+    for (int nw = kLayoutWavesPerBlock;; nw >>= 1) {
+        int group = most / nw * nw;
+        if (group == 0) {
+            group = 1;
+            while (2 * group <= most) group *= 2;
+        }
+        if (nw == 2) group = std::max(group, 2);  // two waves and one block always fit, and 512 wave-chunks allow no fewer
+        if (nw == 2 || sizeof(int32_t) * (size_t)(lds_ints(W, nw) + walk_lds_ints(E, nw, group)) <= kLdsLimit) {
+            *waves = nw;
+            return group;
+        }
+    }
+}
 
 // The read-ahead rides on the layout kernel of inputs that are laid out by several workgroups.
 bool layout_prefetches(const LayoutArgs& a) {
@@ -863,7 +933,7 @@ constexpr int64_t kFusedMaxBytes = 176ll << 20;
 
 bool layout_dispatch_fusable(const LayoutArgs& a, const DispatchArgs& d) {
     // may go in destination order; and the runs are recorded by the cut of the plan, which this launch may change
-    if (a.run_start) return false;
+    if (a.walk) return false;
     if (((int64_t)a.n + a.T) * d.H * 2 > kFusedMaxBytes) return false;
     return a.n >= 1 && a.n <= kFusedMaxEntries && a.K <= kWave && a.E <= kLayoutWavesPerBlock * kWave && d.H >= 8 &&
            lds_bytes(a, kLayoutWavesPerBlock) <= kLdsLimit;
@@ -919,8 +989,8 @@ hipError_t launch_layout(const LayoutArgs& a_in, hipStream_t s) {
     LayoutArgs a = a_in;
     a.nchunks = 1;
     // Workgroups of 16 waves, fewer when the bin tables would not fit the LDS otherwise.
-    int wpb = kLayoutWavesPerBlock;
-    while (wpb > 1 && lds_bytes(a, wpb) > kLdsLimit) wpb >>= 1;
+    int wpb = a.walk ? a.walk_waves : kLayoutWavesPerBlock;
+    while (wpb > 1 && !a.walk && lds_bytes(a, wpb) > kLdsLimit) wpb >>= 1;
     if (lds_bytes(a, wpb) > kLdsLimit) return hipErrorInvalidValue;
     int nblk = (a.nwc + wpb - 1) / wpb;
     if (nblk < 1) nblk = 1;
@@ -933,10 +1003,13 @@ hipError_t launch_layout(const LayoutArgs& a_in, hipStream_t s) {
     const dim3 grid(nlay + nwarm), block(wpb * kWave);
     const size_t lds = lds_bytes(a, wpb);
     const bool one_group = a.passes <= PU;
-    if (nblk > 1 && one_group) hipLaunchKernelGGL((layout_kernel<true, true>), grid, block, lds, s, a);
-    else if (nblk > 1) hipLaunchKernelGGL((layout_kernel<true, false>), grid, block, lds, s, a);
-    else if (one_group) hipLaunchKernelGGL((layout_kernel<false, true>), grid, block, lds, s, a);
-    else hipLaunchKernelGGL((layout_kernel<false, false>), grid, block, lds, s, a);
+    if (a.walk && nblk == 1) return hipErrorInvalidValue;  // inputs this small have no walk list
+    if (a.walk && one_group) hipLaunchKernelGGL((layout_kernel<true, true, true>), grid, block, lds, s, a);
+    else if (a.walk) hipLaunchKernelGGL((layout_kernel<true, false, true>), grid, block, lds, s, a);
+    else if (nblk > 1 && one_group) hipLaunchKernelGGL((layout_kernel<true, true, false>), grid, block, lds, s, a);
+    else if (nblk > 1) hipLaunchKernelGGL((layout_kernel<true, false, false>), grid, block, lds, s, a);
+    else if (one_group) hipLaunchKernelGGL((layout_kernel<false, true, false>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((layout_kernel<false, false, false>), grid, block, lds, s, a);
     return hipGetLastError();
 }
 

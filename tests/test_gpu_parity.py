@@ -888,6 +888,43 @@ def test_dispatch_destination_order_parity(ep, hx, oracle_mod, name, T, H, mode,
     _run_path(ep, hx, oracle_mod, name, T, H, mode, C, order=int(str(order)[0]), prefetch=prefetch)
 
 
+@pytest.mark.parametrize("R,E,K,T,H,C,masked", [
+    (8, 64, 1, 8201, 16384, 0, 0.02),      # blocks of the walk list smaller than a workgroup of the layout, one pass
+    (8, 64, 1, 140001, 2048, 0, 0.0),      # the same with more passes than a wave keeps in registers
+    (8, 64, 1, 8201, 16384, 150, 0.02),    # and with rows cut by the capacity, blocks in the middle of an expert's last ones
+    (4, 24, 5, 40003, 64, 3000, 0.3),      # several passes, one block over all workgroups, many masked entries
+    (1024, 1024, 2, 4099, 72, 0, 0.01),    # tables that leave two waves per workgroup; over 32 workgroups look across
+    (8, 1000, 9, 1003, 136, 9, 0.05),
+    (1, 1, 1, 8193, 128, 5000, 0.0),       # one expert takes every row, some are cut
+    (2, 6, 3, 2731, 1096, 0, 1.0),         # nothing is routed
+])
+def test_walk_list_places_every_row_as_the_token_walk_does(ep, hx, R, E, K, T, H, C, masked):
+    """The destination-ordered dispatch against the token-ordered one over the cuts of the walk list, byte for byte:
+    rows, side arrays, counts and everything around them."""
+    gen = torch.Generator(hx.DEV).manual_seed(T)
+    topk = torch.rand((T, E), generator=gen, device=hx.DEV).topk(K, dim=1).indices.to(torch.int32) if E > 1 else \
+        torch.zeros((T, 1), dtype=torch.int32, device=hx.DEV)
+    topk[torch.rand((T, K), generator=gen, device=hx.DEV) < masked] = -1
+    x = torch.randint(-30000, 30000, (T, H), generator=gen, device=hx.DEV, dtype=torch.int32).to(torch.int16).view(torch.bfloat16)
+    w = torch.rand((T, K), generator=gen, device=hx.DEV)
+    rows = E * C if C else T * K
+    got = []
+    for order in (0, 1):
+        g = ep.ep_group_create(ep.make_config(R, E, H, K, T, mode=ep.EP_MODE_LL if C else ep.EP_MODE_HT, slots_per_subregion=C,
+                                              dispatch_order=order))
+        store = torch.full((rows, H), -7.0, dtype=torch.bfloat16, device=hx.DEV)
+        side = [torch.full((rows,), -3.5, device=hx.DEV), torch.full((rows,), -9, dtype=torch.int32, device=hx.DEV),
+                torch.full((E,), -1, dtype=torch.int32, device=hx.DEV)]
+        h = ep.ep_layout(g, topk)
+        ep.ep_dispatch(h, x, store.view(E, C, H) if C else store, topk_weights=w, recv_w=side[0], recv_src=side[1], recv_count=side[2])
+        info = ep.ep_handle_query(h)
+        got.append([store.view(torch.int16)] + side + [(info.rows_kept, info.rows_dropped, info.status)])
+        ep.ep_handle_destroy(h)
+        ep.ep_group_destroy(g)
+    for a, b in zip(*got):
+        assert torch.equal(a, b) if isinstance(a, torch.Tensor) else a == b
+
+
 def test_layout_dispatch_one_call_quantises_ahead(ep, hx, oracle_mod):
     """ep_layout_dispatch on a large input with FP8 outputs in a group that quantises ahead: the
     layout part quantises the tokens it is given, the dispatch part copies the staged rows; codes,

@@ -628,6 +628,7 @@ static ep_result_t prepare_layout(ep_handle_t* handle, ep_group_t g, const ep_te
     a.topk_stride = topk_idx->stride[0];
     a.expert_base = expert_base ? (const int32_t*)expert_base->data : nullptr;
     a.T = (int)T; a.K = c.top_k; a.E = c.num_experts; a.R = c.num_ranks; a.L = g->L; a.L_shift = g->L_shift; a.K_shift = g->K_shift;
+    a.K_magic = divide_magic(a.K); a.L_magic = divide_magic(a.L);
     a.padded = c.mode == EP_MODE_LL; a.C = g->C; a.C_rank = c.max_tokens_per_rank;
     a.n = (int)(T * c.top_k);
     plan_layout(a.n, &a.passes, &a.nwc);
@@ -639,12 +640,12 @@ static ep_result_t prepare_layout(ep_handle_t* handle, ep_group_t g, const ep_te
     a.slot = s.slot; a.dst_row = s.dst_row; a.rank_row = s.rank_row; a.sorted_token = s.sorted_token;
     a.sorted_k = s.sorted_k; a.sorted_row = s.sorted_row;
     a.entry_rank = s.entry_rank;
-    a.walk = nullptr; a.walk_group = 1; a.walk_waves = 0;
+    a.walk = nullptr; a.walk_group = 1;
     if (makes_walk(c, T)) {
         DispatchPlan plan;
         const bool there = c.quantize_ahead ? plan_dispatch_fp8_staged(a.T, a.K, c.hidden, a.E, a.R, true, &plan)
                                             : plan_dispatch(a.T, a.K, c.hidden, a.E, a.R, EP_ORDER_DESTINATION_RESIDENT, true, 0, &plan);
-        if (there) { a.walk = (int2*)s.walk; a.walk_group = plan.group; a.walk_waves = plan.waves; }
+        if (there) { a.walk = (int2*)s.walk; a.walk_group = plan.group; }
     }
     a.warm_x = nullptr; a.warm_stride = 0; a.warm_rows = 0; a.warm_units = c.hidden / 8; a.nchunks = 1;
     a.rows_cap = -1; a.recv_count = nullptr;
@@ -1065,6 +1066,7 @@ ep_result_t ep_layout_static(const ep_group_config_t* cfg, const ep_tensor_t* to
     a.topk_stride = topk_idx->stride[0];
     a.expert_base = expert_base ? (const int32_t*)expert_base->data : nullptr;
     a.L = a.E / a.R; a.L_shift = log2_exact(a.L); a.K_shift = log2_exact(a.K);
+    a.K_magic = divide_magic(a.K); a.L_magic = divide_magic(a.L);
     a.padded = c.mode == EP_MODE_LL;
     a.C = c.slots_per_subregion ? c.slots_per_subregion : c.max_tokens_per_rank;
     a.C_rank = c.max_tokens_per_rank;
@@ -1080,7 +1082,7 @@ ep_result_t ep_layout_static(const ep_group_config_t* cfg, const ep_tensor_t* to
     a.rank_offset = out->rank_offset; a.totals = out->totals;
     a.slot = out->slot; a.dst_row = out->dst_row; a.rank_row = out->rank_row; a.entry_rank = out->entry_rank;
     a.sorted_token = out->sorted_token; a.sorted_k = out->sorted_k; a.sorted_row = out->sorted_row;
-    a.walk = nullptr; a.walk_group = 1; a.walk_waves = 0; a.drop_hint = nullptr; a.quant_out = nullptr; a.quant_pitch = 0;
+    a.walk = nullptr; a.walk_group = 1; a.drop_hint = nullptr; a.quant_out = nullptr; a.quant_pitch = 0;
     a.warm_x = nullptr; a.warm_stride = 0; a.warm_rows = 0; a.warm_units = c.hidden / 8; a.nchunks = 1;
     a.rows_cap = -1; a.recv_count = nullptr;
     return launch_layout(a, (hipStream_t)stream) == hipSuccess ? EP_SUCCESS : EP_ERR_HIP;

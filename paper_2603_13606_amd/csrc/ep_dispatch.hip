@@ -376,7 +376,7 @@ static bool plan_rows(int T, int K, int H, int units, int slices, int E, int R, 
     const int chunk_entries = passes * kWave;
     const int64_t l2_tokens = (2ll << 20) / std::max(16 * units / slices, 1);
     const int64_t most = std::max<int64_t>(768, l2_tokens * K);
-    d.group = plan_walk(E, R, (int)std::min<int64_t>(std::max<int64_t>(1, most / chunk_entries), kMaxWaveChunks), &d.waves);
+    d.group = plan_walk(E, R, passes, (int)std::min<int64_t>(std::max<int64_t>(1, most / chunk_entries), kMaxWaveChunks));
     d.blocks = (nwc + d.group - 1) / d.group;
     d.piece = (units + slices - 1) / slices;
     if (d.piece >= 8) d.piece = (d.piece + 7) / 8 * 8;  // whole 128-byte lines per slice (the last slices get less)

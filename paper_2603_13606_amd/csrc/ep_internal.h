@@ -33,6 +33,7 @@ struct LayoutArgs {
     int T, K, E, R, L;
     int L_shift;              // log2(L) if L is a power of two, else -1
     int K_shift;              // log2(K) if K is a power of two, else -1
+    uint32_t K_magic, L_magic;  // else: i / K = (i * magic >> 32) >> floor(log2 K), see divide_magic
     int padded;               // 1 = [E, C, H] layout
     int C;                    // slots per (expert, source) sub-region
     int C_rank;               // staging slots per destination rank in padded mode
@@ -71,7 +72,6 @@ struct LayoutArgs {
     int2* walk;               // or nullptr: {token, row} of every entry that has a row, block of walk_group wave-chunks
                               // by block, within a block expert by expert, within an expert in entry order, no gaps
     int walk_group;           // a multiple or a divisor of walk_waves
-    int walk_waves;           // wavefronts per workgroup of a layout that makes a walk list
 };
 
 // Addressing of the receive windows: element offset of logical row r is
@@ -259,13 +259,19 @@ hipError_t launch_calibration_fill(void* dst, size_t bytes, hipStream_t s);
 hipError_t launch_calibration_read(const void* src, size_t bytes, uint32_t* sink, hipStream_t s);
 
 // Host-side planning helpers (pure functions, testable without a GPU).
+// m = ceil(2^(32 + s) / d), s = floor(log2 d), for d no power of two: i / d == (i * m >> 32) >> s for i < 2^31.  m * d exceeds
+// 2^(32 + s) by less than d <= 2^(s + 1), so i * m / 2^(32 + s) exceeds i / d by less than 1 / d.
+constexpr uint32_t divide_magic(int d) {
+    int s = 0;
+    while ((2 << s) <= d) ++s;
+    return (d & (d - 1)) == 0 ? 0u : (uint32_t)(((uint64_t(1) << (32 + s)) + d - 1) / d);
+}
 void plan_layout(int n, int* passes, int* nwc);
 
 // How launch_dispatch walks an input (see ep_dispatch.hip).
 struct DispatchPlan {
     int run_order;          // 1: destination order; 0: token order (nothing else is set then)
     int group;              // wave-chunks of the layout per block
-    int waves;              // wavefronts per workgroup of the layout
     int blocks;             // blocks of the input
     int block_entries;      // routed entries per block
     int splits;             // workgroups that a run of average length -- the entries of one expert in one block -- takes
@@ -278,9 +284,8 @@ struct DispatchPlan {
 bool plan_dispatch(int T, int K, int H, int E, int R, int order, bool have_walk, int prefetched_rows, DispatchPlan* out);
 // The same for FP8 rows copied from a staging copy (destination order).
 bool plan_dispatch_fp8_staged(int T, int K, int H, int E, int R, bool have_walk, DispatchPlan* out);
-// How a layout that makes a walk list in blocks of up to `most` wave-chunks is cut: returns the wave-chunks per block,
-// and in *waves the wavefronts per workgroup.
-int plan_walk(int E, int R, int most, int* waves);
+// Wave-chunks per block of a walk list with blocks of up to `most` wave-chunks of `passes` passes.
+int plan_walk(int E, int R, int passes, int most);
 constexpr int kWalkPad = 32;  // entries behind the list that a copy may read (and does not use)
 // True when launch_layout reads LayoutArgs::warm_x for this plan.
 bool layout_prefetches(const LayoutArgs& a);

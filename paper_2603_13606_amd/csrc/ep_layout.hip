@@ -10,23 +10,23 @@
 // to 16 wavefronts, and every chunk into wave-chunks of 64*passes consecutive entries,
 // one per wavefront.  ONE launch (Sec. IV-C "Token Count": the count runs next to the
 // send, not as a phase of its own):
-//   histogram   every wave histograms its wave-chunk -- bins: E experts, masked,
-//               invalid, R destination ranks -- with LDS integer atomics;
-//   publish     one thread per bin sums the wave histograms of the chunk and stores
+//   rows        a pass of a wave is a row of 64 entries; per row and bin -- E experts, masked,
+//               invalid, R destination ranks -- a 64-bit word of LDS gets the bits of the lanes
+//               that hold the bin: the lower bits of an entry's word are its rank in the row.
+//               (Large inputs and tables: a histogram per wave, and ballots, see layout_chunk.)
+//   publish     one thread per bin sums the row counts of the chunk and stores
 //               the sum, tagged with the number of this launch, to global memory;
-//   in-chunk    meanwhile every wave ranks its entries inside the chunk: prefix of the
-//   ranks       bin over the earlier waves + number of lower lanes holding the same
-//               key, found with one ballot per key bit;
 //   look across one thread per bin reads that bin's sums of ALL chunks (it waits, a
 //               bounded number of polls, until each carries this launch's tag): entries
 //               in earlier chunks (the prefix) and in all chunks (the totals, hence
 //               the expert offsets).  Only sums of counts cross between workgroups,
 //               so the result does not depend on which chunk is published first;
-//   scan        one exclusive scan of the totals over all bins by the whole workgroup;
-//   emit        slot = prefix of earlier chunks + in-chunk rank, the destination row
-//               and the expert-sorted entry list.
+//   scan        one exclusive scan of the totals over all bins by one wavefront, and one per
+//               block of the walk list by others;
+//   emit        slot = prefix of earlier chunks + in-chunk rank, the destination row,
+//               the expert-sorted entry list and the walk list.
 // The chunks wait for each other, so all of them must be resident at the same time:
-// there are at most 256 of them (32 with the usual bin counts), no more than the part
+// there are at most 256 of them (64 when entries go by rows), no more than the part
 // has compute units, they are the lowest workgroup ids of the launch, and every
 // wait gives up after a fixed number of polls (status bit, never a hang).
 // The work is latency bound (a chain of dependent LDS and global round trips per
@@ -80,11 +80,6 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
     return v;
 }
 
-__device__ __forceinline__ int wave_sum(int v) {
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
-}
-
 __device__ __forceinline__ int wave_max(int v) {
     for (int off = kWave / 2; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, kWave));
     return v;
@@ -103,11 +98,11 @@ __device__ __forceinline__ uint64_t match_key(int key, bool valid, int nbits) {
 
 // Token index of flattened entry i (i / K), with a shift when K is a power of two.
 __device__ __forceinline__ int token_of(const LayoutArgs& a, int i) {
-    return a.K_shift >= 0 ? (i >> a.K_shift) : (i / a.K);
+    return a.K_shift >= 0 ? (i >> a.K_shift) : (int)(__umulhi((uint32_t)i, a.K_magic) >> (31 - __builtin_clz(a.K)));
 }
 
 __device__ __forceinline__ int owner_of(const LayoutArgs& a, int e) {
-    return a.L_shift >= 0 ? (e >> a.L_shift) : (e / a.L);
+    return a.L_shift >= 0 ? (e >> a.L_shift) : (int)(__umulhi((uint32_t)e, a.L_magic) >> (31 - __builtin_clz(a.L)));
 }
 
 struct Entry {
@@ -119,9 +114,9 @@ struct Entry {
     bool lead;     // first k of its token that names destination rank d
 };
 
-// LDS carve-up shared by the kernels.  wh .. flag are contiguous.
+// LDS carve-up shared by the kernels: the per-wave or per-pass tables, then
 struct Lds {
-    int32_t *wh;      // [nw+1][W] per-wave histograms, later "entries of the bin in the earlier waves of the
+    int32_t *wh;      // layout_chunk: [nw+1][W] per-wave histograms, later "entries of the bin in the earlier waves of the
                       //     chunk"; row nw stands in for the rows a smaller workgroup does not have, so that
                       //     sweeps over kLayoutWavesPerBlock rows need no branch: it reads as 0 and is never used
     int32_t *tot;     // [W] totals over the whole input
@@ -129,7 +124,7 @@ struct Lds {
                       //     e in the expert-sorted list (S[E] = routed entries), and its first row in the
                       //     concatenated layout unless the caller gave the first rows; the rank bins are the
                       //     last R bins: for compact staging windows rank_offset[d] = S[E+2+d] - S[E+2]
-    int32_t *before;  // [W] entries of each bin in earlier chunks
+    int32_t *before;  // [W] entries of each bin in earlier chunks (several chunks only)
     int32_t *flag;    // [1] set when a thread of the workgroup gave up waiting for another chunk
     // with a walk list only
     int32_t *first;   // [kLayoutWavesPerBlock] where each block of the chunk starts in the list
@@ -138,10 +133,10 @@ struct Lds {
     int32_t *walk;    // [blocks of the chunk][E] place of an entry in the list, less its slot and the block's start
 };
 
-__device__ __forceinline__ Lds carve_lds(int32_t* base, const LayoutArgs& a, int nw) {
+__device__ __forceinline__ Lds carve_lds(int32_t* base, const LayoutArgs& a, int tables) {
     Lds l;
     l.wh = base;
-    l.tot = l.wh + (nw + 1) * a.W;
+    l.tot = l.wh + tables;
     l.S = l.tot + a.W;
     l.before = l.S + a.W;
     l.flag = l.before + a.W;
@@ -152,13 +147,40 @@ __device__ __forceinline__ Lds carve_lds(int32_t* base, const LayoutArgs& a, int
     return l;
 }
 
-constexpr int lds_ints(int W, int nw) { return (nw + 1) * W + 3 * W + 1; }
+// Row-by-row layouts (layout_rows): a workgroup of 16 / passes wavefronts has 16 rows of 64 entries, and LDS holds one 64-bit
+// word per row and bin.  Rows start on 16-byte boundaries.
+constexpr int kRows = 16;
+__host__ __device__ constexpr int row_words(int W) { return (W + 1) & ~1; }
 
+constexpr int lds_ints(int W, int nw) { return (nw + 1) * W + 3 * W + 1; }
+constexpr int rows_lds_ints(int W) { return 2 * kRows * row_words(W) + 3 * W + 1; }
 // What the walk list adds, with blocks of `group` wave-chunks.
 constexpr int walk_lds_ints(int E, int nw, int group) { return kLayoutWavesPerBlock + (2 + (nw > group ? nw / group : 1)) * E; }
 
-size_t lds_bytes(const LayoutArgs& a, int nw) {
-    return sizeof(int32_t) * (size_t)(lds_ints(a.W, nw) + (a.walk ? walk_lds_ints(a.E, nw, a.walk_group) : 0));
+// How a layout is cut into workgroups, and what LDS they take.
+struct LayoutCut {
+    bool rows;    // layout_rows
+    int waves;    // wavefronts per workgroup
+    size_t lds;   // bytes
+};
+
+constexpr size_t kLdsLimit = 64 * 1024;   // of layout_chunk
+constexpr size_t kLdsUnit = 160 * 1024;   // of a compute unit: what a workgroup of layout_rows may take
+
+// group: wave-chunks per block of the walk list, 0 without one.  A wave keeps its entries in registers for up to PU passes;
+// the tables of 1024 experts on up to 128 ranks fit.
+LayoutCut cut_layout(int E, int R, int passes, int group) {
+    const int W = E + 2 + R;
+    LayoutCut c;
+    c.rows = true;
+    c.waves = kRows / std::min(passes, PU);
+    c.lds = sizeof(int32_t) * (size_t)(rows_lds_ints(W) + (group ? walk_lds_ints(E, c.waves, group) : 0));
+    if (passes <= PU && c.lds <= kLdsUnit) return c;
+    c.rows = false;
+    for (c.waves = kLayoutWavesPerBlock;; c.waves >>= 1) {  // fewer waves when the bin tables are large
+        c.lds = sizeof(int32_t) * (size_t)(lds_ints(W, c.waves) + (group ? walk_lds_ints(E, c.waves, group) : 0));
+        if (c.lds <= kLdsLimit || c.waves == 1) return c;
+    }
 }
 
 // Marks the entries that are the first of their token to name their destination
@@ -166,7 +188,32 @@ size_t lds_bytes(const LayoutArgs& a, int nw) {
 // rank with the ranks held by lanes l-1 .. l-k (one shift of the wave per step); only
 // when a token began before lane 0 are its earlier entries read from memory.
 // Must be called by all 64 lanes.
+//
+// With K a power of two up to 16 tokens do not straddle the rows of 16 lanes: key ^ (key of lane l-j), j < K, by shifts
+// inside the row, is 0 for an earlier entry of the same token and rank (two instructions per step where the
+// general walk takes five).  Lanes shifted in from outside the row read 0, which is no key.
+template <int K>
+__device__ __forceinline__ uint32_t closest_key(uint32_t key) {
+    uint32_t m = ~0u;
+#define EP_STEP(j) if (j < K) m = min(m, key ^ (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, kDppRowShr + j, 0xf, 0xf, true));
+    EP_STEP(1) EP_STEP(2) EP_STEP(3) EP_STEP(4) EP_STEP(5) EP_STEP(6) EP_STEP(7) EP_STEP(8)
+    EP_STEP(9) EP_STEP(10) EP_STEP(11) EP_STEP(12) EP_STEP(13) EP_STEP(14) EP_STEP(15)
+#undef EP_STEP
+    return m;
+}
+
 __device__ __forceinline__ void mark_leaders(const LayoutArgs& a, Entry& en, int lane) {
+    if (a.K_shift >= 0 && a.K_shift <= 4) {  // uniform
+        // token of the row of lanes (at most 16), rank; no two lanes without a rank share a key
+        const uint32_t key = 0x40000000u | ((uint32_t)(lane >> a.K_shift) << 16) | (uint32_t)(en.ok ? en.d : 0x8000 + lane);
+        uint32_t m = ~0u;
+        if (a.K_shift == 1) m = closest_key<2>(key);
+        else if (a.K_shift == 2) m = closest_key<4>(key);
+        else if (a.K_shift == 3) m = closest_key<8>(key);
+        else if (a.K_shift == 4) m = closest_key<16>(key);
+        en.lead = en.ok && m != 0;
+        return;
+    }
     const int dkey = en.ok ? en.d : -1;
     bool lead = en.ok;
     int prev = dkey;
@@ -184,11 +231,12 @@ __device__ __forceinline__ void mark_leaders(const LayoutArgs& a, Entry& en, int
     en.lead = lead;
 }
 
-// Issues the global loads of the ids of passes p0 .. p0+PU-1 of wave-chunk wc
+// Issues the global loads of the ids of passes p0 .. p0+N-1 of wave-chunk wc
 // (nothing waits on them here).
-__device__ __forceinline__ void issue_group(const LayoutArgs& a, int wc, int p0, int lane, int (&raw)[PU]) {
+template <int N>
+__device__ __forceinline__ void issue_group(const LayoutArgs& a, int wc, int p0, int lane, int (&raw)[N]) {
 #pragma unroll
-    for (int j = 0; j < PU; ++j) {
+    for (int j = 0; j < N; ++j) {
         const int p = p0 + j;
         const int i = (wc * a.passes + p) * kWave + lane;
         raw[j] = 0;
@@ -200,10 +248,11 @@ __device__ __forceinline__ void issue_group(const LayoutArgs& a, int wc, int p0,
 }
 
 // Classifies the ids loaded by issue_group.  Must be called by all 64 lanes.
+template <int N>
 __device__ __forceinline__ void classify_group(const LayoutArgs& a, int wc, int p0, int lane,
-                                               const int (&raw)[PU], Entry (&en)[PU]) {
+                                               const int (&raw)[N], Entry (&en)[N]) {
 #pragma unroll
-    for (int j = 0; j < PU; ++j) {
+    for (int j = 0; j < N; ++j) {
         Entry& x = en[j];
         const int p = p0 + j;
         const int i = (wc * a.passes + p) * kWave + lane;
@@ -254,32 +303,36 @@ __device__ __forceinline__ int first_slot(const LayoutArgs& a, const Lds& l, int
     return end - l.S[a.E + 2];
 }
 
+// p[i] = v for arrays of less than 2^30 words: a 32-bit offset goes into the store instruction, a 64-bit index
+// takes four more to add up.
+__device__ __forceinline__ void put(int32_t* p, int i, int32_t v) { *(int32_t*)((uint8_t*)p + ((uint32_t)i << 2)) = v; }
+
 // Writes what the layout records for one entry, given its rank inside the chunk among the
 // entries of its expert and (for a leader) among the tokens of its destination rank; the
 // entries of earlier chunks (l.before) turn the ranks into slots.
 // walk: the places of the wave's block, walk_base: where the block starts in the walk list.
-template <bool WALK>
+template <bool MULTI, bool WALK>
 __device__ __forceinline__ void emit_entry(const LayoutArgs& a, const Entry& x, int slot, int rslot, const Lds& l,
                                            const int32_t* walk, int walk_base) {
     int row = -1, rrow = -1;
     if (x.ok) {
-        slot += l.before[x.e];
+        if (MULTI) slot += l.before[x.e];
         if (a.padded) row = slot < a.C ? x.e * a.C + slot : -1;
         else row = first_row(a, l, x.e) + slot;
         if (a.sorted_token) {
             const int pos = l.S[x.e] + slot;
-            a.sorted_token[pos] = x.t;
-            a.sorted_k[pos] = x.k;
-            a.sorted_row[pos] = row;
+            put(a.sorted_token, pos, x.t);
+            put(a.sorted_k, pos, x.k);
+            put(a.sorted_row, pos, row);
         }
         if (WALK && row >= 0) a.walk[walk_base + walk[x.e] + slot] = make_int2(x.t, row);
     }
-    if (x.lead) rrow = first_slot(a, l, x.d) + l.before[a.E + 2 + x.d] + rslot;
+    if (x.lead) rrow = first_slot(a, l, x.d) + (MULTI ? l.before[a.E + 2 + x.d] : 0) + rslot;
     if (x.i >= 0) {
-        if (a.slot) a.slot[x.i] = slot;
-        a.dst_row[x.i] = row;
-        if (a.rank_row) a.rank_row[x.i] = rrow;
-        if (a.entry_rank) a.entry_rank[x.i] = x.ok ? x.d : -1;
+        if (a.slot) put(a.slot, x.i, slot);
+        put(a.dst_row, x.i, row);
+        if (a.rank_row) put(a.rank_row, x.i, rrow);
+        if (a.entry_rank) put(a.entry_rank, x.i, x.ok ? x.d : -1);
     }
 }
 
@@ -328,12 +381,12 @@ __device__ __forceinline__ void place_group(const LayoutArgs& a, const Entry (&e
     }
 }
 
-template <bool WALK>
-__device__ __forceinline__ void emit_group(const LayoutArgs& a, const Entry (&en)[PU], int p0, const int (&slot)[PU],
-                                           const int (&rslot)[PU], const Lds& l, const int32_t* walk, int walk_base) {
+template <bool MULTI, bool WALK, int N>
+__device__ __forceinline__ void emit_group(const LayoutArgs& a, const Entry (&en)[N], int p0, const int (&slot)[N],
+                                           const int (&rslot)[N], const Lds& l, const int32_t* walk, int walk_base) {
 #pragma unroll
-    for (int j = 0; j < PU; ++j)  // wave-uniform condition
-        if (p0 + j < a.passes) emit_entry<WALK>(a, en[j], slot[j], rslot[j], l, walk, walk_base);
+    for (int j = 0; j < N; ++j)  // wave-uniform condition
+        if (p0 + j < a.passes) emit_entry<MULTI, WALK>(a, en[j], slot[j], rslot[j], l, walk, walk_base);
 }
 
 // The scans over the bins are done by one wavefront each, while the others wait: done by all 16, every wave adds up the
@@ -364,13 +417,12 @@ __device__ void scan_totals(const LayoutArgs& a, const Lds& l, int lane) {
 // l.walk[sb][e] + slot is the place, counted from the start of the block, of the entry of expert e with that slot;
 // l.first[sb] is where the block starts: the rows of all earlier blocks.  A row count of an expert is its entry count
 // cut at the capacity.
-template <bool ONE_GROUP>
-__device__ void scan_walk(const LayoutArgs& a, const Lds& l, int sb, int nsub, int lane) {
+// before0: of block 0's first wave, the entries of every bin in the waves of the chunk before it, a word every `step`,
+// then the next waves' at `pitch`.
+__device__ void scan_walk(const LayoutArgs& a, const Lds& l, const int32_t* before0, int pitch, int step, int sb, int nsub, int lane) {
     const int E = a.E, cap = a.padded ? a.C : 0x7fffffff;
-    // the wave histograms hold, per bin, the entries of the chunk before a wave, or, once a single load group has been
-    // placed, those up to and including it
-    const int32_t* lo = l.wh + (sb * a.walk_group - (ONE_GROUP ? 1 : 0)) * a.W;
-    const int32_t* hi = lo + a.walk_group * a.W;
+    const int32_t* lo = before0 + sb * a.walk_group * pitch;
+    const int32_t* hi = lo + a.walk_group * pitch;
     int base = 0, carry = 0;
     for (int c0 = 0; c0 < E; c0 += kScanRows * kWave) {
         int start[kScanRows], rows[kScanRows];
@@ -380,8 +432,8 @@ __device__ void scan_walk(const LayoutArgs& a, const Lds& l, int sb, int nsub, i
             start[r] = rows[r] = 0;
             if (c < E) {
                 const int bstart = l.bstart[c];
-                start[r] = bstart + (sb == 0 ? 0 : lo[c]);
-                rows[r] = bstart + (sb == nsub - 1 ? l.bcount[c] : hi[c]);
+                start[r] = bstart + (sb == 0 ? 0 : lo[c * step]);
+                rows[r] = bstart + (sb == nsub - 1 ? l.bcount[c] : hi[c * step]);
             }
         }
 #pragma unroll
@@ -398,21 +450,25 @@ __device__ void scan_walk(const LayoutArgs& a, const Lds& l, int sb, int nsub, i
 }
 
 // The per-expert / per-rank arrays and the totals block (all but the status word) in
-// global memory, from tot and S in LDS.  By every thread of one workgroup.  Returns one past
-// the highest destination row (in wave 0; other waves get 0).
-__device__ int write_tables(const LayoutArgs& a, const Lds& l, int tid, int lane, int w) {
+// global memory, from tot and S in LDS.  By every thread of one workgroup: the experts, the ranks and the sums
+// over all experts fall to different waves, which have their share of other work too (by wave 0 alone, one after the
+// other, this was the last 1.4 us of a small layout).  STATUS: the status word too (there is one chunk; the caller of a
+// fused launch says how many rows its output takes).
+template <bool STATUS>
+__device__ __forceinline__ void write_tables(const LayoutArgs& a, const Lds& l, int tid, int lane, int w) {
     const int32_t* tot = l.tot;
     const int32_t* S = l.S;
-    const int E = a.E, R = a.R;
-    for (int e = tid; e < E; e += blockDim.x) {
+    const int E = a.E, R = a.R, threads = blockDim.x;  // a power of two
+    for (int e = (tid + threads / 2) & (threads - 1); e < E; e += threads) {
         const int v = tot[e];
+        const int kept = a.padded ? min(v, a.C) : v;
         a.expert_count[e] = v;
-        a.expert_kept[e] = a.padded ? min(v, a.C) : v;
-        if (a.recv_count) a.recv_count[e] = a.padded ? min(v, a.C) : v;
+        a.expert_kept[e] = kept;
+        if (a.recv_count) a.recv_count[e] = kept;
         a.expert_offset[e] = first_row(a, l, e);
     }
     if (a.rank_pair_count) {
-        for (int d = tid; d <= R; d += blockDim.x) {
+        for (int d = (tid + threads / 4) & (threads - 1); d <= R; d += threads) {
             if (d < R) {
                 a.rank_pair_count[d] = S[(d + 1) * a.L] - S[d * a.L];
                 a.rank_token_count[d] = tot[E + 2 + d];
@@ -420,33 +476,34 @@ __device__ int write_tables(const LayoutArgs& a, const Lds& l, int tid, int lane
             a.rank_offset[d] = first_slot(a, l, d);
         }
     }
-    if (w != 0) return 0;
-    // wave 0: the sums over all experts
-    int kept = 0, dropped = 0, rend = 0;
-    for (int e = lane; e < E; e += kWave) {
-        const int v = tot[e];
-        const int k = a.padded ? min(v, a.C) : v;
-        kept += k;
-        dropped += v - k;
-        if (!a.padded && a.expert_base && v > 0) rend = max(rend, a.expert_base[e] + v);
-    }
-    kept = wave_sum(kept);
-    dropped = wave_sum(dropped);
-    rend = wave_max(rend);
+    if (w != threads / kWave - 1) return;
     const int total_e = S[E];
+    int kept = total_e, rend = 0;
+    if (a.padded) {
+        kept = 0;
+#pragma unroll 4
+        for (int e = lane; e < E; e += kWave) kept += min(tot[e], a.C);
+        kept = __builtin_amdgcn_readlane(wave_inclusive_scan(kept), kWave - 1);
+    } else if (a.expert_base) {
+        for (int e = lane; e < E; e += kWave)
+            if (tot[e] > 0) rend = max(rend, a.expert_base[e] + tot[e]);
+        rend = wave_max(rend);
+    }
     const int rows_end = a.padded ? E * a.C : (a.expert_base ? rend : total_e);
     if (lane == 0) {
         a.expert_offset[E] = rows_end;
         a.totals[TOT_KEPT] = kept;
-        a.totals[TOT_DROPPED] = dropped;
+        a.totals[TOT_DROPPED] = total_e - kept;
         a.totals[TOT_MASKED] = tot[E];
         a.totals[TOT_INVALID] = tot[E + 1];
         a.totals[TOT_SORTED] = total_e;
         a.totals[TOT_MSGS] = S[a.W - 1] + tot[a.W - 1] - S[E + 2];  // the rank bins are the last R bins
         a.totals[TOT_ROWS_END] = rows_end;
-        if (a.drop_hint) *a.drop_hint = (int64_t)kept | ((int64_t)dropped << 32);
+        if (a.drop_hint) *a.drop_hint = (int64_t)kept | ((int64_t)(total_e - kept) << 32);
+        if (STATUS)
+            a.totals[TOT_STATUS] = (tot[E + 1] ? STATUS_INVALID_IDS : 0) | (kept < total_e ? STATUS_CAPACITY_DROP : 0) |
+                                   (!a.padded && a.rows_cap >= 0 && rows_end > a.rows_cap ? STATUS_OUTPUT_OVERFLOW : 0);
     }
-    return rows_end;
 }
 
 // One past the highest destination row of the concatenated layout.  One wavefront; must be called
@@ -535,10 +592,7 @@ __device__ __forceinline__ void look_across(const LayoutArgs& a, int c, int r0, 
 // which no launch uses as a tag.
 //
 // HB: chunks whose published words a thread loads in one batch (at most 32: bit masks), 0 = there
-// is one chunk.  FUSED: the launch also dispatches (apart, so that the code of the
-// plain launch does not change with it: with the check of the output in both, the prefill step was
-// 1.5 us of 185 slower on two boxes of three).  ONE_GROUP: a wave's entries fit one load group
-// (at most PU passes) and stay in registers from the histogram to the emit.
+// is one chunk.  FUSED: the launch also dispatches.
 // The same workgroups, for a group that quantises ahead: instead of only reading the token
 // rows they quantise them (the FP8 dispatch's format, see ep_fp8.h) into a staging copy, row t
 // at quant_out + t * quant_pitch: H bytes of codes, then H/128 float scales.  The quantising
@@ -564,10 +618,205 @@ __device__ void quantize_tokens(const LayoutArgs& a, int wb, int nwb) {
     }
 }
 
-template <int HB, bool ONE_GROUP, bool FUSED, bool WALK>
+// (A) per bin: entries in earlier chunks and in all chunks, into LDS (and of the block of the walk list).  A batch of words is
+//     polled as a whole until every word of it carries this launch's tag (rows beyond the last
+//     chunk repeat its words, and the chunk's own word is among them: no exceptions to
+//     test for).  Which words of a batch count, and which belong to earlier chunks, are
+//     wave-uniform bit masks.
+template <int HB, bool WALK>
+__device__ __forceinline__ void gather_chunks(const LayoutArgs& a, const Lds& l, int b, int waves, uint32_t tag) {
+    const int nchunks = a.nchunks, W = a.W, tid = threadIdx.x;
+    const int gchunks = WALK ? max(a.walk_group / waves, 1) : 1, g0 = WALK ? b / gchunks * gchunks : 0;  // of its block
+    int rounds = 0;  // of this thread, over all its batches
+    bool gave_up = false;
+    for (int c = tid; c < W; c += blockDim.x) {
+        int before = 0, total = 0, bstart = 0, bcount = 0;
+        for (int r0 = 0; r0 < nchunks; r0 += HB) {
+            uint32_t hv[HB];
+            for (;;) {
+                look_across(a, c, r0, hv);
+                bool all = true;
+#pragma unroll
+                for (int j = 0; j < HB; ++j) all = all && (hv[j] >> kTagShift) == tag;
+                if (all) break;
+                if (++rounds >= kLookLimit) {  // a chunk never published: flag it (the counts are then undefined)
+                    gave_up = true;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+            auto up_to = [&](int chunk) {  // the chunks of the batch that come before this one
+                const int m = min(max(chunk - r0, 0), HB);
+                return m >= 32 ? ~0u : (1u << m) - 1u;
+            };
+            const uint32_t valid = up_to(nchunks), earlier = up_to(b);
+            const uint32_t blk_earlier = WALK ? up_to(g0) : 0u, blk = WALK ? up_to(g0 + gchunks) & ~blk_earlier : 0u;
+#pragma unroll
+            for (int j = 0; j < HB; ++j) {
+                const uint32_t cnt = hv[j] & kCountMask & (0u - ((valid >> j) & 1u));
+                total += (int)cnt;
+                before += (int)(cnt & (0u - ((earlier >> j) & 1u)));
+                if (WALK) bstart += (int)(cnt & (0u - ((blk_earlier >> j) & 1u)));
+                if (WALK) bcount += (int)(cnt & (0u - ((blk >> j) & 1u)));
+            }
+        }
+        if (WALK && c < a.E) {
+            l.bstart[c] = bstart;
+            l.bcount[c] = bcount;
+        }
+        l.tot[c] = total;  // the chunk's own sum is one of the words
+        l.before[c] = before;
+    }
+    if (gave_up) atomicOr(l.flag, 1);
+}
+
+constexpr uint32_t kGaveUp = 1u << 16;  // of ctl[1]: the low 16 bits count workgroups, the rest flags a time-out
+
+// (B) with several chunks: thread 0 reports for the workgroup; the value it gets back tells wave 0 whether this
+//     workgroup is the last to have looked across (then every chunk is done with pub and ctl,
+//     and it may advance the generation) and whether any workgroup gave up waiting.
+__device__ __forceinline__ uint32_t report_chunk(const LayoutArgs& a, const Lds& l) {
+    uint32_t seen = 0;
+    const uint32_t mine = 1u + (*l.flag ? kGaveUp : 0u);
+    if (threadIdx.x == 0)
+        seen = __hip_atomic_fetch_add(&a.ctl[1], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
+    return seen;
+}
+
+// (C) wave 0 of the last workgroup to have reported (lane 0 holds `seen`): the status word, and the cross-workgroup words
+//     made ready for the next launch.  All 64 lanes.
+template <bool FUSED>
+__device__ __forceinline__ void finish_chunks(const LayoutArgs& a, const Lds& l, int lane, uint32_t seen_lane0, uint32_t gen) {
+    const uint32_t seen = __builtin_amdgcn_readfirstlane(seen_lane0);
+    if ((int)(seen & (kGaveUp - 1u)) != a.nchunks + 1) return;  // the chunks and the workgroup of the tables
+    int extra = seen >= kGaveUp ? STATUS_TIMEOUT : 0;
+    if (FUSED && !a.padded && last_row_end(a, l, lane) > a.rows_cap) extra |= STATUS_OUTPUT_OVERFLOW;
+    write_status(a, l, lane, extra);
+    uint32_t next = gen + 1u;
+    if (next >= kTags) {  // the tags have run out: clear every published word and start over
+        for (int64_t j = lane; j < (int64_t)kMaxChunks * a.W; j += kWave) a.pub[j] = 0u;
+        next = 0u;
+    }
+    if (lane == 0) {
+        __hip_atomic_store(&a.ctl[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&a.ctl[0], next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// The scans over the bins, between two barriers: the totals by wave 0, the blocks of the walk list by the others
+// (the workgroup of the tables has none).
+template <bool WALK>
+__device__ __forceinline__ void scan_bins(const LayoutArgs& a, const Lds& l, int b, int w, int waves, int nsub, const int32_t* before0,
+                                          int pitch, int step, int lane) {
+    lds_barrier();
+    if (w == 0) scan_totals(a, l, lane);
+    else if (WALK && b < a.nchunks) {
+        for (int sb = w - 1; sb < nsub; sb += waves - 1) scan_walk(a, l, before0, pitch, step, sb, nsub, lane);
+    }
+    lds_barrier();
+}
+
+// One workgroup's share of a layout of at most PASSES = PU passes per wavefront (64 K entries), whose entries stay in
+// registers: 16 rows of 64 entries, row = a pass of a wave.  The standing of an entry among those of its row with the same bin
+// comes from a word of LDS per row and bin in which every entry sets the bit of its lane (an OR: no order is
+// decided), and so does the row's count of the bin: 16 waves share the four instruction streams of a compute unit, so what
+// bounds a small layout is instructions per wave, and ballots over the bits of the keys, with histograms beside them,
+// take several times as many (744 entries of 256 experts in one workgroup: 6.4 us from its first instruction to its last, now
+// 3.4; 18 006 entries of 96 experts: 9.3 us, now 7.1).
+template <int HB, int PASSES, bool FUSED, bool WALK>
+__device__ __forceinline__ void layout_rows(const LayoutArgs& a, int32_t* lds, const int b) {
+    constexpr int waves = kRows / PASSES;
+    constexpr bool multi = HB > 0;
+    const int W = a.W, Wr = row_words(W);
+    const Lds l = carve_lds(lds, a, 2 * kRows * Wr);
+    const int tid = threadIdx.x, lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wc = b * waves + w;
+    const bool active = wc < a.nwc;
+    uint64_t* rows = (uint64_t*)lds;           // [kRows][Wr]
+    uint64_t* mine = rows + w * PASSES * Wr;   // the rows of this wave
+
+    // the loads of the ids, and meanwhile the clearing of the wave's own rows
+    int raw[PASSES];
+    if (active) issue_group(a, wc, 0, lane, raw);
+    uint32_t gen = 0;
+    if (multi) gen = __hip_atomic_load(&a.ctl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int j = lane; j < PASSES * Wr / 2; j += kWave) ((u32x4*)mine)[j] = (u32x4){0u, 0u, 0u, 0u};
+    if (multi && tid == 0) *l.flag = 0;
+
+    Entry en[PASSES];
+    int sl[PASSES], rsl[PASSES];
+    if (active) {
+        classify_group(a, wc, 0, lane, raw, en);
+        // LDS accesses of one wavefront are performed in program order; the fences keep the compiler to it
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        const uint64_t bit = 1ull << lane;
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            uint64_t* row = mine + p * Wr;
+            const int bin = en[p].ok ? en[p].e : en[p].masked ? a.E : a.E + 1;
+            if (en[p].i >= 0) __hip_atomic_fetch_or(&row[bin], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (en[p].lead) __hip_atomic_fetch_or(&row[a.E + 2 + en[p].d], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const uint64_t* row = mine + p * Wr;
+            sl[p] = (int)__popcll(row[en[p].e] & (bit - 1ull));  // lanes without an expert hold e = 0 and use neither
+            rsl[p] = (int)__popcll(row[a.E + 2 + en[p].d] & (bit - 1ull));
+        }
+    }
+    lds_barrier();
+
+    // per bin (thread = column): the sum of the chunk, which is published at once, and the running sum down the rows,
+    // which takes the place of the bits
+    if (multi) asm volatile("" : "+v"(gen));  // the generation is first looked at here
+    const uint32_t tag = gen + 1u;
+    for (int c = tid; c < W; c += waves * kWave) {
+        uint64_t v[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) v[r] = rows[r * Wr + c];
+        int run = 0;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            *(int32_t*)&rows[r * Wr + c] = run;
+            run += (int)__popcll(v[r]);
+        }
+        if (multi && b < a.nchunks)  // the workgroup after the last chunk has no entries: it only writes the tables
+            __hip_atomic_store(&a.pub[(int64_t)b * W + c], (tag << kTagShift) | (uint32_t)run, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        if (!multi) l.tot[c] = run;
+    }
+    if constexpr (multi) gather_chunks<HB, WALK>(a, l, b, waves, tag);
+    const int nsub = WALK && waves > a.walk_group ? waves / a.walk_group : 1;  // blocks of the walk list in this chunk
+    scan_bins<WALK>(a, l, b, w, waves, nsub, (const int32_t*)rows, 2 * PASSES * Wr, 2, lane);
+    uint32_t seen = 0;
+    if (multi) seen = report_chunk(a, l);
+
+    // slots
+    if (active) {
+        const int sb = nsub > 1 ? w / a.walk_group : 0;  // the block of this wave
+        const int walk_base = WALK ? __builtin_amdgcn_readfirstlane(l.first[sb]) : 0;
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const uint64_t* row = mine + p * Wr;
+            sl[p] = en[p].ok ? sl[p] + *(const int32_t*)&row[en[p].e] : -1;
+            rsl[p] += *(const int32_t*)&row[a.E + 2 + en[p].d];
+        }
+        emit_group<multi, WALK>(a, en, 0, sl, rsl, l, l.walk + sb * a.E, walk_base);
+    }
+    // the tables: with several chunks from a workgroup of their own, number nchunks, which has no entries: it looks across,
+    // scans and writes the tables while the chunks still write theirs
+    if (b == (multi ? a.nchunks : 0)) write_tables<!multi>(a, l, tid, lane, w);
+    if (multi && w == 0) finish_chunks<FUSED>(a, l, lane, seen, gen);
+}
+
+// The same for any number of passes and tables of any size: a wave walks its entries PU passes at a time, twice, with one
+// histogram per wave.
+template <int HB, bool WALK>
 __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, const int b) {
     const int wpb = blockDim.x >> 6;
-    const Lds l = carve_lds(lds, a, wpb);
+    const Lds l = carve_lds(lds, a, (wpb + 1) * a.W);
     const int W = a.W;
     const int tid = threadIdx.x;
     const int lane = lane_id();
@@ -575,7 +824,7 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
     const int wc = b * wpb + w;
     const int nchunks = a.nchunks;
     const bool active = wc < a.nwc;
-    constexpr bool one_group = ONE_GROUP, multi = HB > 0;
+    constexpr bool multi = HB > 0;
 
     // (1) the global loads this workgroup can issue at once: its own ids and the generation
     //     (first needed in (3): nothing here waits for it)
@@ -619,130 +868,35 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
 #pragma unroll
         for (int r = 0; r < kLayoutWavesPerBlock; ++r) l.wh[min(r, wpb) * W + c] = v[r];
     }
-    // (4) ranks inside the chunk; with one load group they are computed here, while the
-    //     other chunks publish, and only then comes the first look across: issued earlier it
-    //     finds some of the other chunks' sums not yet there and has to be repeated, a second
-    //     round trip (measured: 0.6 us per step later, 1.2 us of the kernel in all)
-    InWave iw[PU];
-    if (active && one_group) rank_group(a, en, 0, lane, iw);
-    lds_barrier();
-    int sl[PU], rsl[PU];
-    if (active && one_group) place_group(a, en, iw, 0, l.wh + w * W, sl, rsl);
-    uint32_t hv[HB > 0 ? HB : 1];
-    if constexpr (multi) look_across(a, min(tid, W - 1), 0, hv);
-
-    // (5) per bin: entries in earlier chunks and in all chunks.  A batch of words is polled
-    //     as a whole until every word of it carries this launch's tag (rows beyond the last
-    //     chunk repeat its words, and the chunk's own word is among them: no exceptions to
-    //     test for).  Which words of a batch count, and which belong to earlier chunks, are
-    //     wave-uniform bit masks.
+    // (4) entries of the other chunks, and the scans
+    if constexpr (multi) gather_chunks<HB, WALK>(a, l, b, wpb, tag);
     const int nsub = WALK && wpb > a.walk_group ? wpb / a.walk_group : 1;  // blocks of the walk list in this chunk
-    if constexpr (multi) {
-        const int gchunks = WALK ? max(a.walk_group / wpb, 1) : 1, g0 = WALK ? b / gchunks * gchunks : 0;  // or chunks in its block
-        int rounds = 0;  // of this thread, over all its batches
-        bool gave_up = false;
-        bool have = true;  // hv holds the batch (tid, 0)
-        for (int c = tid; c < W; c += blockDim.x) {
-            int before = 0, total = 0, bstart = 0, bcount = 0;
-            for (int r0 = 0; r0 < nchunks; r0 += HB) {
-                for (;;) {
-                    if (!have) look_across(a, c, r0, hv);
-                    have = false;
-                    bool all = true;
-#pragma unroll
-                    for (int j = 0; j < HB; ++j) all = all && (hv[j] >> kTagShift) == tag;
-                    if (all) break;
-                    if (++rounds >= kLookLimit) {  // a chunk never published: flag it (the counts are then undefined)
-                        gave_up = true;
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                }
-                auto up_to = [&](int chunk) {  // the chunks of the batch that come before this one
-                    const int m = min(max(chunk - r0, 0), HB);
-                    return m >= 32 ? ~0u : (1u << m) - 1u;
-                };
-                const uint32_t valid = up_to(nchunks), earlier = up_to(b);
-                const uint32_t blk_earlier = WALK ? up_to(g0) : 0u, blk = WALK ? up_to(g0 + gchunks) & ~blk_earlier : 0u;
-#pragma unroll
-                for (int j = 0; j < HB; ++j) {
-                    const uint32_t cnt = hv[j] & kCountMask & (0u - ((valid >> j) & 1u));
-                    total += (int)cnt;
-                    before += (int)(cnt & (0u - ((earlier >> j) & 1u)));
-                    if (WALK) bstart += (int)(cnt & (0u - ((blk_earlier >> j) & 1u)));
-                    if (WALK) bcount += (int)(cnt & (0u - ((blk >> j) & 1u)));
-                }
-            }
-            if (WALK && c < a.E) {
-                l.bstart[c] = bstart;
-                l.bcount[c] = bcount;
-            }
-            l.tot[c] = total;  // the chunk's own sum is one of the words
-            l.before[c] = before;
-        }
-        if (gave_up) atomicOr(l.flag, 1);
-    }
-    // (6) the scans over the bins: the totals by wave 0, the walk list by the others (the workgroup of the tables has none)
-    lds_barrier();
-    if (w == 0) scan_totals(a, l, lane);
-    else if (WALK && b < nchunks) {
-        for (int sb = w - 1; sb < nsub; sb += wpb - 1) scan_walk<ONE_GROUP>(a, l, sb, nsub, lane);
-    }
-    lds_barrier();
-    const int sb = nsub > 1 ? w / a.walk_group : 0;  // the block of this wave
-    const int walk_base = WALK ? __builtin_amdgcn_readfirstlane(l.first[sb]) : 0;
-    // thread 0 reports for the workgroup: the value it gets back tells wave 0 whether this
-    // workgroup is the last to have looked across (then every chunk is done with pub and ctl,
-    // and it may advance the generation) and whether any workgroup gave up waiting
-    const int any_gave_up = *l.flag;
-    uint32_t ticket = 0;
-    constexpr uint32_t kGaveUp = 1u << 16;  // low 16 bits count workgroups, the rest flags a time-out
-    const uint32_t mine = 1u + (any_gave_up ? kGaveUp : 0u);
-    if (multi && tid == 0) ticket = __hip_atomic_fetch_add(&a.ctl[1], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    scan_bins<WALK>(a, l, b, w, wpb, nsub, l.wh, W, 1, lane);
+    uint32_t seen = 0;
+    if (multi) seen = report_chunk(a, l);
 
-    // (7) slots
+    // (5) ranks inside the chunk, and slots
     if (active) {
+        const int sb = nsub > 1 ? w / a.walk_group : 0;  // the block of this wave
+        const int walk_base = WALK ? __builtin_amdgcn_readfirstlane(l.first[sb]) : 0;
+        InWave iw[PU];
+        int sl[PU], rsl[PU];
         for (int p0 = 0; p0 < a.passes; p0 += PU) {
-            if (!one_group) {
-                load_group(a, wc, p0, lane, en);
-                rank_group(a, en, p0, lane, iw);
-                place_group(a, en, iw, p0, l.wh + w * W, sl, rsl);
-            }
-            emit_group<WALK>(a, en, p0, sl, rsl, l, l.walk + sb * a.E, walk_base);
+            load_group(a, wc, p0, lane, en);
+            rank_group(a, en, p0, lane, iw);
+            place_group(a, en, iw, p0, l.wh + w * W, sl, rsl);
+            emit_group<multi, WALK>(a, en, p0, sl, rsl, l, l.walk + sb * a.E, walk_base);
         }
     }
-    // (8) the per-expert / per-rank arrays and the totals.  With several chunks they come from a
-    //     workgroup of their own, number nchunks, which has no entries: it looks across, scans
-    //     and writes the tables while the chunks are still walking theirs (written by a chunk
-    //     after its walk they were the last thing the launch waited for).  The status word comes
-    //     from one wavefront: with several chunks wave 0 of the workgroup that finished looking
-    //     across last, which then also leaves the cross-workgroup words ready for the next launch
-    int rows_end = 0;
-    if (b == (multi ? nchunks : 0)) rows_end = write_tables(a, l, tid, lane, w);
-    if (w != 0) return;
-    if (!multi) {  // the caller of a fused launch says how many rows its output takes
-        write_status(a, l, lane, (!a.padded && a.rows_cap >= 0 && rows_end > a.rows_cap) ? STATUS_OUTPUT_OVERFLOW : 0);
-        return;
-    }
-    const uint32_t seen = __builtin_amdgcn_readfirstlane(ticket) + mine;  // lane 0 holds the ticket
-    if ((int)(seen & (kGaveUp - 1u)) != nchunks + 1) return;  // the chunks and the workgroup of the tables
-    int extra = seen >= kGaveUp ? STATUS_TIMEOUT : 0;
-    if (FUSED && !a.padded && last_row_end(a, l, lane) > a.rows_cap) extra |= STATUS_OUTPUT_OVERFLOW;
-    write_status(a, l, lane, extra);
-    uint32_t next = gen + 1u;
-    if (next >= kTags) {  // the tags have run out: clear every published word and start over
-        for (int64_t j = lane; j < (int64_t)kMaxChunks * W; j += kWave) a.pub[j] = 0u;
-        next = 0u;
-    }
-    if (lane == 0) {
-        __hip_atomic_store(&a.ctl[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&a.ctl[0], next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    // (6) the tables, as in layout_rows
+    if (b == (multi ? nchunks : 0)) write_tables<!multi>(a, l, tid, lane, w);
+    if (multi && w == 0) finish_chunks<false>(a, l, lane, seen, gen);
 }
 
-template <bool MULTI, bool ONE_GROUP, bool WALK>
-__global__ __launch_bounds__(1024) void layout_kernel(LayoutArgs a) {
-    extern __shared__ int32_t lds[];
+// PASSES: of layout_rows; 0: layout_chunk.
+template <bool MULTI, int PASSES, bool WALK>
+__global__ __launch_bounds__(1024, MULTI ? 4 : 8) void layout_kernel(LayoutArgs a) {
+    extern __shared__ __align__(16) int32_t lds[];
     const int nlay = a.nchunks + (MULTI ? 1 : 0);  // workgroups that lay out: the chunks and, with several, the one of the tables
     if ((int)blockIdx.x >= nlay) {  // a whole workgroup: no barrier is reached by part of one
         // a short pause first (about 0.4 us): the chunks' loads of their ids then go ahead of the flood of
@@ -752,7 +906,8 @@ __global__ __launch_bounds__(1024) void layout_kernel(LayoutArgs a) {
         else warm_tokens(a, blockIdx.x - nlay, gridDim.x - nlay);
         return;
     }
-    layout_chunk<MULTI ? 32 : 0, ONE_GROUP, false, WALK>(a, lds, blockIdx.x);
+    if constexpr (PASSES > 0) layout_rows<MULTI ? 32 : 0, PASSES, false, WALK>(a, lds, blockIdx.x);
+    else layout_chunk<MULTI ? 32 : 0, WALK>(a, lds, blockIdx.x);
 }
 
 // ---- layout and direct dispatch of a small input in ONE launch (Sec. IV-C: in the
@@ -770,24 +925,23 @@ __global__ __launch_bounds__(1024) void layout_kernel(LayoutArgs a) {
 // ids, same arithmetic as the layout: the rows are those it records.  No copying workgroup
 // waits for another.
 //
-// What bounds it: the id loads, five barriers and the random-placement write rate; the layout, a
-// chain of latencies of about the same length as a short copy, is hidden behind it.
+// What bounds it: the id loads, three barriers and the random-placement write rate; the layout, a
+// chain of latencies of about the same length as a short copy, is hidden behind it.  128 tokens of 14 336 bytes,
+// top-8: 6.2 us (9.1 before the layout went by rows of LDS words), 64 tokens of 512 bytes, top-2: 3.4 (5.8).
 constexpr int kFusedIds = 8;  // ids per thread
 constexpr int kFusedMaxEntries = kFusedIds * kLayoutWavesPerBlock * kWave;
 
-// IDS: ids per thread.  With one, the copying workgroups are about as many as compute units and
-// the registers are not cut to what two workgroups per unit leave each (0.5 us of 7.2).
+// IDS: ids per thread.
 template <int IDS, bool MULTI>
-__global__ __launch_bounds__(1024, IDS == 1 ? 4 : 8) void layout_dispatch_kernel(LayoutArgs a, DispatchArgs d, int nlay, int nseg, int units,
+__global__ __launch_bounds__(1024, 8) void layout_dispatch_kernel(LayoutArgs a, DispatchArgs d, int nlay, int nseg, int units,
                                                                int group, int parts, int spp) {
-    extern __shared__ int32_t lds[];
+    extern __shared__ __align__(16) int32_t lds[];
     if ((int)blockIdx.x < nlay) {
-        layout_chunk<MULTI ? kFusedIds : 0, true, true, false>(a, lds, blockIdx.x);  // at most kFusedIds chunks
+        layout_rows<MULTI ? kFusedIds : 0, 1, true, false>(a, lds, blockIdx.x);  // at most kFusedIds chunks
         return;
     }
     constexpr int threads = kLayoutWavesPerBlock * kWave;
     uint32_t* bins = (uint32_t*)lds;  // [E]
-    int32_t* wsum = lds + a.E;        // [kLayoutWavesPerBlock]
     const int tid = threadIdx.x;
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -830,19 +984,28 @@ __global__ __launch_bounds__(1024, IDS == 1 ? 4 : 8) void layout_dispatch_kernel
         if ((unsigned)id[j] < (unsigned)a.E) atomicAdd(&bins[id[j]], tid + j * threads < first ? 0x10001u : 1u);
     lds_barrier();
     if (!a.padded && !a.expert_base) {  // the first row of every expert: entries that name a lower one
-        const uint32_t word = tid < a.E ? bins[tid] : 0u;
-        const int count = (int)(word & 0xffffu);
-        const int inc = wave_inclusive_scan(count);
-        if (lane == kWave - 1) wsum[w] = inc;
-        lds_barrier();
-        int below = 0;
+        if (w == kLayoutWavesPerBlock - 1) {  // one wave, the one with the fewest segments; the others rank the group's entries
+            int carry = 0;
+            for (int c0 = 0; c0 < a.E; c0 += kScanRows * kWave) {
+                uint32_t word[kScanRows];
 #pragma unroll
-        for (int r = 0; r < kLayoutWavesPerBlock; ++r) below += r < w ? wsum[r] : 0;
-        if (tid < a.E) bins[tid] = (word & 0xffff0000u) | (uint32_t)(below + inc - count);
-        lds_barrier();
+                for (int r = 0; r < kScanRows; ++r) {
+                    const int c = c0 + r * kWave + lane;
+                    word[r] = c < a.E ? bins[c] : 0u;
+                }
+#pragma unroll
+                for (int r = 0; r < kScanRows; ++r) {
+                    const int c = c0 + r * kWave + lane, count = (int)(word[r] & 0xffffu);
+                    const int inc = wave_inclusive_scan(count);
+                    if (c < a.E) bins[c] = (word[r] & 0xffff0000u) | (uint32_t)(carry + inc - count);
+                    carry += __builtin_amdgcn_readlane(inc, kWave - 1);
+                }
+            }
+        }
     }
-    if (w >= items) return;
     const uint64_t peers = match_key(my_e, routed, a.bits_e);
+    if (!a.padded && !a.expert_base) lds_barrier();
+    if (w >= items) return;
     const int in_group = (int)__popcll(peers & ((1ull << lane) - 1ull));
     int my_row = -1;
     int64_t my_off = 0;
@@ -881,8 +1044,6 @@ __global__ __launch_bounds__(1024, IDS == 1 ? 4 : 8) void layout_dispatch_kernel
     }
 }
 
-constexpr size_t kLdsLimit = 64 * 1024;
-
 }  // namespace
 
 // Wave-chunk plan for n entries: 64*passes consecutive entries per wavefront.  Up to
@@ -898,22 +1059,20 @@ void plan_layout(int n, int* passes, int* nwc) {
     *nwc = (n + kWave * p - 1) / (kWave * p);
 }
 
-// A block of the walk list is a whole number of chunks (workgroups of the layout) or a whole part of one; the workgroup
-// is as large as the tables in LDS allow.
-int plan_walk(int E, int R, int most, int* waves) {
-    const int W = E + 2 + R;
-    for (int nw = kLayoutWavesPerBlock;; nw >>= 1) {
-        int group = most / nw * nw;
+// A block of the walk list is a whole number of chunks (workgroups of the layout) or a whole part of one.
+int plan_walk(int E, int R, int passes, int most) {
+    int group = 0;
+    for (int waves = kLayoutWavesPerBlock; waves >= 1; waves >>= 1) {
+        group = most / waves * waves;
         if (group == 0) {
             group = 1;
             while (2 * group <= most) group *= 2;
         }
-        if (nw == 2) group = std::max(group, 2);  // two waves and one block always fit, and 512 wave-chunks allow no fewer
-        if (nw == 2 || sizeof(int32_t) * (size_t)(lds_ints(W, nw) + walk_lds_ints(E, nw, group)) <= kLdsLimit) {
-            *waves = nw;
-            return group;
-        }
+        // two waves and one block always fit, and 512 wave-chunks allow no fewer
+        if (waves == 2) group = std::max(group, 2);
+        if (cut_layout(E, R, passes, group).waves >= waves) break;
     }
+    return group;
 }
 
 // The read-ahead rides on the layout kernel of inputs that are laid out by several workgroups.
@@ -930,13 +1089,14 @@ bool layout_prefetches(const LayoutArgs& a) {
 // 132 MB; top-2 40.2/39.6 at 4096 = 176 MB; top-1 47.4/49.8 at 8192 = 235 MB; 8192 rows of 512 bytes
 // 13.0/9.8).
 constexpr int64_t kFusedMaxBytes = 176ll << 20;
+constexpr int kFusedMaxBins = 818;  // 112 KB of tables, one workgroup per compute unit; not tried beyond
 
 bool layout_dispatch_fusable(const LayoutArgs& a, const DispatchArgs& d) {
     // may go in destination order; and the runs are recorded by the cut of the plan, which this launch may change
     if (a.walk) return false;
     if (((int64_t)a.n + a.T) * d.H * 2 > kFusedMaxBytes) return false;
     return a.n >= 1 && a.n <= kFusedMaxEntries && a.K <= kWave && a.E <= kLayoutWavesPerBlock * kWave && d.H >= 8 &&
-           lds_bytes(a, kLayoutWavesPerBlock) <= kLdsLimit;
+           a.W <= kFusedMaxBins && cut_layout(a.E, a.R, 1, 0).rows;
 }
 
 // Copying workgroups of a fused launch: two of 1024 threads fit a compute unit, the layout's come first.
@@ -948,13 +1108,11 @@ hipError_t launch_layout_dispatch(const LayoutArgs& a_in, const DispatchArgs& d,
     if (!layout_dispatch_fusable(a, d)) return hipErrorInvalidValue;
     a.rows_cap = d.win.rows_cap;
     a.recv_count = d.recv_count;
-    // up to PU passes one workgroup lays out; more entries are cut into chunks of one pass
-    const bool multi = a.passes > PU || a.nwc > kLayoutWavesPerBlock;
-    if (multi) {
-        a.passes = 1;
-        a.nwc = (a.n + kWave - 1) / kWave;
-        a.nchunks = (a.nwc + kLayoutWavesPerBlock - 1) / kLayoutWavesPerBlock;
-    }
+    // chunks of one pass; one workgroup lays out where there is one
+    a.passes = 1;
+    a.nwc = (a.n + kWave - 1) / kWave;
+    a.nchunks = (a.nwc + kLayoutWavesPerBlock - 1) / kLayoutWavesPerBlock;
+    const bool multi = a.nchunks > 1;
     const int nlay = multi ? a.nchunks + 1 : 1;
     const int units = d.H / 8;
     const int nseg = (units + kWave - 1) / kWave;
@@ -963,35 +1121,41 @@ hipError_t launch_layout_dispatch(const LayoutArgs& a_in, const DispatchArgs& d,
     // 32 768 bytes, top-8: 29.5 us, in two launches 43.5).
     const int group = std::max(1, std::min((a.T + kFusedCopyBlocks - 1) / kFusedCopyBlocks, kWave / a.K));
     const int ngroups = (a.T + group - 1) / group;
-    // workgroups per group: enough of them to put every compute unit to work, at most 16 segments of a token each
+    // workgroups per group: at most 16 segments of a token each, and as many as leave every workgroup of the launch a
+    // compute unit of its own (rows of 14 336 bytes, top-8, at 85 tokens 5.1 us in 170 workgroups, 6.2 in 340; at 128 tokens
+    // 6.2 us in 128, 6.5 in 256 beside the one of the layout)
     int parts = (nseg + kLayoutWavesPerBlock - 1) / kLayoutWavesPerBlock;
-    while (parts < nseg && (int64_t)ngroups * parts < 256) ++parts;
+    while (parts < nseg && nlay + (int64_t)ngroups * (parts + 1) <= 256) ++parts;
     const int spp = (nseg + parts - 1) / parts;
     parts = (nseg + spp - 1) / spp;
     const int64_t nblk = nlay + (int64_t)ngroups * parts;
     if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nblk), block(kLayoutWavesPerBlock * kWave);
-    const size_t lds = lds_bytes(a, kLayoutWavesPerBlock);  // holds the copying workgroups' E + 16 words as well
-    if (multi) hipLaunchKernelGGL((layout_dispatch_kernel<kFusedIds, true>), grid, block, lds, s, a, d, nlay, nseg, units, group, parts, spp);
-    else if (a.passes > 1) hipLaunchKernelGGL((layout_dispatch_kernel<PU, false>), grid, block, lds, s, a, d, nlay, nseg, units, group, parts, spp);
+    const size_t lds = cut_layout(a.E, a.R, 1, 0).lds;  // holds the copying workgroups' E words as well
+    if (a.nchunks > 2) hipLaunchKernelGGL((layout_dispatch_kernel<kFusedIds, true>), grid, block, lds, s, a, d, nlay, nseg, units, group, parts, spp);
+    else if (multi) hipLaunchKernelGGL((layout_dispatch_kernel<2, true>), grid, block, lds, s, a, d, nlay, nseg, units, group, parts, spp);
     else hipLaunchKernelGGL((layout_dispatch_kernel<1, false>), grid, block, lds, s, a, d, nlay, nseg, units, group, parts, spp);
     return hipGetLastError();
 }
 
-// Extra workgroups of the layout kernel that read tokens.  All of them should be running from the
-// start: a compute unit of this part holds two workgroups of 1024 threads, the part has 256 units,
-// and the layout workgroups take their places first; workgroups that find no place start when the
-// others are done and then read their share alone, as a tail.
-constexpr int kWarmBlocks = 448;
-constexpr int kResidentBlocks = 2 * 256;
+// Wavefronts of the extra workgroups of the layout kernel that read tokens.  All of them should be running from the
+// start, so that none reads its share as a tail: a compute unit holds 16 waves of this kernel (its registers) and
+// the layout workgroups take their places first, of 256 units.  Fewer leave the chunks' words to each other a freer
+// way (layout + read-ahead of 59 MB, 448 workgroups of 16 waves 14.8 us, 224 14.2, 192 13.9, 160 13.4; of 34 MB, with
+// rows cut by the capacity, 13.2, 11.4, 11.2, 11.6).
+constexpr int kWarmWaves = 192 * 16;
 
 hipError_t launch_layout(const LayoutArgs& a_in, hipStream_t s) {
     LayoutArgs a = a_in;
     a.nchunks = 1;
-    // Workgroups of 16 waves, fewer when the bin tables would not fit the LDS otherwise.
-    int wpb = a.walk ? a.walk_waves : kLayoutWavesPerBlock;
-    while (wpb > 1 && !a.walk && lds_bytes(a, wpb) > kLdsLimit) wpb >>= 1;
-    if (lds_bytes(a, wpb) > kLdsLimit) return hipErrorInvalidValue;
+    if (!a.walk && a.passes > 1 && a.nwc <= kLayoutWavesPerBlock) {  // chunks of one pass rather than one workgroup of several
+        a.passes = 1;
+        a.nwc = (a.n + kWave - 1) / kWave;
+    }
+    const LayoutCut cut = cut_layout(a.E, a.R, a.passes, a.walk ? a.walk_group : 0);
+    const int wpb = cut.waves;
+    if (cut.lds > kLdsUnit || (!cut.rows && cut.lds > kLdsLimit)) return hipErrorInvalidValue;
+    if (a.walk && a.walk_group % wpb != 0 && wpb % a.walk_group != 0) return hipErrorInvalidValue;
     int nblk = (a.nwc + wpb - 1) / wpb;
     if (nblk < 1) nblk = 1;
     if (nblk > kMaxChunks) return hipErrorInvalidValue;
@@ -999,17 +1163,19 @@ hipError_t launch_layout(const LayoutArgs& a_in, hipStream_t s) {
     a.nchunks = nblk;
     const bool pf = layout_prefetches(a);
     const int nlay = nblk + (nblk > 1 ? 1 : 0);
-    const int nwarm = pf ? std::max(64, std::min(kWarmBlocks, kResidentBlocks - nlay - 16)) : 0;
+    const int nwarm = pf ? kWarmWaves / wpb : 0;
     const dim3 grid(nlay + nwarm), block(wpb * kWave);
-    const size_t lds = lds_bytes(a, wpb);
-    const bool one_group = a.passes <= PU;
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, cut.lds, s, a); };
+    const int passes = cut.rows ? a.passes : 0;
     if (a.walk && nblk == 1) return hipErrorInvalidValue;  // inputs this small have no walk list
-    if (a.walk && one_group) hipLaunchKernelGGL((layout_kernel<true, true, true>), grid, block, lds, s, a);
-    else if (a.walk) hipLaunchKernelGGL((layout_kernel<true, false, true>), grid, block, lds, s, a);
-    else if (nblk > 1 && one_group) hipLaunchKernelGGL((layout_kernel<true, true, false>), grid, block, lds, s, a);
-    else if (nblk > 1) hipLaunchKernelGGL((layout_kernel<true, false, false>), grid, block, lds, s, a);
-    else if (one_group) hipLaunchKernelGGL((layout_kernel<false, true, false>), grid, block, lds, s, a);
-    else hipLaunchKernelGGL((layout_kernel<false, false, false>), grid, block, lds, s, a);
+    if (a.walk && passes == 1) launch(layout_kernel<true, 1, true>);
+    else if (a.walk && passes == 2) launch(layout_kernel<true, 2, true>);
+    else if (a.walk) launch(layout_kernel<true, 0, true>);
+    else if (nblk > 1 && passes == 1) launch(layout_kernel<true, 1, false>);
+    else if (nblk > 1 && passes == 2) launch(layout_kernel<true, 2, false>);
+    else if (nblk > 1) launch(layout_kernel<true, 0, false>);
+    else if (passes == 1) launch(layout_kernel<false, 1, false>);
+    else launch(layout_kernel<false, 0, false>);
     return hipGetLastError();
 }
 

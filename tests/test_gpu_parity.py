@@ -362,6 +362,30 @@ def test_several_sources_into_one_receiver_tensor(ep, hx, oracle_mod, n_src, pad
             ep.ep_group_destroy(g)
 
 
+@pytest.mark.parametrize("R,E,K,T,n_invalid", [
+    (2, 8, 2, 64, 0), (1, 1, 1, 1, 0), (32, 256, 8, 128, 1), (32, 256, 8, 129, 0), (16, 128, 16, 63, 1), (8, 64, 4, 300, 0),
+    (12, 96, 6, 3001, 1), (64, 192, 3, 1366, 0), (6, 30, 5, 205, 1), (4, 28, 7, 147, 0), (5, 25, 16, 129, 1), (8, 64, 1, 1025, 0),
+    (1, 40, 33, 31, 1), (16, 400, 64, 40, 0), (64, 512, 8, 600, 1),      # tables beyond 64 KiB
+    (64, 1024, 8, 700, 0), (512, 1024, 2, 2000, 1),                      # and beyond a compute unit
+    (64, 256, 8, 8192, 0), (8, 24, 6, 10000, 1), (8, 24, 6, 11200, 0),   # two passes, three
+])
+def test_layout_cuts_against_the_oracle(ep, hx, oracle_mod, R, E, K, T, n_invalid):
+    """Layouts over the cuts into rows, passes and workgroups: top-k that is a power of two or not, up to 16 and
+    beyond, experts per rank that are no power of two, an expert named twice by a token, masked and invalid ids."""
+    rng = np.random.default_rng(R * E + K * T)
+    topk = rng.integers(0, E, size=(T, K)).astype(np.int32)  # with repetitions
+    topk[rng.random((T, K)) < 0.02] = -1
+    if n_invalid:
+        topk[T // 2, K // 2] = E
+    lay = oracle_mod.layout(topk, E=E, R=R, layout=0, C=0, C_rank=T)
+    g = ep.ep_group_create(ep.make_config(R, E, 64, K, T))
+    for _ in range(3):  # the words through which the workgroups talk are ready for the next launch
+        h = ep.ep_layout(g, torch.from_numpy(topk).to(hx.DEV))
+        hx.assert_layout_equal(hx.fetch_layout(h, T, K, E, R, ok=(ep.EP_SUCCESS, ep.EP_ERR_INVALID_ROUTING)), lay)
+        ep.ep_handle_destroy(h)
+    ep.ep_group_destroy(g)
+
+
 def test_layout_many_launches_on_one_slab(ep, hx, oracle_mod):
     """The workgroups of a layout launch tell each other's published counts from stale ones by a
     tag that counts the launches on the handle's slab and starts over after 255 of them (the

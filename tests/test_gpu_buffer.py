@@ -404,6 +404,78 @@ def test_inputs_of_a_third_stream_dropped_behind_a_call_are_not_handed_out_again
         buf.close()
 
 
+@pytest.mark.parametrize("path", ["direct", "once_per_rank"])
+def test_calls_keep_their_order_on_whatever_stream_each_runs(hx, path):
+    """Calls without an event run on the stream they are made on, one after the other: from two streams, behind an
+    overlapping call, and, once the communication stream has been asked for, behind what is queued there.  On a stream that
+    torch did not make, and under graph capture, the communication stream takes them."""
+    from paper_2603_13606_amd.buffer import EPBuffer
+    R, E, H, K, T = 4, 16, 512, 4, 256
+    gen = torch.Generator(hx.DEV).manual_seed(12)
+    topk = [torch.randint(0, E, (T, K), generator=gen, device=hx.DEV, dtype=torch.int32) for _ in range(3)]
+    gate = torch.rand((T, K), generator=gen, device=hx.DEV)
+    xs = [torch.randn((T, H), generator=gen, device=hx.DEV).bfloat16() for _ in range(3)]
+    buf = EPBuffer(R, E, H, K, max_tokens_per_rank=T, mode="ht", dispatch_path=path)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    try:
+        want = []
+        for i in range(3):
+            r = buf.dispatch(xs[i], topk[i], gate)
+            want.append([t.clone() for t in r[:3]] + [buf.combine(r[0], r[3], gate)[0].clone()])
+            buf.destroy_handle(r[3])
+        torch.cuda.synchronize()
+        early = buf.capture()
+        with torch.cuda.stream(a):
+            torch.cuda._sleep(50_000_000)
+            r0 = buf.dispatch(xs[0], topk[0], gate)
+        with torch.cuda.stream(b):
+            r1 = buf.dispatch(xs[1], topk[1], gate)
+            r2 = buf.dispatch(xs[2], topk[2], gate, previous_event=early)
+            outs = [buf.combine(r[0], r[3], gate) for r in (r0, r1, r2)]
+        assert not r0[4].query(), "the first call ran too early for this test to say anything"
+        r1[4].synchronize()
+        assert r0[4].query()
+        r2[4].synchronize()
+        outs[2][1].synchronize()
+        for r, o, w in zip((r0, r1, r2), outs, want):
+            assert all(torch.equal(x.view(torch.int16) if x.dtype == torch.bfloat16 else x, y.view(torch.int16) if y.dtype == torch.bfloat16 else y)
+                       for x, y in zip([*r[:3], o[0]], w))
+            buf.destroy_handle(r[3])
+        outside = torch.cuda.ExternalStream(a.cuda_stream)
+        with torch.cuda.stream(outside):
+            assert buf._start(None)[1] is buf._comm
+            r = buf.dispatch(xs[0], topk[0], gate)
+        r[4].synchronize()
+        assert torch.equal(r[0].view(torch.int16), want[0][0].view(torch.int16))
+        buf.destroy_handle(r[3])
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            assert buf._start(None)[1] is buf._comm
+            r = buf.dispatch(xs[1], topk[1], gate)
+            out = buf.combine(r[0], r[3], gate)[0]
+        for _ in range(3):
+            r[0].zero_(), out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(r[0].view(torch.int16), want[1][0].view(torch.int16)) and torch.equal(out.view(torch.int16), want[1][3].view(torch.int16))
+        h = r[3]
+        r = buf.dispatch(xs[2], topk[2], gate)  # outside the capture again
+        comm = buf.get_comm_stream()
+        with torch.cuda.stream(comm):
+            torch.cuda._sleep(50_000_000)
+            queued = buf.capture()
+        out, done = buf.combine(r[0], r[3], gate)
+        assert not queued.query()
+        done.synchronize()
+        assert queued.query() and torch.equal(out.view(torch.int16), want[2][3].view(torch.int16))
+        buf.destroy_handle(r[3])
+        buf.destroy_handle(h)
+    finally:
+        torch.cuda.synchronize()
+        buf.close()
+
+
 @pytest.mark.parametrize("C", [0, 100])
 def test_large_backward_through_strided_windows_and_special_values(hx, C):
     """12 000 rows of 8 KiB in windows with a pitch: 128 bytes more per row (two launches) and 16 more (rows that start

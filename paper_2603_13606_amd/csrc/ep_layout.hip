@@ -454,8 +454,9 @@ __device__ void scan_walk(const LayoutArgs& a, const Lds& l, const int32_t* befo
 // over all experts fall to different waves, which have their share of other work too (by wave 0 alone, one after the
 // other, this was the last 1.4 us of a small layout).  STATUS: the status word too (there is one chunk; the caller of a
 // fused launch says how many rows its output takes).
+// kept: rows of padded windows in use (in the last wave; see sum_kept).
 template <bool STATUS>
-__device__ __forceinline__ void write_tables(const LayoutArgs& a, const Lds& l, int tid, int lane, int w) {
+__device__ __forceinline__ void write_tables(const LayoutArgs& a, const Lds& l, int tid, int lane, int w, int kept) {
     const int32_t* tot = l.tot;
     const int32_t* S = l.S;
     const int E = a.E, R = a.R, threads = blockDim.x;  // a power of two
@@ -478,13 +479,9 @@ __device__ __forceinline__ void write_tables(const LayoutArgs& a, const Lds& l, 
     }
     if (w != threads / kWave - 1) return;
     const int total_e = S[E];
-    int kept = total_e, rend = 0;
-    if (a.padded) {
-        kept = 0;
-#pragma unroll 4
-        for (int e = lane; e < E; e += kWave) kept += min(tot[e], a.C);
-        kept = __builtin_amdgcn_readlane(wave_inclusive_scan(kept), kWave - 1);
-    } else if (a.expert_base) {
+    int rend = 0;
+    if (!a.padded) kept = total_e;
+    if (!a.padded && a.expert_base) {
         for (int e = lane; e < E; e += kWave)
             if (tot[e] > 0) rend = max(rend, a.expert_base[e] + tot[e]);
         rend = wave_max(rend);
@@ -703,17 +700,34 @@ __device__ __forceinline__ void finish_chunks(const LayoutArgs& a, const Lds& l,
     }
 }
 
+// Rows of padded windows in use.  One wavefront; must be called by all 64 lanes.
+__device__ __forceinline__ int sum_kept(const LayoutArgs& a, const Lds& l, int lane) {
+    int kept = 0;
+    for (int c0 = 0; c0 < a.E; c0 += kScanRows * kWave) {
+        int v[kScanRows];
+#pragma unroll
+        for (int r = 0; r < kScanRows; ++r) v[r] = l.tot[min(c0 + r * kWave + lane, a.E - 1)];
+#pragma unroll
+        for (int r = 0; r < kScanRows; ++r) kept += c0 + r * kWave + lane < a.E ? min(v[r], a.C) : 0;
+    }
+    return __builtin_amdgcn_readlane(wave_inclusive_scan(kept), kWave - 1);
+}
+
 // The scans over the bins, between two barriers: the totals by wave 0, the blocks of the walk list by the others
-// (the workgroup of the tables has none).
-template <bool WALK>
-__device__ __forceinline__ void scan_bins(const LayoutArgs& a, const Lds& l, int b, int w, int waves, int nsub, const int32_t* before0,
-                                          int pitch, int step, int lane) {
+// (the workgroup of the tables has none).  Returns, in the last wave of the workgroup of the tables, the rows of padded
+// windows in use.
+template <bool MULTI, bool WALK>
+__device__ __forceinline__ int scan_bins(const LayoutArgs& a, const Lds& l, int b, int w, int waves, int nsub, const int32_t* before0,
+                                         int pitch, int step, int lane) {
+    int kept = 0;
     lds_barrier();
     if (w == 0) scan_totals(a, l, lane);
     else if (WALK && b < a.nchunks) {
         for (int sb = w - 1; sb < nsub; sb += waves - 1) scan_walk(a, l, before0, pitch, step, sb, nsub, lane);
     }
+    if (a.padded && w == waves - 1 && b == (MULTI ? a.nchunks : 0)) kept = sum_kept(a, l, lane);
     lds_barrier();
+    return kept;
 }
 
 // One workgroup's share of a layout of at most PASSES = PU passes per wavefront (64 K entries), whose entries stay in
@@ -789,7 +803,7 @@ __device__ __forceinline__ void layout_rows(const LayoutArgs& a, int32_t* lds, c
     }
     if constexpr (multi) gather_chunks<HB, WALK>(a, l, b, waves, tag);
     const int nsub = WALK && waves > a.walk_group ? waves / a.walk_group : 1;  // blocks of the walk list in this chunk
-    scan_bins<WALK>(a, l, b, w, waves, nsub, (const int32_t*)rows, 2 * PASSES * Wr, 2, lane);
+    const int kept = scan_bins<multi, WALK>(a, l, b, w, waves, nsub, (const int32_t*)rows, 2 * PASSES * Wr, 2, lane);
     uint32_t seen = 0;
     if (multi) seen = report_chunk(a, l);
 
@@ -807,7 +821,7 @@ __device__ __forceinline__ void layout_rows(const LayoutArgs& a, int32_t* lds, c
     }
     // the tables: with several chunks from a workgroup of their own, number nchunks, which has no entries: it looks across,
     // scans and writes the tables while the chunks still write theirs
-    if (b == (multi ? a.nchunks : 0)) write_tables<!multi>(a, l, tid, lane, w);
+    if (b == (multi ? a.nchunks : 0)) write_tables<!multi>(a, l, tid, lane, w, kept);
     if (multi && w == 0) finish_chunks<FUSED>(a, l, lane, seen, gen);
 }
 
@@ -871,7 +885,7 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
     // (4) entries of the other chunks, and the scans
     if constexpr (multi) gather_chunks<HB, WALK>(a, l, b, wpb, tag);
     const int nsub = WALK && wpb > a.walk_group ? wpb / a.walk_group : 1;  // blocks of the walk list in this chunk
-    scan_bins<WALK>(a, l, b, w, wpb, nsub, l.wh, W, 1, lane);
+    const int kept = scan_bins<multi, WALK>(a, l, b, w, wpb, nsub, l.wh, W, 1, lane);
     uint32_t seen = 0;
     if (multi) seen = report_chunk(a, l);
 
@@ -889,7 +903,7 @@ __device__ __forceinline__ void layout_chunk(const LayoutArgs& a, int32_t* lds, 
         }
     }
     // (6) the tables, as in layout_rows
-    if (b == (multi ? nchunks : 0)) write_tables<!multi>(a, l, tid, lane, w);
+    if (b == (multi ? nchunks : 0)) write_tables<!multi>(a, l, tid, lane, w, kept);
     if (multi && w == 0) finish_chunks<false>(a, l, lane, seen, gen);
 }
 

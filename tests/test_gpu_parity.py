@@ -1844,6 +1844,13 @@ def test_combine_two_level_order(ep, hx, oracle_mod, name, T, H, rpn, mode):
         ep.ep_group_destroy(g)
 
 
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 7, 9, 15])
+@pytest.mark.parametrize("mode", ["ht", "ll"])
+def test_combine_two_level_batches(ep, hx, oracle_mod, K, mode):
+    """The two-level combine over the batches its rows are gathered in: up to four entries per token, up to eight, and more."""
+    test_combine_two_level_order(ep, hx, oracle_mod, ("skew", dict(K=K)), 67, 520 if K % 2 else 1032, 3, mode)
+
+
 # ------------------------------------------------------------------------------ randomised shapes
 
 

@@ -614,7 +614,7 @@ def main() -> int:
         dom_bytes = dispatch_bytes if dom == "dispatch" else ab["combine"]
         run_order = args.dispatch_order != 0 and T * K >= 8192
         kernel_name = {"dispatch": "layout_dispatch_kernel" if sb.fused else
-                                   "dispatch_runs_kernel" if run_order else "dispatch_direct_kernel",
+                                   "dispatch_walk_kernel" if run_order else "dispatch_direct_kernel",
                        "combine": "combine_kernel"}[dom]
         traffic_key = spec.name + ("_padded" if sb.ll else "") + ["_token_order", "", "_destination_order_resident"][args.dispatch_order]
         if dom == "combine":

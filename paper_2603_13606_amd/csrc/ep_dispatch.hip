@@ -439,6 +439,12 @@ static void launch_walk(const DispatchArgs& a, const DispatchPlan& d, int units,
     }
 }
 
+// LDS that a workgroup of the token walk reserves and does not use: 6 of them fit a compute unit then, not 8.  The stores
+// on their way spread over less memory, which the memory system rewards (tokens of 14 336 bytes, top-8, us with 8, 6, 5 and 4
+// workgroups: 4096 tokens 115, 106.7, 106.6, 108.5, 2000 tokens 56.8, 53.3, 53.2, 54.2; 8192 bytes 61.5, 59.3, 59.2, 60.3; 512
+// bytes 18.4, 16.7 with 6).
+constexpr size_t kDirectLds = 27000;
+
 hipError_t launch_dispatch(const DispatchArgs& a, hipStream_t s) {
     const int units = a.H / 8;  // 16-byte units per row
     DispatchPlan d;
@@ -460,7 +466,7 @@ hipError_t launch_dispatch(const DispatchArgs& a, hipStream_t s) {
     int64_t nblk = (nwaves + 3) / 4;
     if (nblk < 1) nblk = 1;  // block 0 also copies the per-expert counts
     if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(dispatch_direct_kernel, dim3((unsigned)nblk), dim3(256), 0, s, a, nseg, units);
+    hipLaunchKernelGGL(dispatch_direct_kernel, dim3((unsigned)nblk), dim3(256), kDirectLds, s, a, nseg, units);
     return hipGetLastError();
 }
 

@@ -257,7 +257,8 @@ typedef struct {
     int32_t blocks;             /* blocks the input is cut into                              */
     int32_t block_entries;      /* routed entries per block                                  */
     int32_t splits;             /* workgroups that a run of average length (the entries of
-                                   one expert in one block) takes per slice               */
+                                   one expert in one block) would take per slice; nothing
+                                   is cut by it                                             */
     int32_t slice_units;        /* 16-byte units of a row per slice (8 slices per row)       */
     int32_t threads_per_piece;  /* threads that copy one row piece                           */
     int32_t blocks_per_launch;  /* blocks per copy launch                                    */

@@ -394,7 +394,12 @@ ep_result_t ep_dispatch_plan(const ep_group_config_t* cfg, int64_t num_tokens, i
     plan_dispatch((int)num_tokens, cfg->top_k, cfg->hidden, cfg->num_experts, cfg->num_ranks, cfg->dispatch_order, have_walk,
                   (int)std::min<int64_t>(prefetched_rows, num_tokens), &d);
     plan->run_order = d.run_order; plan->group = d.group; plan->blocks = d.blocks;
-    plan->block_entries = d.block_entries; plan->splits = d.splits; plan->slice_units = d.piece;
+    plan->block_entries = d.block_entries; plan->slice_units = d.piece;
+    plan->splits = 0;
+    if (d.run_order) {
+        const int run = (d.block_entries + cfg->num_experts - 1) / cfg->num_experts;
+        plan->splits = std::max(1, (run + d.rows - 1) / d.rows);
+    }
     plan->threads_per_piece = d.run_order ? 1 << d.tpr_shift : 0;
     plan->blocks_per_launch = d.blocks_per_launch; plan->launches = d.launches; plan->read_passes = d.read_passes;
     return EP_SUCCESS;

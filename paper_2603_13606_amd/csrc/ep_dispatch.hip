@@ -91,6 +91,21 @@ constexpr int kSlices = 8;
 // 94), two of shorter ones (8192 x 1024 bytes, top-8: 26.2 us, with one 28.2; 8192-byte rows 47.4/48.0).
 constexpr int walk_unroll(int tpr_shift) { return tpr_shift >= 7 ? 1 : 2; }
 
+// A launch takes fewer than 2^32 work-items.  kMaxEntries is what a group may be made for.
+constexpr int64_t kMaxWalkWorkgroups = (1ll << 32) / 256 - 1;
+constexpr int64_t kMaxEntries = 1ll << 28;
+constexpr int64_t side_workgroups(int64_t entries) { return (entries + 2047) / 2048 * 8; }
+// Places of the walk list one launch can cover, `rows` per workgroup.  A block is shorter: at most 2^20 entries where it is two
+// wave-chunks of the longest input, and otherwise bounded by its share of L2 (65 536 entries of the longest pieces, one row
+// per workgroup, top-64).
+constexpr int64_t launch_places(int slices, int rows) {
+    return (kMaxWalkWorkgroups - side_workgroups(kMaxEntries)) / slices * rows;
+}
+constexpr bool launch_fits(int slices, int rows) {  // with the side arrays of the longest input beside it
+    const int64_t workgroups = slices * ((launch_places(slices, rows) + rows - 1) / rows);
+    return launch_places(slices, rows) >= 1 << 20 && (workgroups + side_workgroups(kMaxEntries)) * 256 < 1ll << 32;
+}
+
 struct WalkPlan {
     int piece;      // 16-byte units per slice
     int units;      // 16-byte units per row
@@ -107,6 +122,9 @@ struct WalkPlan {
 // into 4 slices instead of 8 (two dies share a slice): the bytes per workgroup stay what they are
 // for bf16 rows.  Window strides are in one-byte elements then.
 constexpr int kFp8Slices = 4;
+
+static_assert(launch_fits(kSlices, 1) && launch_fits(kSlices, 2) && launch_fits(kSlices, 32), "bf16 rows");
+static_assert(launch_fits(kFp8Slices, 1) && launch_fits(kFp8Slices, 2) && launch_fits(kFp8Slices, 32), "staged FP8 rows");
 
 struct StagedRows {
     const uint8_t* staged;
@@ -382,16 +400,15 @@ static bool plan_rows(int T, int K, int H, int units, int slices, int E, int R, 
     if (d.piece >= 8) d.piece = (d.piece + 7) / 8 * 8;  // whole 128-byte lines per slice (the last slices get less)
     d.tpr_shift = 4;
     while ((1 << d.tpr_shift) < d.piece && d.tpr_shift < 8) ++d.tpr_shift;
-    const int rows_per_step = (256 >> d.tpr_shift) * walk_unroll(d.tpr_shift);
-    const int avg_run = (int)(((int64_t)d.group * chunk_entries + E - 1) / E);
-    d.splits = std::max(1, (avg_run + rows_per_step - 1) / rows_per_step);
+    d.rows = (256 >> d.tpr_shift) * walk_unroll(d.tpr_shift);
     d.block_entries = d.group * chunk_entries;
-    // blocks per launch: all of them, or as many as cover kWarmBytes of tokens
-    d.blocks_per_launch = d.blocks;
+    // blocks per launch: as many as a grid holds (3.9 million rows of 14 336 bytes), or as cover kWarmBytes of tokens
+    int64_t per_launch = launch_places(slices, d.rows) / d.block_entries;
     if (order == EP_ORDER_DESTINATION) {
         const int64_t block_bytes = ((int64_t)d.block_entries + K - 1) / K * H * 2;
-        d.blocks_per_launch = (int)std::max<int64_t>(1, std::min<int64_t>(d.blocks, kWarmBytes / std::max<int64_t>(block_bytes, 1)));
+        per_launch = std::min(per_launch, kWarmBytes / std::max<int64_t>(block_bytes, 1));
     }
+    d.blocks_per_launch = (int)std::max<int64_t>(1, std::min<int64_t>(d.blocks, per_launch));
     for (int b0 = 0; b0 < d.blocks; b0 += d.blocks_per_launch) {
         const int nb = std::min(d.blocks_per_launch, d.blocks - b0);
         const int t1 = (int)std::min<int64_t>(T, ((int64_t)(b0 + nb) * d.block_entries + K - 1) / K);
@@ -429,7 +446,7 @@ static void launch_walk(const DispatchArgs& a, const DispatchPlan& d, int units,
     WalkPlan p;
     p.piece = d.piece; p.units = units; p.tpr_shift = d.tpr_shift; p.first = first; p.last = last;
     p.entries = a.T * a.K;
-    p.side_blocks = first == 0 && (a.recv_w || a.recv_src) ? (p.entries + 2047) / 2048 * 8 : 0;
+    p.side_blocks = first == 0 && (a.recv_w || a.recv_src) ? (int)side_workgroups(p.entries) : 0;
     switch (d.tpr_shift) {
         case 4: launch_walk_kernel<4, FP8>(a, p, f, s); break;
         case 5: launch_walk_kernel<5, FP8>(a, p, f, s); break;
@@ -497,8 +514,9 @@ hipError_t launch_dispatch_fp8_staged(const DispatchArgs& a, float* recv_scales,
     DispatchPlan d;
     if (a.H % 128 != 0 || !plan_dispatch_fp8_staged(a.T, a.K, a.H, a.E, a.R, a.walk != nullptr, &d)) return hipErrorInvalidValue;
     const StagedRows f = {staged, pitch, recv_scales, fp8_code_units(a.H), a.H / 128};
-    // the whole list in one launch: the staged rows were written just before, nothing to read ahead
-    launch_walk<true>(a, d, fp8_row_units(a.H), 0, a.T * a.K, f, s);
+    // the staged rows were written just before, nothing to read ahead
+    const int64_t n = (int64_t)a.T * a.K, step = (int64_t)d.blocks_per_launch * d.block_entries;
+    for (int64_t e0 = 0; e0 < n; e0 += step) launch_walk<true>(a, d, fp8_row_units(a.H), (int)e0, (int)std::min(n, e0 + step), f, s);
     return hipGetLastError();
 }
 

@@ -274,7 +274,7 @@ struct DispatchPlan {
     int group;              // wave-chunks of the layout per block
     int blocks;             // blocks of the input
     int block_entries;      // routed entries per block
-    int splits;             // workgroups that a run of average length -- the entries of one expert in one block -- takes
+    int rows;               // places of the walk list a workgroup takes
     int piece;              // 16-byte units of a row per XCD slice
     int tpr_shift;          // log2(threads that share one row piece)
     int blocks_per_launch;  // blocks per copy launch

@@ -131,7 +131,9 @@ def test_dispatch_plan_covers_the_input_and_fits_the_launch_limits(ep):
     rows were announced to the layout call, and small inputs or the token order plan nothing."""
     import ctypes
     shapes = [(32, 256, 7168, 8, 4096), (64, 256, 7168, 8, 8192), (16, 128, 4096, 8, 4096), (1, 1024, 7168, 16, 4096),
-              (8, 8, 64, 1, 9000), (4, 24, 1000, 3, 3000), (64, 1024, 8192, 64, 100000), (2, 2, 8, 2, 5000)]
+              (8, 8, 64, 1, 9000), (4, 24, 1000, 3, 3000), (64, 1024, 8192, 64, 100000), (2, 2, 8, 2, 5000),
+              (32, 256, 7168, 8, 524288), (32, 256, 7168, 8, 1 << 25), (8, 64, 8256, 2, 1 << 20), (8, 64, 16384, 1, 1 << 28),
+              (1024, 1024, 4104, 64, 1 << 22), (2, 2, 64, 64, 1 << 22), (64, 256, 640, 3, 89478485)]
     for R, E, H, K, T in shapes:
         for order in (ep.EP_ORDER_DESTINATION, ep.EP_ORDER_DESTINATION_RESIDENT):
             cfg = ep.make_config(R, E, H, K, T, dispatch_order=order)
@@ -143,14 +145,19 @@ def test_dispatch_plan_covers_the_input_and_fits_the_launch_limits(ep):
             assert p.run_order == 1
             assert p.group >= 1 and p.blocks * p.group >= nwc > (p.blocks - 1) * p.group
             assert p.block_entries == p.group * passes * 64
-            assert 1 <= p.splits and 8 * E * p.splits < 2 ** 31 and p.blocks <= 65535
+            # the grid of a copy launch: 8 slices, 256 threads per workgroup, pieces of 128 threads and more copied one per
+            # thread, shorter ones two; the first launch has a workgroup per 256 entries for the side arrays as well
+            rows = 256 // p.threads_per_piece * (1 if p.threads_per_piece >= 128 else 2)
+            places = min(T * K, p.blocks_per_launch * p.block_entries)
+            assert (8 * -(-places // rows) + 8 * -(-T * K // 2048)) * 256 < 2 ** 32
+            assert p.splits == max(1, -(-(-(-p.block_entries // E)) // rows))
             slack = 8 if p.slice_units >= 8 else 1  # slices of 8 units or more hold whole 128-byte lines
             assert p.slice_units * 8 >= H // 8 > (p.slice_units - slack) * 8 and (slack == 1 or p.slice_units % 8 == 0)
             assert p.threads_per_piece in (16, 32, 64, 128, 256)
             assert p.launches == -(-p.blocks // p.blocks_per_launch)
             # one slice of a block's tokens stays within 2 MiB (half of an XCD's L2), or the block is
-            # a single wave-chunk, which cannot be cut
-            assert p.group == 1 or (p.block_entries // K) * (2 * H // 8) <= 2 << 20 or p.block_entries <= 768
+            # a single wave-chunk, which cannot be cut, or the two of a workgroup where tables leave no more waves
+            assert p.group == 1 or (p.group == 2 and E + R == 2048) or (p.block_entries // K) * (2 * H // 8) <= 2 << 20 or p.block_entries <= 768
             if order == ep.EP_ORDER_DESTINATION:
                 assert p.read_passes == p.launches
                 tokens_per_launch = -(-p.blocks_per_launch * p.block_entries // K)
@@ -160,7 +167,8 @@ def test_dispatch_plan_covers_the_input_and_fits_the_launch_limits(ep):
                 q = ep.ep_dispatch_plan(cfg, T, first)
                 assert q.read_passes == p.read_passes - (1 if first >= min(T, tokens_per_launch) else 0)
             else:
-                assert p.read_passes == 0 and p.launches == 1
+                assert p.read_passes == 0
+                assert p.launches == 1 or 8 * -(-(places + p.block_entries) // rows) * 256 > 2 ** 31
         cfg = ep.make_config(R, E, H, K, T)
         assert ep.ep_dispatch_plan(cfg, T).run_order == 0
     with pytest.raises(ep.EpError):

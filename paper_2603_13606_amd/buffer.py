@@ -83,13 +83,22 @@ class EPBuffer:
     # ------------------------------------------------------------------ streams and events
     @property
     def comm_stream(self) -> torch.cuda.Stream:
-        """The communication stream.  Once asked for, it takes every call: its owner may queue work between them."""
+        """The communication stream.  Once asked for, it takes every call: its owner may queue work between them.  It comes
+        behind the calls made so far, but for one that is given out under graph capture: it may be part of the capture, which
+        can't wait for work outside of it.  The next call or request outside the capture makes up for that."""
         with self._lock:
-            if not self._comm_given:
-                self._comm_given = True
-                if self._order_event is not None:
-                    self._comm.wait_event(self._order_event)
+            if self._order_event is not None and self._comm.cuda_stream not in self._order_streams and not self._capturing():
+                self._comm.wait_event(self._order_event)
+                self._order_streams += (self._comm.cuda_stream,)
+            self._comm_given = True
         return self._comm
+
+    def _capturing(self) -> bool:
+        """Whether the compute stream or the communication stream is under graph capture."""
+        if torch.cuda.is_current_stream_capturing():
+            return True
+        with torch.cuda.stream(self._comm):
+            return torch.cuda.is_current_stream_capturing()
 
     def get_comm_stream(self) -> torch.cuda.Stream:
         return self.comm_stream

@@ -93,6 +93,11 @@ class EPBuffer:
             self._comm_given = True
         return self._comm
 
+    @comm_stream.setter
+    def comm_stream(self, stream: torch.cuda.Stream) -> None:
+        with self._lock:
+            self._comm, self._comm_given = stream, True
+
     def _capturing(self) -> bool:
         """Whether the compute stream or the communication stream is under graph capture."""
         if torch.cuda.is_current_stream_capturing():

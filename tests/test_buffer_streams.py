@@ -60,3 +60,11 @@ def test_a_wait_that_fails_is_not_taken_for_done(buf, monkeypatch):
         assert not buf._comm_given
     buf.get_comm_stream()
     assert buf._comm.waited == ["first call"]
+
+
+def test_another_communication_stream_can_be_set(buf):
+    """It takes the calls from then on, behind the last one made."""
+    other = Stream(3)
+    buf.comm_stream = other
+    assert buf.comm_stream is other and buf.get_comm_stream() is other and buf._comm_given
+    assert other.waited == ["first call"]

@@ -41,7 +41,8 @@ typedef enum {
     EP_ERR_BUSY = 5,            /* group destroyed while handles are alive                     */
     EP_ERR_HIP = 6,             /* a HIP runtime call failed                                   */
     EP_ERR_NOMEM = 7,
-    EP_ERR_TIMEOUT = 8          /* ep_complete waited for counters that were never published   */
+    EP_ERR_TIMEOUT = 8          /* a wait on the device ran out: ep_complete's for counters, or
+                                   a layout's for its own workgroups (see ep_layout)          */
 } ep_result_t;
 
 /* Algorithm mode, fixed at group creation (Sec. III-D).  It selects the output
@@ -336,6 +337,10 @@ EP_API ep_result_t ep_group_query(ep_group_t group, ep_group_info_t *info);
  * at which this source's rows of expert e start in the receiver's tensor (what the
  * handle-time metadata exchange of Sec. III-C would deliver).  NULL = exclusive
  * prefix sum of this source's own counts.
+ * More than 1024 entries are laid out by several workgroups, which have to run at the same
+ * time and wait for each other, no longer than about a second: where other work holds the
+ * compute units beyond that, the status bit 3 is set, ep_handle_query returns EP_ERR_TIMEOUT,
+ * and rows are missing or placed wrongly (inside the arrays and windows).
  * The handle is read-only afterwards and may serve any number of dispatch/combine
  * calls (forward and backward reuse, Sec. III-C).  Takes a slab from the group's
  * pool; allocates only if the pool is exhausted.

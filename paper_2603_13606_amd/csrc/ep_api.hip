@@ -359,7 +359,7 @@ const char* ep_error_string(ep_result_t code) {
         case EP_ERR_BUSY: return "group still has live handles";
         case EP_ERR_HIP: return "HIP runtime error";
         case EP_ERR_NOMEM: return "out of device memory";
-        case EP_ERR_TIMEOUT: return "coordination counters were not published within the spin limit";
+        case EP_ERR_TIMEOUT: return "a wait on the device ran out: coordination counters or workgroups of a layout";
     }
     return "unknown error code";
 }

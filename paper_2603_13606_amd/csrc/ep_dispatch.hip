@@ -134,16 +134,22 @@ struct StagedRows {
     int groups;          // H / 128
 };
 
+// The row of a place of the walk list, -1 where it holds none.  A layout that ended without all of its counts
+// (STATUS_TIMEOUT) leaves places as they were before it: such an entry may name any token.
+__device__ __forceinline__ int listed_row(const DispatchArgs& a, const int2& entry) {
+    return (unsigned)entry.x < (unsigned)a.T ? entry.y : -1;
+}
+
 // Fills the side arrays in the order of the expert-sorted list, that is of the rows: 64 neighbouring
 // words per store, by workgroups of their own.  Done by the copying workgroups of one slice, one word per row,
 // all of it fell to one die, and its workgroups were the last to end (101 us for 82).
 __device__ void walk_sides(const DispatchArgs& a, int i, int entries) {
     if (i >= min(entries, a.totals[TOT_SORTED])) return;
-    const int row = a.sorted_row[i];
+    const int row = a.sorted_row[i], t = a.sorted_token[i], k = a.sorted_k[i];
     if (row < 0 || row >= a.win.rows_cap) return;
-    const int t = a.sorted_token[i];
+    if ((unsigned)t >= (unsigned)a.T || (unsigned)k >= (unsigned)a.K) return;  // never written: see listed_row
     if (a.recv_src) a.recv_src[row] = t;
-    if (a.recv_w) a.recv_w[row] = a.w ? a.w[(int64_t)t * a.w_stride + a.sorted_k[i]] : 1.0f;
+    if (a.recv_w) a.recv_w[row] = a.w ? a.w[(int64_t)t * a.w_stride + k] : 1.0f;
 }
 
 // TPR_SHIFT = log2(threads that share one row piece); PADDED = window addressing mode; FP8 =
@@ -195,7 +201,7 @@ __global__ __launch_bounds__(256) void dispatch_walk_kernel(DispatchArgs a, Walk
     bool have_all = true;
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-        row[q] = pos0 + q < end ? en[q].y : -1;
+        row[q] = pos0 + q < end ? listed_row(a, en[q]) : -1;
         if (row[q] >= a.win.rows_cap) {
             if (xs == 0 && u == 0) atomicOr(&a.totals[TOT_STATUS], STATUS_OUTPUT_OVERFLOW);
             row[q] = -1;

@@ -558,6 +558,11 @@ constexpr int kTagShift = 24;        // a published word is (tag << 24) | count:
 constexpr uint32_t kCountMask = (1u << kTagShift) - 1u;
 constexpr uint32_t kTags = 255;      // tags 1 .. 255; 0 is what a cleared word holds
 
+// What a word says to launch `tag`: a chunk that has not published counts nothing.
+constexpr uint32_t published(uint32_t word, uint32_t tag) { return word >> kTagShift == tag ? word & kCountMask : 0u; }
+static_assert(published((7u << kTagShift) | 300u, 7u) == 300u && published((6u << kTagShift) | 300u, 7u) == 0u &&
+              published(0u, 1u) == 0u && published((kTags << kTagShift) | kCountMask, kTags) == kCountMask, "stale words count nothing");
+
 // Loads the words chunks r0 .. r0+HB-1 have published for bin c.  Every lane loads from a
 // valid address (rows beyond the last chunk repeat it, their words are ignored later):
 // no branch, so all HB loads are in flight together.
@@ -636,8 +641,13 @@ __device__ __forceinline__ void gather_chunks(const LayoutArgs& a, const Lds& l,
 #pragma unroll
                 for (int j = 0; j < HB; ++j) all = all && (hv[j] >> kTagShift) == tag;
                 if (all) break;
-                if (++rounds >= kLookLimit) {  // a chunk never published: flag it (the counts are then undefined)
+                if (++rounds >= kLookLimit) {  // a chunk has not published: flag it
+                    // The counts are too small then, never too large, and every one of them is used as it is read here: slots and
+                    // places of the lists come out below the true ones, inside their arrays.  (The words of an earlier and larger
+                    // launch would point beyond them.)
                     gave_up = true;
+#pragma unroll
+                    for (int j = 0; j < HB; ++j) hv[j] = published(hv[j], tag);
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);

@@ -152,6 +152,10 @@ __device__ __forceinline__ Lds carve_lds(int32_t* base, const LayoutArgs& a, int
 constexpr int kRows = 16;
 __host__ __device__ constexpr int row_words(int W) { return (W + 1) & ~1; }
 
+// The low half of such a word, which holds a count in place of the bits later on: the compiler must not take accesses to the half for
+// independent of those to the word.
+typedef int32_t __attribute__((may_alias)) half_word;
+
 constexpr int lds_ints(int W, int nw) { return (nw + 1) * W + 3 * W + 1; }
 constexpr int rows_lds_ints(int W) { return 2 * kRows * row_words(W) + 3 * W + 1; }
 // What the walk list adds, with blocks of `group` wave-chunks.
@@ -419,10 +423,10 @@ __device__ void scan_totals(const LayoutArgs& a, const Lds& l, int lane) {
 // cut at the capacity.
 // before0: of block 0's first wave, the entries of every bin in the waves of the chunk before it, a word every `step`,
 // then the next waves' at `pitch`.
-__device__ void scan_walk(const LayoutArgs& a, const Lds& l, const int32_t* before0, int pitch, int step, int sb, int nsub, int lane) {
+__device__ void scan_walk(const LayoutArgs& a, const Lds& l, const half_word* before0, int pitch, int step, int sb, int nsub, int lane) {
     const int E = a.E, cap = a.padded ? a.C : 0x7fffffff;
-    const int32_t* lo = before0 + sb * a.walk_group * pitch;
-    const int32_t* hi = lo + a.walk_group * pitch;
+    const half_word* lo = before0 + sb * a.walk_group * pitch;
+    const half_word* hi = lo + a.walk_group * pitch;
     int base = 0, carry = 0;
     for (int c0 = 0; c0 < E; c0 += kScanRows * kWave) {
         int start[kScanRows], rows[kScanRows];
@@ -727,7 +731,7 @@ __device__ __forceinline__ int sum_kept(const LayoutArgs& a, const Lds& l, int l
 // (the workgroup of the tables has none).  Returns, in the last wave of the workgroup of the tables, the rows of padded
 // windows in use.
 template <bool MULTI, bool WALK>
-__device__ __forceinline__ int scan_bins(const LayoutArgs& a, const Lds& l, int b, int w, int waves, int nsub, const int32_t* before0,
+__device__ __forceinline__ int scan_bins(const LayoutArgs& a, const Lds& l, int b, int w, int waves, int nsub, const half_word* before0,
                                          int pitch, int step, int lane) {
     int kept = 0;
     lds_barrier();
@@ -803,7 +807,7 @@ __device__ __forceinline__ void layout_rows(const LayoutArgs& a, int32_t* lds, c
         int run = 0;
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
-            *(int32_t*)&rows[r * Wr + c] = run;
+            *(half_word*)&rows[r * Wr + c] = run;
             run += (int)__popcll(v[r]);
         }
         if (multi && b < a.nchunks)  // the workgroup after the last chunk has no entries: it only writes the tables
@@ -813,7 +817,7 @@ __device__ __forceinline__ void layout_rows(const LayoutArgs& a, int32_t* lds, c
     }
     if constexpr (multi) gather_chunks<HB, WALK>(a, l, b, waves, tag);
     const int nsub = WALK && waves > a.walk_group ? waves / a.walk_group : 1;  // blocks of the walk list in this chunk
-    const int kept = scan_bins<multi, WALK>(a, l, b, w, waves, nsub, (const int32_t*)rows, 2 * PASSES * Wr, 2, lane);
+    const int kept = scan_bins<multi, WALK>(a, l, b, w, waves, nsub, (const half_word*)rows, 2 * PASSES * Wr, 2, lane);
     uint32_t seen = 0;
     if (multi) seen = report_chunk(a, l);
 
@@ -824,8 +828,8 @@ __device__ __forceinline__ void layout_rows(const LayoutArgs& a, int32_t* lds, c
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const uint64_t* row = mine + p * Wr;
-            sl[p] = en[p].ok ? sl[p] + *(const int32_t*)&row[en[p].e] : -1;
-            rsl[p] += *(const int32_t*)&row[a.E + 2 + en[p].d];
+            sl[p] = en[p].ok ? sl[p] + *(const half_word*)&row[en[p].e] : -1;
+            rsl[p] += *(const half_word*)&row[a.E + 2 + en[p].d];
         }
         emit_group<multi, WALK>(a, en, 0, sl, rsl, l, l.walk + sb * a.E, walk_base);
     }

@@ -462,11 +462,28 @@ static void launch_walk(const DispatchArgs& a, const DispatchPlan& d, int units,
     }
 }
 
-// LDS that a workgroup of the token walk reserves and does not use: 6 of them fit a compute unit then, not 8.  The stores
-// on their way spread over less memory, which the memory system rewards (tokens of 14 336 bytes, top-8, us with 8, 6, 5 and 4
-// workgroups: 4096 tokens 115, 106.7, 106.6, 108.5, 2000 tokens 56.8, 53.3, 53.2, 54.2; 8192 bytes 61.5, 59.3, 59.2, 60.3; 512
-// bytes 18.4, 16.7 with 6).
-constexpr size_t kDirectLds = 27000;
+// LDS that a workgroup of the token walk reserves and does not use, so that fewer than 8 workgroups share a compute unit.  LDS is
+// handed out in units of 1280 bytes of 160 KiB: 21 of them leave 6 workgroups, 25 leave 5 (counted on the card).  The stores on
+// their way spread over less memory then, which the memory system rewards where a launch is long and a wave has several
+// rows to write.  Elsewhere the waves are needed to keep loads in flight, or the workgroups that do not fit run as a tail.
+// Dispatch alone, with 8 / 6 / 5 workgroups, in us, at 128 experts; us before the reserve was introduced (and the side arrays
+// were written by lanes) in front:
+//   top-1  32.7: 33.5/39.1/43.0 at 134 000 rows of 512 bytes, 91.6: 91.9/95.3/101 at 19 100 of 14 336       -> 8
+//   top-2  44.7: 41.1/49.6/56.0 at 128 MB of 512-byte rows (so from 1 KiB rows on), 134: 132/132/128 at 440 MB of 14 336
+//   top-4  15.4: 15.6/15.8/16.8 at 64 MB of 14 336, 32.8: 31.3/31.1/31.1 at 128 MB, 109: 109/107/107 at 440 MB
+//   top-6  8.9: 8.7/9.6/9.2 at 40 MB of 14 336, 30.0: 30.5/29.3/29.7 at 128 MB, 106: 111/103/103 at 440 MB
+//   top-8  9.1: 8.9/9.0/9.8 at 40 MB of 14 336, 15.4: 15.1/14.9/14.6 at 64 MB with side arrays, 31.0: 30.9/29.1/29.2 at 128 MB,
+//          106: 112/101/104 at 440 MB; 103: 110/103/107 at 440 MB of 2048
+//   top-12 14.3: 14.1/14.0/14.3 at 64 MB of 14 336, 28.4: 28.2/29.0/28.1 at 128 MB, 99.3: 109/104/98.2 at 440 MB
+// In between, how evenly the workgroups fill the rounds of resident ones decides, within 5 % either way.
+constexpr size_t kLdsGranule = 1280, kSixWorkgroups = 21 * kLdsGranule, kFiveWorkgroups = 25 * kLdsGranule;
+
+static size_t token_walk_reserve(int T, int K, int H) {
+    const int64_t bytes = (int64_t)T * K * H * 2;
+    if (K < 2 || H < 512) return 0;
+    if (bytes >= 112ll << 20) return K > 8 ? kFiveWorkgroups : kSixWorkgroups;
+    return K >= 6 && K <= 8 && bytes >= 48ll << 20 ? kFiveWorkgroups : 0;
+}
 
 hipError_t launch_dispatch(const DispatchArgs& a, hipStream_t s) {
     const int units = a.H / 8;  // 16-byte units per row
@@ -489,7 +506,7 @@ hipError_t launch_dispatch(const DispatchArgs& a, hipStream_t s) {
     int64_t nblk = (nwaves + 3) / 4;
     if (nblk < 1) nblk = 1;  // block 0 also copies the per-expert counts
     if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(dispatch_direct_kernel, dim3((unsigned)nblk), dim3(256), kDirectLds, s, a, nseg, units);
+    hipLaunchKernelGGL(dispatch_direct_kernel, dim3((unsigned)nblk), dim3(256), token_walk_reserve(a.T, a.K, a.H), s, a, nseg, units);
     return hipGetLastError();
 }
 

@@ -277,7 +277,10 @@ __global__ __launch_bounds__(256) void dispatch_warm_kernel(DispatchArgs a, int 
 // amax == 0 gives scale 1.  Work unit = one wavefront x 1024 channels of one token:
 // a lane owns 16 consecutive channels (32 bytes in, 16 bytes out), a group is 8 lanes.
 // The row is quantised once and stored K times.
-
+//
+// LATE: the destination rows are loaded behind the quantisation, a round trip later, and the stores of a wave begin
+// that much apart from those of the others (see launch_dispatch_fp8).
+template <bool LATE>
 __global__ __launch_bounds__(256) void dispatch_fp8_kernel(DispatchArgs a, float* recv_scales, int nseg) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -296,11 +299,19 @@ __global__ __launch_bounds__(256) void dispatch_fp8_kernel(DispatchArgs a, float
         in0 = __builtin_nontemporal_load(src);
         in1 = __builtin_nontemporal_load(src + 1);
     }
-    int my_row = lane < a.K ? a.dst_row[(int64_t)t * a.K + lane] : -1;
-    const float my_w = entry_weight(a, t, lane, seg == 0);
+    int my_row = -1;
+    float my_w = 1.0f;
+    if (!LATE) {
+        my_row = lane < a.K ? a.dst_row[(int64_t)t * a.K + lane] : -1;
+        my_w = entry_weight(a, t, lane, seg == 0);
+    }
     float scale;
     const u32x4 q = quantize16(in0, in1, &scale);
     const int groups = a.H >> 7;
+    if (LATE) {
+        my_row = lane < a.K ? a.dst_row[(int64_t)t * a.K + lane] : -1;
+        my_w = entry_weight(a, t, lane, seg == 0);
+    }
     my_row = deliver_sides(a.win, a.recv_w, a.recv_src, a.totals, seg == 0, my_row, my_w, t);
     uint8_t* base = (uint8_t*)a.win.base;  // window strides are in one-byte elements here
     for (int k = 0; k < a.K; ++k) {
@@ -523,7 +534,13 @@ hipError_t launch_dispatch_fp8(const DispatchArgs& a, float* recv_scales, hipStr
     int64_t nblk = (nwaves + 3) / 4;
     if (nblk < 1) nblk = 1;
     if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(dispatch_fp8_kernel, dim3((unsigned)nblk), dim3(256), 0, s, a, recv_scales, nseg);
+    // Rows loaded late where the launch fills the 8192 waves that are resident at a time, or nearly: all of their stores would come at
+    // once otherwise.  Dispatch with side arrays, us, early / late: 8000 waves of 1024 channels, top-8, 18.7/16.5, 8192
+    // waves of 512 12.9/11.1, 8192 of 1024, top-2, 8.3/7.4; fewer waves, and shorter rows, are
+    // bound by the round trip: 7000 waves of 14 336-byte tokens 13.8/14.1, 3500 7.3/7.6, 30 000 of 256 channels 24.5/26.6.
+    const bool late = nwaves >= 7680 && a.H >= 512;
+    if (late) hipLaunchKernelGGL(dispatch_fp8_kernel<true>, dim3((unsigned)nblk), dim3(256), 0, s, a, recv_scales, nseg);
+    else hipLaunchKernelGGL(dispatch_fp8_kernel<false>, dim3((unsigned)nblk), dim3(256), 0, s, a, recv_scales, nseg);
     return hipGetLastError();
 }
 

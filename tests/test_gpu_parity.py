@@ -1624,6 +1624,8 @@ FP8_CASES = [
     ("ll_decode", 1100, 128, "ll", 60, True, "ahead"),     # one group per row
     ("ll_decode", 90, 1152, "ht", 0, True, "ahead"),       # too small for the destination order: token walk
     ("stress_hot", None, None, "ht", 0, False, "ahead"),   # 117 MB of tokens, more than one read-ahead covers
+    (("skew", dict(K=6)), 3840, 1152, "ht", 0, True, 0),   # 7680 waves: the rows are loaded behind the quantisation
+    ("skew", 7685, 640, "ll", 300, True, 0),               # the same with capacity drops, part-filled segments
     (("skew", dict(K=33)), 300, 512, "ht", 0, True, "ahead"),
 ]
 

@@ -15,7 +15,6 @@ constexpr int kMaxTopK = 64;
 constexpr int kMaxWaveChunks = 512;        // wave-chunks per layout
 constexpr int kMaxChunks = 256;            // workgroups (chunks) per layout, and rows of the published bin sums
 constexpr int kLayoutWavesPerBlock = 16;   // wavefronts per workgroup (chunk); fewer when the bin tables are large
-constexpr int kLayoutOneBlockEntries = 4096;  // inputs up to this size are laid out by one workgroup
 constexpr int kTotalsWords = 16;
 constexpr int kLayoutCtlWords = 4;
 

@@ -107,20 +107,16 @@ def test_header_is_plain_c_and_cxx(tmp_path):
 
 def test_layout_plan_covers_every_entry(ep):
     """Host-side planning: the wave-chunks cover the input, there are at most 512 of them (256
-    workgroups of at least two), small inputs fit one workgroup of 16 waves, and up to 512 * 128
-    entries a wave keeps its entries in registers (at most two passes)."""
+    workgroups of at least two), inputs of one workgroup's 1024 entries and all others are cut into passes of 64 as long
+    as that gives no more, and up to 512 * 128 entries a wave keeps its entries in registers (at most two passes)."""
     for n in [0, 1, 63, 64, 65, 1023, 1024, 1025, 4095, 4096, 4097, 16384, 32768, 65536, 65537,
               160000, 262144, 1 << 20, (1 << 28)]:
         passes, chunks = ep.ep_layout_plan(n)
         assert passes >= 1 and 0 <= chunks <= 512
         assert chunks * passes * 64 >= n
         assert (chunks - 1) * passes * 64 < n or n == 0
-        if n <= 1024:
-            assert passes == 1
-        if n <= 4096:
-            assert chunks <= 16
-        elif n <= 65536:
-            assert passes <= 2
+        assert passes == 1 or n > 512 * 64
+        assert passes <= 2 or n > 512 * 128
     with pytest.raises(ep.EpError):
         ep.ep_layout_plan(-1)
 

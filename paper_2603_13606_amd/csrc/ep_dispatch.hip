@@ -134,22 +134,20 @@ struct StagedRows {
     int groups;          // H / 128
 };
 
-// The row of a place of the walk list, -1 where it holds none.  A layout that ended without all of its counts
-// (STATUS_TIMEOUT) leaves places as they were before it: such an entry may name any token.
-__device__ __forceinline__ int listed_row(const DispatchArgs& a, const int2& entry) {
-    return (unsigned)entry.x < (unsigned)a.T ? entry.y : -1;
-}
+// The token an entry of the layout's lists names.  A layout that ended without all of its counts (STATUS_TIMEOUT) leaves
+// places of the lists as they were before it: such an entry may hold anything.
+__device__ __forceinline__ int listed_token(const DispatchArgs& a, int t) { return (int)min((uint32_t)t, (uint32_t)a.T - 1u); }
 
 // Fills the side arrays in the order of the expert-sorted list, that is of the rows: 64 neighbouring
 // words per store, by workgroups of their own.  Done by the copying workgroups of one slice, one word per row,
 // all of it fell to one die, and its workgroups were the last to end (101 us for 82).
 __device__ void walk_sides(const DispatchArgs& a, int i, int entries) {
     if (i >= min(entries, a.totals[TOT_SORTED])) return;
-    const int row = a.sorted_row[i], t = a.sorted_token[i], k = a.sorted_k[i];
+    const int row = a.sorted_row[i];
     if (row < 0 || row >= a.win.rows_cap) return;
-    if ((unsigned)t >= (unsigned)a.T || (unsigned)k >= (unsigned)a.K) return;  // never written: see listed_row
+    const int t = listed_token(a, a.sorted_token[i]);
     if (a.recv_src) a.recv_src[row] = t;
-    if (a.recv_w) a.recv_w[row] = a.w ? a.w[(int64_t)t * a.w_stride + k] : 1.0f;
+    if (a.recv_w) a.recv_w[row] = a.w ? a.w[(int64_t)t * a.w_stride + min((uint32_t)a.sorted_k[i], (uint32_t)a.K - 1u)] : 1.0f;
 }
 
 // TPR_SHIFT = log2(threads that share one row piece); PADDED = window addressing mode; FP8 =
@@ -201,12 +199,12 @@ __global__ __launch_bounds__(256) void dispatch_walk_kernel(DispatchArgs a, Walk
     bool have_all = true;
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-        row[q] = pos0 + q < end ? listed_row(a, en[q]) : -1;
+        row[q] = pos0 + q < end ? en[q].y : -1;
         if (row[q] >= a.win.rows_cap) {
             if (xs == 0 && u == 0) atomicOr(&a.totals[TOT_STATUS], STATUS_OUTPUT_OVERFLOW);
             row[q] = -1;
         }
-        const int t = row[q] >= 0 ? en[q].x : 0, r = max(row[q], 0);
+        const int t = row[q] >= 0 ? listed_token(a, en[q].x) : 0, r = max(row[q], 0);
         const int64_t off = PADDED ? window_offset(a.win, r) : (int64_t)r * a.win.stride0;
         src[q] = src_base + (int64_t)t * src_pitch;
         dst[q] = (uint8_t*)a.win.base + off * elem_bytes;

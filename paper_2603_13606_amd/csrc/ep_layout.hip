@@ -646,12 +646,7 @@ __device__ __forceinline__ void gather_chunks(const LayoutArgs& a, const Lds& l,
                 for (int j = 0; j < HB; ++j) all = all && (hv[j] >> kTagShift) == tag;
                 if (all) break;
                 if (++rounds >= kLookLimit) {  // a chunk has not published: flag it
-                    // The counts are too small then, never too large, and every one of them is used as it is read here: slots and
-                    // places of the lists come out below the true ones, inside their arrays.  (The words of an earlier and larger
-                    // launch would point beyond them.)
                     gave_up = true;
-#pragma unroll
-                    for (int j = 0; j < HB; ++j) hv[j] = published(hv[j], tag);
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);
@@ -669,6 +664,20 @@ __device__ __forceinline__ void gather_chunks(const LayoutArgs& a, const Lds& l,
                 before += (int)(cnt & (0u - ((earlier >> j) & 1u)));
                 if (WALK) bstart += (int)(cnt & (0u - ((blk_earlier >> j) & 1u)));
                 if (WALK) bcount += (int)(cnt & (0u - ((blk >> j) & 1u)));
+            }
+        }
+        if (__builtin_expect(gave_up, 0)) {
+            // Without all of the counts, what this launch has published so far, word by word: the sums are too small then, never too
+            // large, and slots and places of the lists come out below the true ones, inside their arrays.  (The words of
+            // an earlier, larger launch would point beyond them.)
+            before = total = bstart = bcount = 0;
+#pragma unroll 1
+            for (int r = 0; r < nchunks; ++r) {
+                const int cnt = (int)published(__hip_atomic_load(a.pub + (int64_t)r * W + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), tag);
+                total += cnt;
+                if (r < b) before += cnt;
+                if (WALK && r < g0) bstart += cnt;
+                if (WALK && r >= g0 && r < g0 + gchunks) bcount += cnt;
             }
         }
         if (WALK && c < a.E) {

@@ -1170,12 +1170,16 @@ hipError_t launch_layout_dispatch(const LayoutArgs& a_in, const DispatchArgs& d,
     return hipGetLastError();
 }
 
-// Wavefronts of the extra workgroups of the layout kernel that read tokens.  All of them should be running from the
-// start, so that none reads its share as a tail: a compute unit holds 16 waves of this kernel (its registers) and
-// the layout workgroups take their places first, of 256 units.  Fewer leave the chunks' words to each other a freer
-// way (layout + read-ahead of 59 MB, 448 workgroups of 16 waves 14.8 us, 224 14.2, 192 13.9, 160 13.4; of 34 MB, with
-// rows cut by the capacity, 13.2, 11.4, 11.2, 11.6).
-constexpr int kWarmWaves = 192 * 16;
+// Extra workgroups of the layout kernel that read tokens: half as many as compute units, whatever their waves.  All of them and
+// the layout's own workgroups (up to 65 of one per unit, where their tables take more than half of its LDS) then run from the start
+// on units of their own.  Counted in waves, two-pass layouts had 384 of 8 waves: beside the chunks, or, with tables of 512
+// experts, half of them as a tail (layout alone, us, 192 or 384 workgroups / 128: 8192 tokens of 14 336 bytes, 256 experts, 16.8 / 13.9;
+// of 8192 bytes, 128 experts, 15.8 / 12.5, 512 experts 20.2 / 18.1; 6000 of 10 240, 1024 experts, 28.4 / 26.3; one pass, 4096 of
+// 14 336, 256 experts, 12.1 / 11.1; 64 workgroups 12.5).
+constexpr int kWarmBlocks = 128;
+// Wavefronts where the tokens are quantised ahead, which is bound by arithmetic (8192 tokens of 4096 channels, 256 experts, layout of
+// 22.7 us with 384 workgroups of 8 waves, 29.2 with 192; 512 experts, whose tables leave one workgroup per unit, 27.6 and 36.0).
+constexpr int kQuantWaves = 192 * 16;
 
 hipError_t launch_layout(const LayoutArgs& a_in, hipStream_t s) {
     LayoutArgs a = a_in;
@@ -1191,7 +1195,7 @@ hipError_t launch_layout(const LayoutArgs& a_in, hipStream_t s) {
     a.nchunks = nblk;
     const bool pf = layout_prefetches(a);
     const int nlay = nblk + (nblk > 1 ? 1 : 0);
-    const int nwarm = pf ? kWarmWaves / wpb : 0;
+    const int nwarm = !pf ? 0 : a.quant_out ? kQuantWaves / wpb : kWarmBlocks;
     const dim3 grid(nlay + nwarm), block(wpb * kWave);
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, cut.lds, s, a); };
     const int passes = cut.rows ? a.passes : 0;

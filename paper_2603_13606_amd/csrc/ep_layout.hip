@@ -168,7 +168,9 @@ struct LayoutCut {
     size_t lds;   // bytes
 };
 
-constexpr size_t kLdsLimit = 64 * 1024;   // of layout_chunk
+// Of layout_chunk: half of a compute unit's.  With 64 KiB the tables of the walk list took the workgroups of 1024 experts from 8 waves
+// to 4 (on 64 ranks) and 2 (on 128; layout of 8800 entries 30.3 us, now 17.0; 1024 ranks 109 and 47, without the list 92 and 41).
+constexpr size_t kLdsLimit = 80 * 1024;
 constexpr size_t kLdsUnit = 160 * 1024;   // of a compute unit: what a workgroup of layout_rows may take
 
 // group: wave-chunks per block of the walk list, 0 without one.  A wave keeps its entries in registers for up to PU passes;

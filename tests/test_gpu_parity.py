@@ -917,7 +917,8 @@ def test_dispatch_destination_order_parity(ep, hx, oracle_mod, name, T, H, mode,
     (8, 64, 1, 140001, 2048, 0, 0.0),      # the same with more passes than a wave keeps in registers
     (8, 64, 1, 8201, 16384, 150, 0.02),    # and with rows cut by the capacity, blocks in the middle of an expert's last ones
     (4, 24, 5, 40003, 64, 3000, 0.3),      # several passes, one block over all workgroups, many masked entries
-    (1024, 1024, 2, 4099, 72, 0, 0.01),    # tables that leave two waves per workgroup; over 32 workgroups look across
+    (1024, 1024, 2, 4099, 72, 0, 0.01),    # tables that leave four waves per workgroup; over 32 workgroups look across
+    (128, 1024, 8, 1100, 136, 0, 0.02),    # tables of 64 to 80 KiB: 8 waves with the list
     (8, 1000, 9, 1003, 136, 9, 0.05),
     (1, 1, 1, 8193, 128, 5000, 0.0),       # one expert takes every row, some are cut
     (2, 6, 3, 2731, 1096, 0, 1.0),         # nothing is routed

@@ -535,8 +535,9 @@ hipError_t launch_dispatch_fp8(const DispatchArgs& a, float* recv_scales, hipStr
     // Rows loaded late where the launch fills the 8192 waves that are resident at a time, or nearly: all of their stores would come at
     // once otherwise.  Dispatch with side arrays, us, early / late: 8000 waves of 1024 channels, top-8, 18.7/16.5, 8192
     // waves of 512 12.9/11.1, 8192 of 1024, top-2, 8.3/7.4; fewer waves, and shorter rows, are
-    // bound by the round trip: 7000 waves of 14 336-byte tokens 13.8/14.1, 3500 7.3/7.6, 30 000 of 256 channels 24.5/26.6.
-    const bool late = nwaves >= 7680 && a.H >= 512;
+    // bound by the round trip: 7000 waves of 14 336-byte tokens 13.8/14.1, 3500 7.3/7.6, 30 000 of 256 channels 24.5/26.6;
+    // so are the single rows of top-1 (11 700 waves of 512 channels 7.0/7.3).
+    const bool late = nwaves >= 7680 && a.H >= 512 && a.K > 1;
     if (late) hipLaunchKernelGGL(dispatch_fp8_kernel<true>, dim3((unsigned)nblk), dim3(256), 0, s, a, recv_scales, nseg);
     else hipLaunchKernelGGL(dispatch_fp8_kernel<false>, dim3((unsigned)nblk), dim3(256), 0, s, a, recv_scales, nseg);
     return hipGetLastError();

@@ -166,8 +166,7 @@ int64_t carve_slab(const ep_group_s* g, Slab* s, int32_t* base) {
     const int64_t o_rt = carve(&cur, R), o_ro = carve(&cur, R + 1);
     const int64_t o_h = carve(&cur, (int64_t)kMaxChunks * g->W), o_ctl = carve(&cur, kLayoutCtlWords);
     const bool walk = may_make_walk(g->cfg);
-    // a list is two words per entry; a slab that holds one has always had kMaxWaveChunks + 1 words per expert for its walk
-    const int64_t o_wk = walk ? carve(&cur, std::max<int64_t>(2 * (nB + kWalkPad), (int64_t)(kMaxWaveChunks + 1) * E)) : 0;
+    const int64_t o_wk = walk ? carve(&cur, 2 * (nB + kWalkPad)) : 0;
     const int64_t o_sl = carve(&cur, nB), o_dr = carve(&cur, nB), o_rr = carve(&cur, nB);
     const int64_t o_st = carve(&cur, nB), o_sk = carve(&cur, nB), o_sr = carve(&cur, nB), o_er = carve(&cur, nB);
     const bool dedup = g->cfg.dispatch_path == EP_PATH_RANK_DEDUP;

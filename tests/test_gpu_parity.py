@@ -1358,9 +1358,10 @@ def test_allocator_callbacks_and_lifecycle(ep, hx):
 
 
 @pytest.mark.parametrize("path", ["direct", "once"])
-def test_handles_hold_a_run_table_only_where_a_dispatch_can_read_it(ep, hx, path):
-    """What a handle takes, by the allocator callback: the table of run starts, 513 * E words, is part of it from
-    the smallest group that can dispatch in destination order on (8192 routed entries), in no other."""
+def test_handles_hold_a_walk_list_only_where_a_dispatch_can_read_it(ep, hx, path):
+    """What a handle takes, by the allocator callback: the walk list, two words per routed entry and the 32 places behind it
+    that a copy may read, is part of it from the smallest group that can dispatch in destination order on (8192
+    routed entries), in no other."""
     E, R, K = 64, 4, 8
     once = path == "once"
 
@@ -1382,9 +1383,10 @@ def test_handles_hold_a_run_table_only_where_a_dispatch_can_read_it(ep, hx, path
         assert not held and len(set(sizes[-3:])) == 1  # the slabs come last
         return sizes[-1]
     without = dict(H=2040, order=0) if once else dict(H=2048, order=0)
-    with_runs = dict(H=2048, order=0) if once else dict(H=2048, order=1)
-    assert slab_bytes(1023, **with_runs) == slab_bytes(1023, **without)
-    assert slab_bytes(1024, **with_runs) >= slab_bytes(1024, **without) + 513 * E * 4
+    with_list = dict(H=2048, order=0) if once else dict(H=2048, order=1)
+    assert slab_bytes(1023, **with_list) == slab_bytes(1023, **without)
+    for B in (1024, 4099):
+        assert slab_bytes(B, **with_list) == slab_bytes(B, **without) + -(-2 * (B * K + 32) // 64) * 64 * 4
 
 
 @pytest.mark.parametrize("nbytes", [16, 4096 + 16, (3 << 20) + 48, 17 * 4096 * 16 + 16 * 1023])

@@ -109,7 +109,6 @@ constexpr bool launch_fits(int slices, int rows) {  // with the side arrays of t
 struct WalkPlan {
     int piece;      // 16-byte units per slice
     int units;      // 16-byte units per row
-    int tpr_shift;  // log2(threads that share one row piece)
     int first, last;  // places of the walk list this launch covers
     int side_blocks;  // leading workgroups that fill the side arrays, a multiple of 8 (the dies stay aligned with the slices)
     int entries;      // routed entries of the input, at most
@@ -459,7 +458,7 @@ template <bool FP8>
 static void launch_walk(const DispatchArgs& a, const DispatchPlan& d, int units, int first, int last, const StagedRows& f,
                         hipStream_t s) {
     WalkPlan p;
-    p.piece = d.piece; p.units = units; p.tpr_shift = d.tpr_shift; p.first = first; p.last = last;
+    p.piece = d.piece; p.units = units; p.first = first; p.last = last;
     p.entries = a.T * a.K;
     p.side_blocks = first == 0 && (a.recv_w || a.recv_src) ? (int)side_workgroups(p.entries) : 0;
     switch (d.tpr_shift) {

@@ -70,7 +70,7 @@ struct LayoutArgs {
     int64_t* drop_hint;       // mapped host word or nullptr: gets kept | dropped << 32 (rows of padded windows)
     int2* walk;               // or nullptr: {token, row} of every entry that has a row, block of walk_group wave-chunks
                               // by block, within a block expert by expert, within an expert in entry order, no gaps
-    int walk_group;           // a multiple or a divisor of walk_waves
+    int walk_group;           // a multiple or a divisor of the wavefronts per workgroup
 };
 
 // Addressing of the receive windows: element offset of logical row r is
@@ -98,7 +98,11 @@ __device__ __forceinline__ int64_t window_offset(const WindowDesc& w, int row) {
 // The side arrays of one token's rows, by the wave of its first segment (`first`): lane k writes for
 // entry k, so that there is one store per array for all K rows.  Written row by row inside the copy
 // loop, each weight was loaded between two row stores, and the wait for it was a wait for the stores
-// before it (token walk, 3001 tokens of 5760 bytes, top-6: step of 56.8 us, now 55.7).  Returns the
+// before it.  Dispatch with side arrays, us, row by row / by lanes: token walk, 8 MB of rows, top-4 4.4/3.7, top-16 8.2/4.4, 1000 tokens of
+// 14 336 bytes, top-8, 26.0/25.0; FP8, 2000 tokens of 1024 channels 7.3/5.7; once per rank, 128 tokens of 14 336 bytes 7.6/6.6, 900
+// 41.4/39.8, 4096, top-2, 46.2/45.9, 8192 of 2048 53.1/52.5.  What the wait had also done was to keep the stores of a wave
+// apart: long token walks and FP8 walks that fill the card lost 5 to 12 % and have rules of their own for it now
+// (token_walk_reserve, launch_dispatch_fp8); the once-per-rank send lost nothing.  Returns the
 // lane's row, -1 if it lies outside the window.
 __device__ __forceinline__ int deliver_sides(const WindowDesc& win, float* recv_w, int32_t* recv_src, int32_t* totals,
                                              bool first, int my_row, float my_w, int t) {

@@ -26,8 +26,8 @@
 //   emit        slot = prefix of earlier chunks + in-chunk rank, the destination row,
 //               the expert-sorted entry list and the walk list.
 // The chunks wait for each other, so all of them must be resident at the same time:
-// there are at most 256 of them (64 when entries go by rows), no more than the part
-// has compute units, they are the lowest workgroup ids of the launch, and every
+// there are at most 256 of them (64 when entries go by rows) and one for the tables, the part has 256
+// compute units, they are the lowest workgroup ids of the launch, and every
 // wait gives up after a fixed number of polls (status bit, never a hang).
 // The work is latency bound (a chain of dependent LDS and global round trips per
 // wave), so every phase issues all of its global loads before it waits for any of
@@ -583,25 +583,7 @@ __device__ __forceinline__ void look_across(const LayoutArgs& a, int c, int r0, 
     }
 }
 
-// Chunk b = wave-chunks [b*wpb, (b+1)*wpb); with several chunks workgroup nchunks writes the
-// tables; the workgroups after those read tokens ahead.
-// With one chunk nothing is published or awaited.
-//
-// Cross-workgroup state (only with more than one chunk), all in a.pub / a.ctl:
-//   pub[r][c]  one word: (tag << 24) | entries of bin c in chunk r, tag = ctl[0] + 1 of the
-//              launch that wrote it; written once per launch with one atomic store, so a
-//              reader that sees the tag of its own launch also sees the count;
-//   ctl[0]     launches completed on this scratch since pub was last cleared (the
-//              generation, 0 .. 254); read at the start, advanced by the workgroup that is
-//              last to finish looking across, which clears pub when the tags run out;
-//   ctl[1]     workgroups of this launch that have finished looking across, in the low 16
-//              bits; a workgroup that gave up waiting also adds 1 << 16.  Back to 0 at the end.
-// Tags never repeat between two clearings of pub, and the scratch starts out all zero,
-// which no launch uses as a tag.
-//
-// HB: chunks whose published words a thread loads in one batch (at most 32: bit masks), 0 = there
-// is one chunk.  FUSED: the launch also dispatches.
-// The same workgroups, for a group that quantises ahead: instead of only reading the token
+// The extra workgroups for a group that quantises ahead: instead of only reading the token
 // rows they quantise them (the FP8 dispatch's format, see ep_fp8.h) into a staging copy, row t
 // at quant_out + t * quant_pitch: H bytes of codes, then H/128 float scales.  The quantising
 // dispatch that follows copies staged rows in destination order and finds them, like the
@@ -626,6 +608,25 @@ __device__ void quantize_tokens(const LayoutArgs& a, int wb, int nwb) {
     }
 }
 
+// Chunk b = wave-chunks [b*wpb, (b+1)*wpb); with several chunks workgroup nchunks writes the
+// tables; the workgroups after those read tokens ahead.
+// With one chunk nothing is published or awaited.
+//
+// Cross-workgroup state (only with more than one chunk), all in a.pub / a.ctl:
+//   pub[r][c]  one word: (tag << 24) | entries of bin c in chunk r, tag = ctl[0] + 1 of the
+//              launch that wrote it; written once per launch with one atomic store, so a
+//              reader that sees the tag of its own launch also sees the count;
+//   ctl[0]     launches completed on this scratch since pub was last cleared (the
+//              generation, 0 .. 254); read at the start, advanced by the workgroup that is
+//              last to finish looking across, which clears pub when the tags run out;
+//   ctl[1]     workgroups of this launch that have finished looking across, in the low 16
+//              bits; a workgroup that gave up waiting also adds 1 << 16.  Back to 0 at the end.
+// Tags never repeat between two clearings of pub, and the scratch starts out all zero,
+// which no launch uses as a tag.
+//
+// HB: chunks whose published words a thread loads in one batch (at most 32: bit masks), 0 = there
+// is one chunk.  FUSED: the launch also dispatches.  In three steps:
+//
 // (A) per bin: entries in earlier chunks and in all chunks, into LDS (and of the block of the walk list).  A batch of words is
 //     polled as a whole until every word of it carries this launch's tag (rows beyond the last
 //     chunk repeat its words, and the chunk's own word is among them: no exceptions to

@@ -1173,13 +1173,15 @@ hipError_t launch_layout_dispatch(const LayoutArgs& a_in, const DispatchArgs& d,
     return hipGetLastError();
 }
 
-// Extra workgroups of the layout kernel that read tokens: half as many as compute units, whatever their waves.  All of them and
-// the layout's own workgroups (up to 65 of one per unit, where their tables take more than half of its LDS) then run from the start
-// on units of their own.  Counted in waves, two-pass layouts had 384 of 8 waves: beside the chunks, or, with tables of 512
-// experts, half of them as a tail (layout alone, us, 192 or 384 workgroups / 128: 8192 tokens of 14 336 bytes, 256 experts, 16.8 / 13.9;
-// of 8192 bytes, 128 experts, 15.8 / 12.5, 512 experts 20.2 / 18.1; 6000 of 10 240, 1024 experts, 28.4 / 26.3; one pass, 4096 of
-// 14 336, 256 experts, 12.1 / 11.1; 64 workgroups 12.5).
-constexpr int kWarmBlocks = 128;
+// Extra workgroups of the layout kernel that read tokens.  All of them and the layout's own (33 of 16 waves up to 32 768 entries, 65 of
+// 8 or fewer beyond) run from the start, one per compute unit: a unit holds 16 waves of this kernel (its registers), and tables of
+// 512 experts take more than half of its LDS.  Layout alone, us, tokens in the memory-side cache / not (us there with the 384 that as
+// many waves of 8 per workgroup make; they share units with the chunks or, with large tables, half of them run as a tail):
+//   192 of 16 waves: 4096 tokens of 14 336 bytes, 256 experts, 12.1 / 12.7 (128 workgroups 11.1 / 14.4, 224 15.2 / 15.6)
+//   160 of 8: 8192 of 14 336 15.1 / 16.5 (384 16.9 / 16.9; 128 14.0 / 18.6; 192 16.5 / 20.9), 8192 of 8192, 128 experts,
+//   13.8 / 16.0 (384 15.4 / 15.8; 128 12.4 / 18.0), 512 experts 19.4 / 18.7 (384 20.2 / 21.1), 6000 of 10 240, 1024 experts,
+//   27.4 / 27.0 (384 28.4 / 28.7)
+constexpr int kWarmBlocks = 192, kWarmBlocksShort = 160;
 // Wavefronts where the tokens are quantised ahead, which is bound by arithmetic (8192 tokens of 4096 channels, 256 experts, layout of
 // 22.7 us with 384 workgroups of 8 waves, 29.2 with 192; 512 experts, whose tables leave one workgroup per unit, 27.6 and 36.0).
 constexpr int kQuantWaves = 192 * 16;
@@ -1198,7 +1200,7 @@ hipError_t launch_layout(const LayoutArgs& a_in, hipStream_t s) {
     a.nchunks = nblk;
     const bool pf = layout_prefetches(a);
     const int nlay = nblk + (nblk > 1 ? 1 : 0);
-    const int nwarm = !pf ? 0 : a.quant_out ? kQuantWaves / wpb : kWarmBlocks;
+    const int nwarm = !pf ? 0 : a.quant_out ? kQuantWaves / wpb : wpb == kLayoutWavesPerBlock ? kWarmBlocks : kWarmBlocksShort;
     const dim3 grid(nlay + nwarm), block(wpb * kWave);
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, cut.lds, s, a); };
     const int passes = cut.rows ? a.passes : 0;

@@ -532,11 +532,13 @@ hipError_t launch_dispatch_fp8(const DispatchArgs& a, float* recv_scales, hipStr
     if (nblk < 1) nblk = 1;
     if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
     // Rows loaded late where the launch fills the 8192 waves that are resident at a time, or nearly: all of their stores would come at
-    // once otherwise.  Dispatch with side arrays, us, early / late: 8000 waves of 1024 channels, top-8, 18.7/16.5, 8192
-    // waves of 512 12.9/11.1, 8192 of 1024, top-2, 8.3/7.4; fewer waves, and shorter rows, are
-    // bound by the round trip: 7000 waves of 14 336-byte tokens 13.8/14.1, 3500 7.3/7.6, 30 000 of 256 channels 24.5/26.6;
-    // so are the single rows of top-1 (11 700 waves of 512 channels 7.0/7.3).
-    const bool late = nwaves >= 7680 && a.H >= 512 && a.K > 1;
+    // once otherwise.  Dispatch, us, early / late: 8000 waves of 1024 channels, top-8, 18.7/16.5, 8192 waves of 512 12.9/11.1,
+    // 8192 of 1024, top-2, 8.3/7.4, 7800 of 1024 to 7168, top-4, 11.8/10.5.  Fewer waves are bound by the round trip (7000 of 7168
+    // channels 13.8/14.1, 3500 7.3/7.6), and so are single rows (11 700 of 512, top-1, 7.0/7.3) and short ones (30 000 of 256
+    // 24.5/26.6).  In longer launches the waves are apart by themselves: top-4 and more rows of 1 KiB still gain (15 600 waves, top-4,
+    // 21.3/20.7, 36 600 48.3/46.4, 30 000, top-8, 63.0/62.5), others lose (15 600 of 512, top-4, 13.1/13.9, 62 500, top-2, 30.7/34.0,
+    // 31 000 of 1024, top-2, 26.3/26.7).
+    const bool late = nwaves >= 7680 && (nwaves < 12288 ? a.K > 1 && a.H >= 512 : a.K >= 4 && a.H >= 1024);
     if (late) hipLaunchKernelGGL(dispatch_fp8_kernel<true>, dim3((unsigned)nblk), dim3(256), 0, s, a, recv_scales, nseg);
     else hipLaunchKernelGGL(dispatch_fp8_kernel<false>, dim3((unsigned)nblk), dim3(256), 0, s, a, recv_scales, nseg);
     return hipGetLastError();
